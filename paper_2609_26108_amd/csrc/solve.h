@@ -21,6 +21,31 @@ struct SolveParams {
 
 constexpr double kWarmWindow = 0.35;  // the polish may move theta_R this far [rad]
 
+// Newton steps below this end the iteration: it is quadratic, so the error
+// left is the square of the last step (times the curvature), far below the
+// rounding of the equations
+constexpr double kNewtonDone = 1e-10;
+
+// One Newton step of (h, ray angle - psi*) at (x, y); (sp, cp) = sine and
+// cosine of psi*.  `el`: theta_I stays 0 and only the direction equation is
+// solved.  *slope: d psi / d theta_R along h = 0 (`el`: along y = 0).
+__device__ __forceinline__ void newton_step(const Medium& m, int mode, int kernel, bool el,
+                                            double x, double y, double sp, double cp, double* dx,
+                                            double* dy, double* slope) {
+  const NewtonSys q = newton_sys(m, mode, kernel, trig_of(x, y), sp, cp);
+  if (el) {
+    *dx = -q.f2 / q.a21;
+    *dy = 0.0;
+    *slope = q.a21 / q.r2;
+    return;
+  }
+  const double det = q.a11 * q.a22 - q.a12 * q.a21;
+  const double inv = 1.0 / det;
+  *dx = -(q.a22 * q.f1 - q.a12 * q.f2) * inv;
+  *dy = -(q.a11 * q.f2 - q.a21 * q.f1) * inv;
+  *slope = -det / (q.a12 * q.r2);
+}
+
 // Newton on F = (h, psi - psi*) from the bracket interpolant.  Elastic modes
 // keep theta_I = 0 exactly and solve the 1D direction equation.
 __device__ __forceinline__ bool newton_root(const Medium& m, int mode, int kernel,
@@ -28,41 +53,23 @@ __device__ __forceinline__ bool newton_root(const Medium& m, int mode, int kerne
                                          double ya, double yb, double fa, double fb,
                                          int iters, double* xo, double* yo) {
   const bool el = theta_i_zero(m, mode);
-  const double eps = kFdEps;
   const double dth = tb - ta;
   double t = fa / (fa - fb);
   double x = ta + t * dth;
   double y = el ? 0.0 : ya + t * (yb - ya);
-  double last = 1.0;
+  double last = 1.0, sp, cp;
+  sincos(psi_star, &sp, &cp);
   for (int it = 0; it < iters; ++it) {
-    const Trig t0 = trig_of(x, y);
-    Vel v0 = energy_velocity_t(m, mode, kernel, t0);
-    double F2 = wrap_pi(ray_angle(v0) - psi_star);
-    double dx, dy = 0.0;
-    if (el) {
-      Vel vx = energy_velocity_t(m, mode, kernel, step_re(t0));
-      double d = dangle(v0, vx) / eps;
-      dx = -F2 / d;
-    } else {
-      double F1 = homog_residual(v0);
-      Vel vx = energy_velocity_t(m, mode, kernel, step_re(t0));
-      Vel vy = energy_velocity_t(m, mode, kernel, step_im(t0));
-      double J11 = (homog_residual(vx) - F1) / eps;
-      double J12 = (homog_residual(vy) - F1) / eps;
-      double J21 = dangle(v0, vx) / eps;
-      double J22 = dangle(v0, vy) / eps;
-      double det = J11 * J22 - J12 * J21;
-      dx = -(J22 * F1 - J12 * F2) / det;
-      dy = -(-J21 * F1 + J11 * F2) / det;
-    }
+    double dx, dy, slope;
+    newton_step(m, mode, kernel, el, x, y, sp, cp, &dx, &dy, &slope);
     if (!isfinite(dx) || !isfinite(dy)) return false;
     x += dx;
     y += dy;
     if (x < ta - dth || x > tb + dth || fabs(y) > 30.0 * kPi / 180.0) return false;
     last = fmax(fabs(dx), fabs(dy));
-    if (last < 1e-15) break;
+    if (last < kNewtonDone) break;
   }
-  if (!(last < 1e-12)) return false;
+  if (!(last < kNewtonDone)) return false;
   *xo = x;
   *yo = y;
   return true;
@@ -89,6 +96,36 @@ __device__ __forceinline__ bool bisect_root(const Medium& m, int mode, int kerne
   if (!theta_imag(m, mode, kernel, x, &y)) return false;
   *xo = x;
   *yo = y;
+  return true;
+}
+
+// Is y the theta_I that theta_imag's outward scan returns at theta_R = x?
+// No bracket of the residual closer to 0 on either side, the bracket
+// holding y on its side, none in the same step on the other side.
+__device__ __forceinline__ bool thi_is_nearest(const Medium& m, int mode, int kernel, double x,
+                                               double y) {
+  const int kr = (int)floor(fabs(y) / kThiStep);
+  if (kr >= kThiSteps || y == 0.0) return false;
+  double sr, cr;
+  sincos(x, &sr, &cr);
+  const double h0 = h_sign(m, mode, kernel, sr, cr, 0.0, 1.0);
+  if (h0 == 0.0) return false;
+  double hp_lo = h0, hn_hi = h0;
+  for (int k = 0; k <= kr; ++k) {
+    double hp_hi, hn_lo;  // the same evaluations as theta_imag's scan
+    h_scan_pair(m, mode, kernel, sr, cr, k, &hp_hi, &hn_lo);
+    const bool bp = brackets(hp_lo, hp_hi);
+    const bool bn = brackets(hn_lo, hn_hi);
+    if (k < kr) {
+      if (bp || bn) return false;
+    } else {
+      const bool mine = y > 0.0 ? bp : bn;
+      const bool other = y > 0.0 ? bn : bp;
+      if (!mine || other) return false;
+    }
+    hp_lo = hp_hi;
+    hn_hi = hn_lo;
+  }
   return true;
 }
 
@@ -148,7 +185,9 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
   // It must also lie in its own bracket (the bisection's interval), not
   // wander into a neighbouring one.
   if (ok) ok = x >= ta - 1e-12 && x <= tb + 1e-12;
-  if (ok && !el) {
+  // (y in the first bracket of the scan, alone there, is that answer without
+  // refining it; anything else is compared with the scan's own root.)
+  if (ok && !el && !thi_is_nearest(m, mode, a.kernel, x, y)) {
     double sx, cx, ys;
     sincos(x, &sx, &cx);
     ok = theta_imag_sc(m, mode, a.kernel, sx, cx, &ys) && fabs(ys - y) <= 1e-9;
@@ -267,72 +306,22 @@ __device__ __forceinline__ int32_t solve_dir(const SolveParams& a, const Medium&
 __device__ __forceinline__ bool warm_newton(const Medium& m, int mode, int kernel, bool el,
                                          double psi_star, double x0, double y0, double* xo,
                                          double* yo, double* slope) {
-  const double eps = kFdEps;
-  double x = x0, y = el ? 0.0 : y0, last = 1.0, sl = NAN;
+  double x = x0, y = el ? 0.0 : y0, last = 1.0, sl = NAN, sp, cp;
+  sincos(psi_star, &sp, &cp);
   for (int it = 0; it < 16; ++it) {
-    const Trig t0 = trig_of(x, y);
-    Vel v0 = energy_velocity_t(m, mode, kernel, t0);
-    double F2 = wrap_pi(ray_angle(v0) - psi_star);
-    double dx, dy = 0.0;
-    if (el) {
-      Vel vx = energy_velocity_t(m, mode, kernel, step_re(t0));
-      double dd = dangle(v0, vx) / eps;
-      dx = -F2 / dd;
-      sl = dd;
-    } else {
-      double F1 = homog_residual(v0);
-      Vel vx = energy_velocity_t(m, mode, kernel, step_re(t0));
-      Vel vy = energy_velocity_t(m, mode, kernel, step_im(t0));
-      double J11 = (homog_residual(vx) - F1) / eps;
-      double J12 = (homog_residual(vy) - F1) / eps;
-      double J21 = dangle(v0, vx) / eps;
-      double J22 = dangle(v0, vy) / eps;
-      double det = J11 * J22 - J12 * J21;
-      dx = -(J22 * F1 - J12 * F2) / det;
-      dy = -(-J21 * F1 + J11 * F2) / det;
-      sl = -det / J12;
-    }
+    double dx, dy;
+    newton_step(m, mode, kernel, el, x, y, sp, cp, &dx, &dy, &sl);
     if (!isfinite(dx) || !isfinite(dy)) return false;
     x += dx;
     y += dy;
     if (fabs(x - x0) > kWarmWindow || fabs(y) > 30.0 * kPi / 180.0) return false;
     last = fmax(fabs(dx), fabs(dy));
-    if (last < 1e-15) break;
+    if (last < kNewtonDone) break;
   }
-  if (!(last < 1e-12)) return false;
+  if (!(last < kNewtonDone)) return false;
   *xo = x;
   *yo = y;
   *slope = sl;
-  return true;
-}
-
-// Is y the theta_I that theta_imag's outward scan returns at theta_R = x?
-// No bracket of the residual closer to 0 on either side, the bracket
-// holding y on its side, none in the same step on the other side.
-__device__ __forceinline__ bool thi_is_nearest(const Medium& m, int mode, int kernel, double x,
-                                               double y) {
-  const int kr = (int)floor(fabs(y) / kThiStep);
-  if (kr >= kThiSteps || y == 0.0) return false;
-  double sr, cr;
-  sincos(x, &sr, &cr);
-  const double h0 = h_t(m, mode, kernel, sr, cr, 0.0, 1.0);
-  if (h0 == 0.0) return false;
-  double hp_lo = h0, hn_hi = h0;
-  for (int k = 0; k <= kr; ++k) {
-    double hp_hi, hn_lo;  // the same evaluations as theta_imag's scan
-    h_scan_pair(m, mode, kernel, sr, cr, k, &hp_hi, &hn_lo);
-    const bool bp = brackets(hp_lo, hp_hi);
-    const bool bn = brackets(hn_lo, hn_hi);
-    if (k < kr) {
-      if (bp || bn) return false;
-    } else {
-      const bool mine = y > 0.0 ? bp : bn;
-      const bool other = y > 0.0 ? bn : bp;
-      if (!mine || other) return false;
-    }
-    hp_lo = hp_hi;
-    hn_hi = hn_lo;
-  }
   return true;
 }
 

@@ -2,6 +2,7 @@
 // compiled on the host to count its floating-point operations.
 #pragma once
 #define __device__
+#define __constant__
 #define __host__
 #define __forceinline__ inline
 #define __all(x) (x)
