@@ -37,7 +37,8 @@ struct SweepArgs {
   int modes[3];
   int kernel;
   int n_sweep;
-  double2* table;  // [n_modes][n_classes][n_sweep] = (theta_I, psi); psi NaN: none
+  double2* table;  // [n_modes][n_classes][h] = (theta_I, psi); psi NaN: none
+                   // (h = sweep_stored(n_sweep): half the samples, or all)
 };
 
 __device__ __forceinline__ bool is_fluid_shear(const chert_class& c, int mode) {
@@ -55,28 +56,39 @@ __device__ __forceinline__ bool class_invalid(const chert_class& c) {
   return false;
 }
 
-__global__ void __launch_bounds__(256) k_sweep(SweepArgs a) {
-  int64_t total = (int64_t)a.n_modes * a.n_classes * a.n_sweep;
+__global__ void __launch_bounds__(64) k_sweep(SweepArgs a) {
+  const int h = sweep_stored(a.n_sweep);
+  int64_t total = (int64_t)a.n_modes * a.n_classes * h;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
        t += (int64_t)gridDim.x * blockDim.x) {
-    int j = (int)(t % a.n_sweep);
-    int64_t job = t / a.n_sweep;
+    int j = (int)(t % h);
+    int64_t job = t / h;
     int64_t k = job % a.n_classes;
     int mode = a.modes[job / a.n_classes];
     chert_class c = a.classes[k];
     double2 out = make_double2(0.0, NAN);
-    if (!class_invalid(c) && !is_fluid_shear(c, mode)) {
-      Medium m = load_medium(c);
-      double thR = (j + 0.5) * (kTwoPi / a.n_sweep);
-      double thI, sr, cr;
-      sincos(thR, &sr, &cr);
-      if (theta_imag_sc(m, mode, a.kernel, sr, cr, &thI)) {
-        double psi = ray_angle_sc(m, mode, a.kernel, sr, cr, thI);
-        if (isfinite(psi)) out = make_double2(thI, psi);
-      }
-    }
+    if (!class_invalid(c) && !is_fluid_shear(c, mode))
+      out = sweep_sample(load_medium(c), mode, a.kernel, a.n_sweep, j);
     a.table[t] = out;
   }
+}
+
+// A job's sweep table in LDS, filled by the whole workgroup: [h] samples,
+// then the chunk ranges.  Ends with a barrier.
+__host__ __device__ inline size_t sweep_lds(int n_sweep) {
+  return (size_t)sweep_stored(n_sweep) * sizeof(double2) +
+         (size_t)sweep_chunks(n_sweep) * 3 * sizeof(double);
+}
+template <class Sample>
+__device__ __forceinline__ SweepTable stage_sweep(double2* tab, int n_sweep, Sample sample) {
+  const int h = sweep_stored(n_sweep);
+  double* rng = reinterpret_cast<double*>(tab + h);
+  for (int j = threadIdx.x; j < h; j += blockDim.x) tab[j] = sample(j);
+  __syncthreads();
+  for (int c = threadIdx.x; c < sweep_chunks(n_sweep); c += blockDim.x)
+    sweep_range(tab, n_sweep, h, c, rng + 3 * c);
+  __syncthreads();
+  return SweepTable{tab, rng, n_sweep, h};
 }
 
 struct SolveArgs : SolveParams {
@@ -207,45 +219,48 @@ __device__ __forceinline__ int32_t class_block(const chert_class& c, int mode) {
   return 0;
 }
 
-// Two-launch path (few classes): one workgroup per (mode, class, 64
+// Two-launch path (few classes): one workgroup per (mode, class, chunk of
 // directions), sweep table from k_sweep staged in LDS.
-// Class caches: SPLIT lanes per target direction, 64 / SPLIT directions per
-// workgroup (SPLIT = 4 when there are too few directions to fill the
-// device, else 1).  Each lane scans its share of the sweep table for
-// brackets and refines them; the direction's first lane then folds the
-// roots in scan order (the plain search's choice, exactly), or, if a share
-// held more than kSolveSlots brackets, runs the serial search itself.
+// SPLIT lanes serve a target direction: 4 when there are too few directions
+// to fill the device (the time is then one lane's chain of brackets), else 1.
+// Each of them finds the direction's brackets and refines every SPLIT-th; the
+// direction's first lane then folds the roots in scan order (the plain
+// search's choice, exactly), or, where there were more than SPLIT *
+// kSolveSlots brackets, runs the serial search itself.
+// SPLIT 1: 256 threads share one staged table.
+// Bound by FP64 issue of the refinements (two wavefronts per SIMD, which
+// spills a few registers and still beats one without spills: 270 -> 206 us)
+// since the directions test chunk ranges instead of all 1440 intervals: the
+// 41,253-direction cache of 6 classes x 2 modes went from 2.17 ms to 0.23 ms,
+// the 5-class 2D cache from 117 to 70 us.
 constexpr int kSolveSlots = 3;
+constexpr int kSolveThreads = 256;
 struct SolveCand {
   Entry e;
   int32_t ok, ill;
 };
 template <int SPLIT>
-__global__ void __launch_bounds__(64) k_solve(SolveArgs a) {
-  constexpr int kSolveSplit = SPLIT, kSolveDirs = 64 / SPLIT;
-  extern __shared__ double2 tab[];
-  __shared__ SolveCand s_c[kSolveDirs][kSolveSplit * kSolveSlots];
-  __shared__ int s_nc[kSolveDirs][kSolveSplit];
-  __shared__ int s_over[kSolveDirs];
-  __shared__ int s_br[64 * kMaxBr];
-  const int chunks = (a.n_solve + kSolveDirs - 1) / kSolveDirs;
+__global__ void __launch_bounds__(SPLIT > 1 ? 64 : kSolveThreads) __attribute__((amdgpu_waves_per_eu(2)))
+k_solve(SolveArgs a) {
+  constexpr int kThreads = SPLIT > 1 ? 64 : kSolveThreads, kDirs = kThreads / SPLIT;
+  constexpr int kCand = SPLIT > 1 ? SPLIT * kSolveSlots : 1;
+  extern __shared__ double2 tab_lds[];
+  __shared__ SolveCand s_c[SPLIT > 1 ? kDirs : 1][kCand];
+  __shared__ int s_br[kThreads * kMaxBr];
+  const int chunks = (a.n_solve + kDirs - 1) / kDirs;
   const int64_t job = blockIdx.x / chunks;
   const int chunk = blockIdx.x % chunks;
   const int64_t k = job % a.n_classes;
   const int mode = a.modes[job / a.n_classes];
-  const double2* src = a.table + job * a.n_sweep;
-  for (int j = threadIdx.x; j < a.n_sweep; j += blockDim.x) tab[j] = src[j];
-  const int dl = threadIdx.x / kSolveSplit, q = threadIdx.x % kSolveSplit;
-  if (q == 0) s_over[dl] = 0;
-  __syncthreads();
-
-  const int sidx = chunk * kSolveDirs + dl;
+  const double2* src = a.table + job * sweep_stored(a.n_sweep);
+  const SweepTable tab = stage_sweep(tab_lds, a.n_sweep, [&](int j) { return src[j]; });
+  const int dl = threadIdx.x / SPLIT, q = threadIdx.x % SPLIT;
+  const int sidx = chunk * kDirs + dl;
   const bool valid = sidx < a.n_solve;
   const int64_t row = ((int64_t)mode * a.n_classes + k) * a.n_cols;
   const chert_class c = a.classes[k];
   const int32_t blocked = class_block(c, mode);
   const Medium m = load_medium(c);
-  const FullTable full{tab, a.n_sweep};
   double3 f = make_double3(0.0, 0.0, 0.0);
   int d = 0, col = 0, pcol = 0;
   double psi_star = 0.0;
@@ -258,46 +273,50 @@ __global__ void __launch_bounds__(64) k_solve(SolveArgs a) {
       psi_star = blocked ? 0.0 : dir_psi(a, d, m.tilt);
     }
   }
-  const bool el = theta_i_zero(m, mode);
-  if (valid && !blocked) {
-    // this lane's share of the bracket scan, then its roots
-    const int span = (a.n_sweep + kSolveSplit - 1) / kSolveSplit;
-    const int lo = q * span, hi = min(a.n_sweep, lo + span);
-    int brj[kSolveSlots];
-    int nb = 0;
-    for (int j = lo; j < hi; ++j) {
-      if (!is_bracket(full, j, a.n_sweep, psi_star)) continue;
-      if (nb < kSolveSlots) brj[nb] = j;
-      ++nb;
-    }
-    if (nb > kSolveSlots) s_over[dl] = 1;
-    const int nk = nb < kSolveSlots ? nb : kSolveSlots;
-    for (int b = 0; b < nk; ++b) {
-      SolveCand& sc = s_c[dl][q * kSolveSlots + b];
-      bool ill = false;
-      const int j = brj[b];
-      sc.ok = bracket_root(a, m, mode, j, tab[j], tab[j + 1 == a.n_sweep ? 0 : j + 1], psi_star,
-                           el, &sc.e, &ill) ? 1 : 0;
-      sc.ill = ill ? 1 : 0;
-    }
-    s_nc[dl][q] = nk;
-  }
-  __syncthreads();
-  if (!valid || q != 0) return;
   Entry best{};
   best.V = NAN;
   int32_t st = blocked;
-  if (!blocked) {
-    if (s_over[dl]) {
-      st = solve_dir(a, m, mode, full, psi_star, s_br + threadIdx.x * kMaxBr, &best);
-    } else {
-      bool found = false, ill = false;
-      for (int qq = 0; qq < kSolveSplit; ++qq)
-        for (int b = 0; b < s_nc[dl][qq]; ++b) {
-          const SolveCand& sc = s_c[dl][qq * kSolveSlots + b];
+  if constexpr (SPLIT == 1) {
+    if (valid && !blocked)
+      st = solve_dir(a, m, mode, tab, psi_star, s_br + threadIdx.x * kMaxBr, &best);
+    if (!valid) return;
+  } else {
+    const bool el = theta_i_zero(m, mode);
+    int nb = 0, mine = 0, brj[kSolveSlots];
+    if (valid && !blocked) {
+      tab.for_brackets(psi_star, [&](int j, double2, double2) {
+#pragma unroll
+        for (int b = 0; b < kSolveSlots; ++b)
+          if (nb == b * SPLIT + q) {
+            brj[b] = j;
+            mine = b + 1;
+          }
+        ++nb;
+      });
+#pragma unroll
+      for (int b = 0; b < kSolveSlots; ++b) {
+        if (b >= mine) break;
+        SolveCand& sc = s_c[dl][b * SPLIT + q];
+        bool ill = false;
+        const int j = brj[b];
+        sc.ok = bracket_root(a, m, mode, j, tab.at(j), tab.at(j + 1 == a.n_sweep ? 0 : j + 1),
+                             psi_star, el, &sc.e, &ill) ? 1 : 0;
+        sc.ill = ill ? 1 : 0;
+      }
+    }
+    __syncthreads();
+    if (!valid || q != 0) return;
+    if (!blocked) {
+      if (nb > kCand) {
+        st = solve_dir(a, m, mode, tab, psi_star, s_br + threadIdx.x * kMaxBr, &best);
+      } else {
+        bool found = false, ill = false;
+        for (int b = 0; b < nb; ++b) {
+          const SolveCand& sc = s_c[dl][b];
           if (sc.ok) fold_choice(sc.e, sc.ill != 0, psi_star, a.resid_tol, &found, &ill, &best);
         }
-      st = solve_status(found, ill, best);
+        st = solve_status(found, ill, best);
+      }
     }
   }
   if (a.dim == 3) {
@@ -311,10 +330,11 @@ __global__ void __launch_bounds__(64) k_solve(SolveArgs a) {
 // (mode, class) sweeps theta_R into LDS, then solves that class's
 // directions; no sweep table in HBM.
 constexpr int kNodeThreads = 256;
-__global__ void __launch_bounds__(kNodeThreads) k_build_fused(SolveArgs a, const int32_t* list,
+__global__ void __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)))
+k_build_fused(SolveArgs a, const int32_t* list,
                                                               const int32_t* list_len,
                                                               int64_t n_jobs) {
-  extern __shared__ double2 tab[];
+  extern __shared__ double2 tab_lds[];
   __shared__ int s_br[kNodeThreads * kMaxBr];
   const int64_t n = list ? (int64_t)*list_len : n_jobs;
   for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
@@ -335,24 +355,16 @@ __global__ void __launch_bounds__(kNodeThreads) k_build_fused(SolveArgs a, const
       continue;  // block-uniform
     }
     const Medium m = load_medium(c);
-    __syncthreads();  // the previous job's solves are done with tab
-    for (int j = threadIdx.x; j < a.n_sweep; j += blockDim.x) {
-      const double thR = (j + 0.5) * (kTwoPi / a.n_sweep);
-      double thI, sr, cr;
-      sincos(thR, &sr, &cr);
-      double2 out = make_double2(0.0, NAN);
-      if (theta_imag_sc(m, mode, a.kernel, sr, cr, &thI)) {
-        const double psi = ray_angle_sc(m, mode, a.kernel, sr, cr, thI);
-        if (isfinite(psi)) out = make_double2(thI, psi);
-      }
-      tab[j] = out;
-    }
+    __syncthreads();  // the previous job's solves are done with the table
+    for (int j = threadIdx.x; j < a.n_sweep; j += blockDim.x)
+      tab_lds[j] = sweep_sample(m, mode, a.kernel, a.n_sweep, j);
     __syncthreads();
+    const SweepTable tab{tab_lds, nullptr, a.n_sweep, a.n_sweep};
     for (int sidx = threadIdx.x; sidx < a.n_solve; sidx += blockDim.x) {
       int d, col, pcol;
       dir_cols(a, sidx, &d, &col, &pcol);
       Entry best{};
-      const int32_t st = solve_dir(a, m, mode, FullTable{tab, a.n_sweep}, dir_psi(a, d, m.tilt),
+      const int32_t st = solve_dir(a, m, mode, tab, dir_psi(a, d, m.tilt),
                                    s_br + threadIdx.x * kMaxBr, &best);
       store_pair(a, row, col, pcol, best, m.tilt, st);
     }
@@ -361,16 +373,21 @@ __global__ void __launch_bounds__(kNodeThreads) k_build_fused(SolveArgs a, const
 
 // MSPM's local tables (Algorithm 1): for each job -- a class -- a fresh
 // theta_R sweep into LDS, then one solve per target global ray angle.  No
-// cache and nothing kept between calls: every call pays for its sweeps.
+// cache and nothing kept between calls: every call pays for its sweeps.  A
+// round holds a few hundred jobs (the woken cells' corners), too few to fill
+// the device, so four wavefronts share a job's sweep (40 x 20 cells, one
+// source: 24.8 -> 4.6 ms with the halved sweep and the chunk ranges).
 // Outputs V, A and the status of each (job, target), with the status rules
 // of cache entries (NaN quantities where there is no usable root).
-__global__ void __launch_bounds__(64) k_mspm_solve(SolveArgs a, const int32_t* job_class,
+constexpr int kMspmThreads = 256;
+__global__ void __launch_bounds__(kMspmThreads) __attribute__((amdgpu_waves_per_eu(2)))
+k_mspm_solve(SolveArgs a, const int32_t* job_class,
                                                    const int32_t* n_jobs_dev, int n_jobs_mul,
                                                    int64_t n_jobs_fixed, const double* psi,
                                                    int n_tgt, double* V, double* A,
                                                    int32_t* st) {
-  extern __shared__ double2 tab[];
-  __shared__ int s_br[64 * kMaxBr];
+  extern __shared__ double2 tab_lds[];
+  __shared__ int s_br[kMspmThreads * kMaxBr];
   const int64_t n = n_jobs_dev ? (int64_t)(*n_jobs_dev) * n_jobs_mul : n_jobs_fixed;
   const int mode = a.modes[0];
   for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
@@ -389,22 +406,13 @@ __global__ void __launch_bounds__(64) k_mspm_solve(SolveArgs a, const int32_t* j
       continue;  // block-uniform
     }
     const Medium m = load_medium(c);
-    __syncthreads();  // the previous job's solves are done with tab
-    for (int j = threadIdx.x; j < a.n_sweep; j += blockDim.x) {
-      const double thR = (j + 0.5) * (kTwoPi / a.n_sweep);
-      double thI, sr, cr;
-      sincos(thR, &sr, &cr);
-      double2 out = make_double2(0.0, NAN);
-      if (theta_imag_sc(m, mode, a.kernel, sr, cr, &thI)) {
-        const double ps = ray_angle_sc(m, mode, a.kernel, sr, cr, thI);
-        if (isfinite(ps)) out = make_double2(thI, ps);
-      }
-      tab[j] = out;
-    }
-    __syncthreads();
+    __syncthreads();  // the previous job's solves are done with the table
+    const SweepTable tab = stage_sweep(tab_lds, a.n_sweep, [&](int j) {
+      return sweep_sample(m, mode, a.kernel, a.n_sweep, j);
+    });
     for (int t = threadIdx.x; t < n_tgt; t += blockDim.x) {
       Entry best{};
-      int32_t s = solve_dir(a, m, mode, FullTable{tab, a.n_sweep}, wrap_pi(psi[t] - m.tilt),
+      int32_t s = solve_dir(a, m, mode, tab, wrap_pi(psi[t] - m.tilt),
                             s_br + threadIdx.x * kMaxBr, &best);
       if ((s & (CHERT_ST_NO_BRACKET | CHERT_ST_FLUID)) || (s == CHERT_ST_NONPHYS && isnan(best.V))) {
         Vq[t] = NAN;
@@ -433,8 +441,8 @@ int enqueue_mspm_solve(const chert_class* classes_dev, int mode, int kernel, int
   so.newton_iters = 12;
   so.bisect_iters = 200;
   const unsigned g = (unsigned)(grid < 1 ? 1 : (grid > 65535 ? 65535 : grid));
-  CHERT_LAUNCH("k_mspm_solve", k_mspm_solve, dim3(g), dim3(64),
-               (size_t)n_sweep * sizeof(double2), s, so, job_class, n_jobs_dev, n_jobs_mul,
+  CHERT_LAUNCH("k_mspm_solve", k_mspm_solve, dim3(g), dim3(kMspmThreads),
+               sweep_lds(n_sweep), s, so, job_class, n_jobs_dev, n_jobs_mul,
                n_jobs_fixed, psi_dev, n_tgt, V, A, st);
   return CHERT_OK;
 }
@@ -598,7 +606,8 @@ __host__ __device__ inline int warm_jobs(int n_solve) {
   return j < kWarmSolveJobs ? j : kWarmSolveJobs;
 }
 
-__global__ void __launch_bounds__(kWarmSolveThreads) k_warm_solve(WarmArgs w, int64_t n_jobs) {
+__global__ void __launch_bounds__(kWarmSolveThreads) __attribute__((amdgpu_waves_per_eu(2)))
+k_warm_solve(WarmArgs w, int64_t n_jobs) {
   __shared__ double s_psi[kWarmSolveJobs][kProxyN];
   __shared__ uint32_t s_fold[kWarmSolveJobs][kFoldWords];
   __shared__ int s_all[kWarmSolveJobs], s_nflag[kWarmSolveJobs], s_rej[kWarmSolveJobs];
@@ -815,7 +824,10 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w) {
       // every bracket of every fold direction goes to the flat refinement
       // (k_warm_fold): one record per direction, its brackets contiguous in
       // scan order.  All lanes scan the table for one direction at a time.
-      const WindowTable tab{s_pos, s_ent, s_idx, nl};
+      const WindowTable tab{s_pos, s_ent};
+      const auto holds = [&](int j, double psi) {
+        return is_bracket(tab.at(j), tab.at(j + 1 == a.n_sweep ? 0 : j + 1), psi);
+      };
       for (int f = 0; f < nflag; ++f) {
         int d, col, pcol;
         const int sidx = s_flag[f];
@@ -824,7 +836,7 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w) {
         int nbr = 0;
         for (int base = 0; base < nl; base += 64)
           nbr += __popcll(__ballot(base + lane < nl &&
-                                   is_bracket(tab, s_idx[base + lane], a.n_sweep, psi_star)));
+                                   holds(s_idx[base + lane], psi_star)));
         int rec = 0, first = 0;
         if (lane == 0) {
           rec = atomicAdd(w.dir_len, 1);
@@ -840,7 +852,7 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w) {
         int q = first;
         for (int base = 0; base < nl; base += 64) {
           const bool br = base + lane < nl &&
-                          is_bracket(tab, s_idx[base + lane], a.n_sweep, psi_star);
+                          holds(s_idx[base + lane], psi_star);
           const unsigned long long mask = __ballot(br);
           if (br) {
             const int jj = s_idx[base + lane];
@@ -871,7 +883,8 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w) {
 // Fold directions across all window jobs, one lane each: refine the
 // direction's brackets in scan order and keep the plain search's choice
 // (the fold of refine_bracket), then store the entry and its copy.
-__global__ void __launch_bounds__(64) k_warm_fold(WarmArgs w) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_warm_fold(WarmArgs w) {
   const SolveArgs& a = w.so;
   const int64_t n = *w.dir_len < w.dir_cap ? *w.dir_len : w.dir_cap;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
@@ -1085,7 +1098,7 @@ __global__ void __launch_bounds__(64) k_warm3_solve(Warm3Args w, int64_t n_rows)
 __global__ void __launch_bounds__(64) k_warm3_plain(Warm3Args w) {
   __shared__ int s_br[64 * kMaxBr];
   const SolveArgs& a = w.so;
-  const int n = *w.fb_len;
+  const int n = *w.fb_len, h = sweep_stored(a.n_sweep);
   for (int64_t q0 = (int64_t)blockIdx.x * blockDim.x; q0 < n; q0 += (int64_t)gridDim.x * blockDim.x) {
     const int64_t q = q0 + threadIdx.x;
     if (q >= n) continue;
@@ -1098,7 +1111,7 @@ __global__ void __launch_bounds__(64) k_warm3_plain(Warm3Args w) {
     const Medium m = load_medium(c);
     const double3 f = fib_dir(a, s);
     Entry best{};
-    const int32_t st = solve_dir(a, m, mode, FullTable{a.table + job * a.n_sweep, a.n_sweep},
+    const int32_t st = solve_dir(a, m, mode, SweepTable{a.table + job * h, nullptr, a.n_sweep, h},
                                  polar_to_axis(f, c), s_br + threadIdx.x * kMaxBr, &best);
     store_single(a, ((int64_t)mode * a.n_classes + k) * a.n_cols + s,
                  3 * a.n_classes * (int64_t)a.n_cols, best, f, st);
@@ -1429,21 +1442,21 @@ static int build_cache(const chert_cache_desc* d, const chert_class* classes_dev
     sa.kernel = d->kernel;
     sa.n_sweep = d->n_sweep;
     sa.table = (double2*)workspace_dev;
-    int64_t total = jobs * d->n_sweep;
-    int64_t blocks = (total + 255) / 256;
+    int64_t total = jobs * sweep_stored(d->n_sweep);
+    int64_t blocks = (total + 63) / 64;
     if (blocks > 65536) blocks = 65536;
-    CHERT_LAUNCH("k_sweep", k_sweep, dim3((unsigned)blocks), dim3(256), 0, s, sa);
+    CHERT_LAUNCH("k_sweep", k_sweep, dim3((unsigned)blocks), dim3(64), 0, s, sa);
     // few directions (latency bound): 4 lanes share each direction's scan
     const bool split = jobs * ((so.n_solve + 63) / 64) < 1024;
-    const int per_wg = split ? 16 : 64;
+    const int per_wg = split ? 16 : kSolveThreads;
     const int64_t chunks = (so.n_solve + per_wg - 1) / per_wg;
     if (jobs * chunks > 0x7fffffffLL) return fail(CHERT_ERR_INVALID_ARG, "too many entries");
     if (split)
       CHERT_LAUNCH("k_solve", k_solve<4>, dim3((unsigned)(jobs * chunks)), dim3(64),
-                   (size_t)d->n_sweep * sizeof(double2), s, so);
+                   sweep_lds(d->n_sweep), s, so);
     else
-      CHERT_LAUNCH("k_solve", k_solve<1>, dim3((unsigned)(jobs * chunks)), dim3(64),
-                   (size_t)d->n_sweep * sizeof(double2), s, so);
+      CHERT_LAUNCH("k_solve", k_solve<1>, dim3((unsigned)(jobs * chunks)), dim3(kSolveThreads),
+                   sweep_lds(d->n_sweep), s, so);
   }
   enqueue_cache_stats(d, n_classes, cache, lay, nullptr, 0, s);
   return launch_status();
@@ -1528,9 +1541,9 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
       sa.kernel = d->kernel;
       sa.n_sweep = d->n_sweep;
       sa.table = table;
-      const int64_t total = jobs * d->n_sweep;
-      const int64_t sb = (total + 255) / 256 > 65536 ? 65536 : (total + 255) / 256;
-      CHERT_LAUNCH("k_sweep", k_sweep, dim3((unsigned)sb), dim3(256), 0, s, sa);
+      const int64_t total = jobs * sweep_stored(d->n_sweep);
+      const int64_t sb = (total + 63) / 64 > 65536 ? 65536 : (total + 63) / 64;
+      CHERT_LAUNCH("k_sweep", k_sweep, dim3((unsigned)sb), dim3(64), 0, s, sa);
       CHERT_LAUNCH("k_warm3_folds", k_warm3_folds, dim3((unsigned)jobs), dim3(64), 0, s, w);
       CHERT_LAUNCH("k_warm3_predict", k_warm3_predict,
                    dim3((unsigned)((rows + mlp::kInferRows - 1) / mlp::kInferRows)),

@@ -133,30 +133,131 @@ __device__ __forceinline__ double ang_dist(double a, double b) { return fabs(wra
 
 constexpr int kMaxBr = 6;  // brackets kept per lane for the lockstep refinement
 
-// Sweep tables as solve_dir reads them: (theta_I, ray angle) of sample j,
-// NaN angle where the sample has no root.  A full table holds every sample;
-// a windowed one holds the marked samples in ascending order (slot q is
-// sample idx[q], pos[j] is the slot of sample j or -1) and reads every other
-// sample as NaN.  count()/sample(q) enumerate the samples that can open a
-// bracket, in ascending order.
-struct FullTable {
-  const double2* t;
-  int n;
-  __device__ __forceinline__ double2 at(int j) const { return t[j]; }
-  __device__ __forceinline__ int count() const { return n; }
-  __device__ __forceinline__ int sample(int q) const { return q; }
+// does the sweep interval with end points sa, sb hold the target angle?
+__device__ __forceinline__ bool is_bracket(double2 sa, double2 sb, double psi_star) {
+  if (isnan(sa.y) || isnan(sb.y)) return false;
+  double fa = wrap_pi(sa.y - psi_star);
+  double fb = wrap_pi(sb.y - psi_star);
+  if (fabs(fb - fa) >= kPi) return false;  // the +-pi seam, not a crossing
+  return brackets(fa, fb);
+}
+
+// Sweep tables: (theta_I, ray angle) of theta_R sample j, NaN angle where
+// the sample has no root.
+//
+// The sweep of a class.  v(theta_R + pi) = -v(theta_R), so with an even
+// number of samples only the first half is solved and stored (h = n / 2):
+// sample j + h has the same theta_I and the ray angle turned by pi.
+// With `rng` the samples are grouped in chunks of kSweepChunk intervals, each
+// with the range of ray angles it spans (base, lowest and highest offset from
+// it): a target tests 2 h / kSweepChunk ranges and then the intervals of the
+// one or two chunks that hold it, instead of all n intervals.  (An odd chunk
+// length: lanes reading different chunks then fall on different LDS banks.)
+constexpr int kSweepChunk = 15;
+__host__ __device__ inline int sweep_stored(int n) { return (n & 1) ? n : n / 2; }
+__host__ __device__ inline int sweep_chunks(int n) {
+  return (sweep_stored(n) + kSweepChunk - 1) / kSweepChunk;
+}
+
+__device__ __forceinline__ double2 sweep_at(const double2* t, int h, int j) {
+  if (j < h) return t[j];
+  const double2 v = t[j - h];
+  return make_double2(v.x, wrap_pi(v.y + kPi));
+}
+
+struct SweepTable {
+  const double2* t;   // [h]
+  const double* rng;  // [chunks][3], or null: every interval is tested
+  int n, h;
+  __device__ __forceinline__ double2 at(int j) const { return sweep_at(t, h, j); }
+  // f(j, sample j, sample j + 1) for every interval j holding psi, ascending
+  template <class Fn>
+  __device__ __forceinline__ void for_brackets(double psi, Fn&& f) const {
+    if (!rng) {
+      scan(0, n, psi, f);
+      return;
+    }
+    const int nc = (h + kSweepChunk - 1) / kSweepChunk;
+    for (int j0 = 0; j0 < n; j0 += h) {
+      const double tgt = j0 ? wrap_pi(psi - kPi) : psi;
+      for (int c0 = 0; c0 < nc; c0 += 64) {
+        // the chunks that may hold the target first, so that the lanes of a
+        // wavefront then walk their own chunks side by side
+        const int nw = nc - c0 < 64 ? nc - c0 : 64;
+        unsigned long long hit = 0ull;
+        for (int q = 0; q < nw; ++q) {
+          const double* r = rng + 3 * (c0 + q);
+          const double d = wrap_pi(tgt - r[0]);
+          if (d >= r[1] && d <= r[2]) hit |= 1ull << q;
+        }
+        while (hit) {
+          const int c = c0 + __builtin_ctzll(hit);
+          hit &= hit - 1ull;
+          const int lo = c * kSweepChunk;
+          scan(j0 + lo, j0 + (lo + kSweepChunk < h ? lo + kSweepChunk : h), psi, f);
+        }
+      }
+    }
+  }
+  template <class Fn>
+  __device__ __forceinline__ void scan(int lo, int hi, double psi, Fn&& f) const {
+    double2 sa = at(lo);
+    for (int j = lo; j < hi; ++j) {
+      const double2 sb = at(j + 1 == n ? 0 : j + 1);
+      if (is_bracket(sa, sb, psi)) f(j, sa, sb);
+      sa = sb;
+    }
+  }
 };
+
+// The range of chunk c of a stored sweep: base angle, lowest and highest
+// offset (widened by far more than the rounding of the sums).  A chunk with a
+// missing sample, or spanning more than 3 rad, is always searched.
+__device__ __forceinline__ void sweep_range(const double2* t, int n, int h, int c, double* r) {
+  const int lo = c * kSweepChunk, hi = lo + kSweepChunk < h ? lo + kSweepChunk : h;
+  double prev = t[lo].y, off = 0.0, mn = 0.0, mx = 0.0;
+  r[0] = prev;
+  bool all = isnan(prev);
+  for (int j = lo; j < hi; ++j) {
+    const double y = sweep_at(t, h, j + 1 == n ? 0 : j + 1).y;
+    all = all || isnan(y);
+    off = off + wrap_pi(y - prev);
+    mn = fmin(mn, off);
+    mx = fmax(mx, off);
+    prev = y;
+  }
+  if (all || mx - mn > 3.0) {
+    r[0] = 0.0;
+    mn = -4.0;
+    mx = 4.0;
+  }
+  r[1] = mn - 1e-9;
+  r[2] = mx + 1e-9;
+}
+
+// One theta_R sample of a class's sweep.
+__device__ __forceinline__ double2 sweep_sample(const Medium& m, int mode, int kernel, int n_sweep,
+                                                int j) {
+  const double thR = (j + 0.5) * (kTwoPi / n_sweep);
+  double thI, sr, cr;
+  sincos(thR, &sr, &cr);
+  if (theta_imag_sc(m, mode, kernel, sr, cr, &thI)) {
+    const double psi = ray_angle_sc(m, mode, kernel, sr, cr, thI);
+    if (isfinite(psi)) return make_double2(thI, psi);
+  }
+  return make_double2(0.0, NAN);
+}
+
+// A windowed table holds the marked samples in ascending order (slot q is
+// sample idx[q], pos[j] is the slot of sample j or -1) and reads every other
+// sample as NaN.
 struct WindowTable {
   const int16_t* pos;
   const double2* ent;
-  const int16_t* idx;
-  int nl;
   __device__ __forceinline__ double2 at(int j) const {
     const int p = pos[j];
     return p < 0 ? make_double2(0.0, NAN) : ent[p];
   }
-  __device__ __forceinline__ int count() const { return nl; }
-  __device__ __forceinline__ int sample(int q) const { return idx[q]; }
 };
 
 // Refine the bracket starting at sweep sample j and fold the root into the
@@ -236,15 +337,6 @@ __device__ __forceinline__ void refine_bracket_at(const SolveParams& a, const Me
     fold_choice(cand, cand_ill, psi_star, a.resid_tol, found, ill, best);
 }
 
-template <class T>
-__device__ __forceinline__ void refine_bracket(const SolveParams& a, const Medium& m,
-                                               int mode,
-                                               const T& tab, int j, double psi_star, bool el,
-                                               bool* found, bool* ill, Entry* best) {
-  refine_bracket_at(a, m, mode, j, tab.at(j), tab.at(j + 1 == a.n_sweep ? 0 : j + 1), psi_star,
-                    el, found, ill, best);
-}
-
 // status of a solved direction from the folded choice (as the plain search)
 __device__ __forceinline__ int32_t solve_status(bool found, bool ill, const Entry& best) {
   if (!found) return CHERT_ST_NO_BRACKET;
@@ -253,49 +345,36 @@ __device__ __forceinline__ int32_t solve_status(bool found, bool ill, const Entr
   return st;
 }
 
-template <class T>
-__device__ __forceinline__ bool is_bracket(const T& tab, int j, int n, double psi_star) {
-  double2 sa = tab.at(j);
-  double2 sb = tab.at(j + 1 == n ? 0 : j + 1);
-  if (isnan(sa.y) || isnan(sb.y)) return false;
-  double fa = wrap_pi(sa.y - psi_star);
-  double fb = wrap_pi(sb.y - psi_star);
-  if (fabs(fb - fa) >= kPi) return false;  // the +-pi seam, not a crossing
-  return brackets(fa, fb);
-}
-
-// Solve target direction d for one (class, mode) from its sweep table in
-// LDS.  Lanes of a wavefront run it in step (brackets first, then the
+// Solve target direction psi_star for one (class, mode) from its sweep
+// table.  Lanes of a wavefront run it in step (brackets first, then the
 // refinements together); `br` is this lane's kMaxBr bracket slots in LDS.
-template <class T>
-__device__ __forceinline__ int32_t solve_dir(const SolveParams& a, const Medium& m,
-                                             int mode,
-                                             const T& tab, double psi_star, int* br,
+__device__ __forceinline__ int32_t solve_dir(const SolveParams& a, const Medium& m, int mode,
+                                             const SweepTable& tab, double psi_star, int* br,
                                              Entry* best) {
   const bool el = theta_i_zero(m, mode);
   // phase 1: every sign change of the ray-direction miss over the sweep
   int nbr = 0;
-  for (int q = 0; q < tab.count(); ++q) {
-    const int j = tab.sample(q);
-    if (!is_bracket(tab, j, a.n_sweep, psi_star)) continue;
+  tab.for_brackets(psi_star, [&](int j, double2, double2) {
     if (nbr < kMaxBr) br[nbr] = j;
     ++nbr;
-  }
+  });
   // phase 2: refine the kept brackets with all lanes in step
   bool found = false, ill = false;
   for (int sidx = 0; sidx < kMaxBr; ++sidx) {
     if (__all(sidx >= nbr)) break;
-    if (sidx < nbr) refine_bracket(a, m, mode, tab, br[sidx], psi_star, el, &found, &ill, best);
+    if (sidx < nbr) {
+      const int j = br[sidx];
+      refine_bracket_at(a, m, mode, j, tab.at(j), tab.at(j + 1 == a.n_sweep ? 0 : j + 1),
+                        psi_star, el, &found, &ill, best);
+    }
   }
   // rare: more brackets than slots; refine the rest in scan order
   if (nbr > kMaxBr) {
     int seen = 0;
-    for (int q = 0; q < tab.count(); ++q) {
-      const int j = tab.sample(q);
-      if (!is_bracket(tab, j, a.n_sweep, psi_star)) continue;
-      if (seen++ < kMaxBr) continue;
-      refine_bracket(a, m, mode, tab, j, psi_star, el, &found, &ill, best);
-    }
+    tab.for_brackets(psi_star, [&](int j, double2 sa, double2 sb) {
+      if (seen++ < kMaxBr) return;
+      refine_bracket_at(a, m, mode, j, sa, sb, psi_star, el, &found, &ill, best);
+    });
   }
   return solve_status(found, ill, *best);
 }

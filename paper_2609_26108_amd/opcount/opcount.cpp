@@ -156,23 +156,18 @@ int main() {
     sp.newton_iters = 12;
     sp.bisect_iters = 200;
     std::vector<double2> tab((size_t)n_sweep);
+    std::vector<F> rng(3 * (size_t)sweep_chunks(n_sweep));
     long long sw_fl = 0, sw_tr = 0, so_fl = 0, so_tr = 0, n_dir = 0, wa_fl = 0, wa_tr = 0;
     long long n_warm = 0, n_warm_ok = 0;
     for (const chert_class& c : cls) {
       const Medium m = load_medium(c);
       const int mode = mode_sel;
       take();
-      for (int j = 0; j < n_sweep; ++j) {  // as k_sweep / k_build_fused
-        const F thR = (j + 0.5) * (kTwoPi / n_sweep);
-        F thI, sr, cr;
-        sincos(thR, &sr, &cr);
-        double2 out = make_double2(0.0, NAN);
-        if (theta_imag_sc(m, mode, sp.kernel, sr, cr, &thI)) {
-          const F ps = ray_angle_sc(m, mode, sp.kernel, sr, cr, thI);
-          if (isfinite(ps)) out = make_double2(thI, ps);
-        }
-        tab[j] = out;
-      }
+      const int h = sweep_stored(n_sweep);
+      for (int j = 0; j < h; ++j)  // as k_sweep / k_build_fused
+        tab[j] = sweep_sample(m, mode, sp.kernel, n_sweep, j);
+      for (int c2 = 0; c2 < sweep_chunks(n_sweep); ++c2)
+        sweep_range(tab.data(), n_sweep, h, c2, &rng[3 * c2]);
       opc::Counts cs = take();
       sw_fl += cs.flops;
       sw_tr += cs.trans;
@@ -182,7 +177,8 @@ int main() {
         Entry best{};
         take();
         const F psi = wrap_pi(d * (kTwoPi / n_dirs) - m.tilt);
-        const int32_t st = solve_dir(sp, m, mode, FullTable{tab.data(), n_sweep}, psi, br, &best);
+        const int32_t st = solve_dir(sp, m, mode, SweepTable{tab.data(), rng.data(), n_sweep, h},
+                                     psi, br, &best);
         opc::Counts c1 = take();
         so_fl += c1.flops;
         so_tr += c1.trans;
