@@ -60,9 +60,6 @@ constexpr int kFlagSeed = 4;    // first visit of the source tile: push the sour
 // neighbour at (sx, sz) changed, so the nodes within R of that side re-pull
 constexpr int kSideShift = 3;
 constexpr int kPullGroup = 8;  // offsets per item of a tile's distributed pull
-// LDS class ids of halo cells carry this bit (push targets must be interior)
-constexpr int32_t kHaloBit = 0x40000000;
-constexpr int32_t kClassMask = 0x3fffffff;
 
 struct JobDev {
   int nx, nz;     // nodes (nx * nz < 2^31)
@@ -149,6 +146,8 @@ struct RelaxArgs {
   const int32_t* oz;
   int32_t* flags;    // [2][n_tiles]
   int32_t* list;     // [2][n_tiles] tiles active in a round (by round parity)
+  const int32_t* tile_prob;  // [n_tiles] problem of each tile
+  uint32_t lw_magic;  // ceil(2^32 / lw): q / lw = umulhi(q, lw_magic) for LDS cells q
   int32_t* counter;  // [max_rounds + 2] tiles active in each round
   uint32_t* tick;    // [2][kTickWords] work tickets of the per-round list walk, by round parity
   int32_t* err;      // out-of-range class ids seen
@@ -352,9 +351,13 @@ __global__ void k_check_classes(const int32_t* cls, int64_t n, int K, int32_t* e
 }
 
 // blockIdx.y = problem; x strides over its nodes
-__global__ void k_init_fields(const ProbDev* probs, const JobDev* jobs, const int32_t* err) {
+__global__ void k_init_fields(const ProbDev* probs, const JobDev* jobs, const int32_t* err,
+                              int32_t* tile_prob) {
   if (*err) return;  // bad class map: outputs stay untouched
   const ProbDev pr = probs[blockIdx.y];
+  const int n_tiles = jobs[pr.job].ntx * jobs[pr.job].ntz;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n_tiles; t += gridDim.x * blockDim.x)
+    tile_prob[pr.tile_base + t] = blockIdx.y;
   const int64_t n = (int64_t)jobs[pr.job].nx * jobs[pr.job].nz;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n;
        j += (int64_t)gridDim.x * blockDim.x) {
@@ -403,8 +406,8 @@ struct TileCtx {
   int active;    // flag bits (0 = not active this round)
 };
 
-// Claim this workgroup's (problem, tile) for the round: find the problem by
-// binary search over the tile bases, read and clear the tile's flag.
+// Claim this workgroup's (problem, tile) for the round: read and clear the
+// tile's flag, look the problem up.
 __device__ __forceinline__ double key_delta(const RelaxArgs& a, int phase, int field) {
   if (phase == 1) return a.bucket;  // hop counts
   const double w = a.wmin[field];
@@ -419,14 +422,9 @@ __device__ __forceinline__ TileCtx tile_begin(const RelaxArgs& a, int round, int
   int32_t* fin = a.flags + (int64_t)(round & 1) * a.n_tiles;
   if (threadIdx.x == 0) {
     int32_t f = fin[T];
+    const int lo = a.tile_prob[T];  // in flight with the flag
     if (f) {
       fin[T] = 0;
-      int lo = 0, hi = a.n_prob - 1;
-      while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (a.probs[mid].tile_base <= T) lo = mid;
-        else hi = mid - 1;
-      }
       *s_prob = lo;
       if (a.bucket > 0.0) {
         unsigned long long* kin = a.key + (int64_t)(round & 1) * a.n_tiles;
@@ -479,38 +477,39 @@ __device__ __forceinline__ int border_bits(int x, int z, int tx, int tz, int R) 
   return m;
 }
 
+// Wake the tiles of `mask` for the next round; the first wavefront of the
+// workgroup calls it, lane b serving neighbour b, so the flags' device-wide
+// round trips overlap (one lane walking the neighbours waited for up to
+// eight of them in a row).
 __device__ __forceinline__ void activate(const RelaxArgs& a, int round, const TileCtx& c,
                                          const ProbDev& pr, const JobDev& jb, int mask,
                                          unsigned long long key) {
-  int32_t* fout = a.flags + (int64_t)((round + 1) & 1) * a.n_tiles;
-  if (a.bucket > 0.0) {
-    // this tile again (iteration cap): key 0 keeps it in the next round
-    if (mask & (1 << 4)) key = 0ull;
+  const int64_t out = (int64_t)((round + 1) & 1) * a.n_tiles;
+  const int bit = threadIdx.x;
+  // this tile again (iteration cap): key 0 keeps it in the next round
+  if (a.bucket > 0.0 && (mask & (1 << 4))) key = 0ull;
+  if (a.bucket > 0.0 && bit == 0)
     atomicMin(&a.pmin[((round + 1) % 3) * a.n_prob + c.p], key);
-  }
-  // set the flags, then reserve list slots for the newly activated tiles
-  // with one atomic (the counter is one address for the whole chip)
-  int fresh = 0;
-  for (int bit = 0; bit < 9; ++bit) {
-    if (!(mask & (1 << bit))) continue;
-    int dx = bit % 3 - 1, dz = bit / 3 - 1;
-    int nx_ = c.tx + dx, nz_ = c.tz + dz;
-    if (nx_ < 0 || nx_ >= jb.ntx || nz_ < 0 || nz_ >= jb.ntz) continue;
-    int32_t* f = &fout[pr.tile_base + nz_ * jb.ntx + nx_];
+  const int nx_ = c.tx + bit % 3 - 1, nz_ = c.tz + bit / 3 - 1;
+  const bool on = bit < 9 && ((mask >> bit) & 1) && nx_ >= 0 && nx_ < jb.ntx && nz_ >= 0 &&
+                  nz_ < jb.ntz;
+  bool fresh = false;
+  const int T = pr.tile_base + nz_ * jb.ntx + nx_;
+  if (on) {
     // the neighbour's halo facing us, i.e. its side (-dx, -dz), changed
     const int32_t bits =
         (bit == 4) ? (kFlagActive | kFlagFull) : (kFlagActive | (1 << (kSideShift + 8 - bit)));
-    if (a.bucket > 0.0)
-      atomicMin(&a.key[(int64_t)((round + 1) & 1) * a.n_tiles + pr.tile_base + nz_ * jb.ntx + nx_],
-                key);
-    if (atomicOr(f, bits) == 0) fresh |= 1 << bit;
+    if (a.bucket > 0.0) atomicMin(&a.key[out + T], key);
+    fresh = atomicOr(&a.flags[out + T], bits) == 0;
   }
-  if (!fresh) return;
-  int slot = atomicAdd(&a.counter[round + 1], __popc(fresh));
-  for (int bit = 0; bit < 9; ++bit)
-    if (fresh & (1 << bit))
-      a.list[(int64_t)((round + 1) & 1) * a.n_tiles + slot++] =
-          pr.tile_base + (c.tz + bit / 3 - 1) * jb.ntx + (c.tx + bit % 3 - 1);
+  // list slots for the newly activated tiles with one atomic (the counter
+  // is one address for the whole chip)
+  const unsigned long long fm = __ballot(fresh);
+  if (!fm) return;
+  int slot = 0;
+  if (bit == 0) slot = atomicAdd(&a.counter[round + 1], __popcll(fm));
+  slot = __shfl(slot, 0);
+  if (fresh) a.list[out + slot + __popcll(fm & ((1ull << bit) - 1ull))] = T;
 }
 
 // Smallest pending key of each problem for round + 2 starts over (round
@@ -523,12 +522,11 @@ __device__ __forceinline__ void reset_pmin(const RelaxArgs& a, int round) {
 
 struct Smem {
   double* val;    // [lw*lh] field values
-  int32_t* cls;   // [lw*lh] class ids (| kHaloBit in the halo); -1 outside, -2 bad id
-  int32_t* off;   // [n_off] LDS offsets of the star
   double* W;      // staged class-pair table
-  int32_t* l0;    // frontier buffers (interior LDS indices)
-  int32_t* l1;
-  int32_t* inq;   // [lw*lh] 1 while queued
+  int32_t* cls;   // [lw*lh] class ids; -1 outside the grid, -2 bad id
+  int32_t* off;   // [n_off] LDS offsets of the star
+  int32_t* list;  // frontier (interior LDS indices)
+  uint8_t* mark;  // [lw*lh] lowered at this level
 };
 
 __device__ __forceinline__ Smem carve(const RelaxArgs& a, void* base) {
@@ -541,43 +539,35 @@ __device__ __forceinline__ Smem carve(const RelaxArgs& a, void* base) {
   p += sizeof(double) * a.w_lds_doubles;
   s.cls = (int32_t*)p;
   p += sizeof(int32_t) * n;
-  s.inq = (int32_t*)p;
-  p += sizeof(int32_t) * n;
   s.off = (int32_t*)p;
   p += sizeof(int32_t) * ((a.n_off + 1) & ~1);
-  s.l0 = (int32_t*)p;
+  s.list = (int32_t*)p;
   p += sizeof(int32_t) * a.tx * a.tz;
-  s.l1 = (int32_t*)p;
+  s.mark = (uint8_t*)p;
   return s;
 }
 
 static size_t lds_bytes(int lw, int lh, int w_doubles, int n_off, int tx, int tz) {
   const size_t n = (size_t)lw * lh;
-  return sizeof(double) * (n + w_doubles) + sizeof(int32_t) * 2 * n +
-         sizeof(int32_t) * ((n_off + 1) & ~1) + sizeof(int32_t) * 2 * tx * tz;
+  return sizeof(double) * (n + w_doubles) + sizeof(int32_t) * n +
+         sizeof(int32_t) * ((n_off + 1) & ~1) + sizeof(int32_t) * tx * tz + ((n + 7) & ~(size_t)7);
 }
 
-// Stage class ids and star offsets of tile + halo.
-__device__ __forceinline__ void load_common(const RelaxArgs& a, const TileCtx& c, const JobDev& jb,
-                                            int32_t* cls, int32_t* inq, int32_t* off) {
-  const int R = a.R, lw = a.lw, n = lw * a.lh;
-  for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    int gx = c.x0 + (q % lw) - R, gz = c.z0 + (q / lw) - R;
-    int32_t k = -1;
-    if (gx >= 0 && gx < jb.nx && gz >= 0 && gz < jb.nz) {
-      k = jb.per_node ? 0 : jb.class_id[(int64_t)gx + (int64_t)jb.nx * gz];
-      if (k < 0 || k >= jb.K) {
-        atomicAdd(a.err, 1);
-        k = -2;
-      } else {
-        const int lx = q % lw - R, lz = q / lw - R;
-        if (lx < 0 || lx >= c.txe || lz < 0 || lz >= c.tze) k |= kHaloBit;
-      }
-    }
-    cls[q] = k;
-    inq[q] = 0;
-  }
-  for (int o = threadIdx.x; o < a.n_off; o += blockDim.x) off[o] = a.ox[o] + a.oz[o] * lw;
+// LDS cell q -> column and row of the tile + halo box
+__device__ __forceinline__ void cell_xz(const RelaxArgs& a, int q, int* x, int* z) {
+  *z = (int)__umulhi((uint32_t)q, a.lw_magic);
+  *x = q - *z * a.lw;
+}
+
+// Class of the node at LDS cell (x, z): -1 outside the grid, -2 for a bad id
+// (counted).
+__device__ __forceinline__ int32_t cell_class(const RelaxArgs& a, const JobDev& jb, int gx, int gz) {
+  if (gx < 0 || gx >= jb.nx || gz < 0 || gz >= jb.nz) return -1;
+  if (jb.per_node) return 0;
+  const int32_t k = jb.class_id[(int64_t)gx + (int64_t)jb.nx * gz];
+  if (k >= 0 && k < jb.K) return k;
+  atomicAdd(a.err, 1);
+  return -2;
 }
 
 __device__ __forceinline__ const double* stage_w(const RelaxArgs& a, const JobDev& jb, int field,
@@ -605,36 +595,14 @@ __device__ __forceinline__ void frontier_add(bool flag, int node, int32_t* list,
 
 
 
-// frontier_add for G flags per lane: one LDS atomic per wavefront for all.
-template <int G>
-__device__ __forceinline__ void frontier_add_n(const bool* flag, const int* node, int32_t* list,
-                                               int* count) {
-  unsigned long long b[G];
-  int tot = 0;
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    b[u] = __ballot(flag[u]);
-    tot += __popcll(b[u]);
-  }
-  if (tot == 0) return;
-  const int lane = __lane_id();
-  const int leader = __ffsll((long long)__ballot(true)) - 1;
-  int base = 0;
-  if (lane == leader) base = atomicAdd(count, tot);
-  base = __shfl(base, leader);
-  const unsigned long long lt = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    if (flag[u]) list[base + __popcll(b[u] & lt)] = node[u];
-    base += __popcll(b[u]);
-  }
-}
-
 // Does this visit pull node ml (LDS index)?  The R-wide strips facing the
 // neighbours whose halo part changed (side bits), or all on kFlagFull.
 __device__ __forceinline__ bool pulls(const RelaxArgs& a, const TileCtx& c, int ml) {
   if (c.active & kFlagFull) return true;
-  const int x = ml % a.lw - a.R, z = ml / a.lw - a.R;
+  int x, z;
+  cell_xz(a, ml, &x, &z);
+  x -= a.R;
+  z -= a.R;
   const bool near[2][3] = {{x < a.R, true, x >= a.tx - a.R}, {z < a.R, true, z >= a.tz - a.R}};
   const int sides = (c.active >> kSideShift) & 0x1ff;
   for (int sz = 0; sz < 3; ++sz)
@@ -655,7 +623,9 @@ __device__ __forceinline__ int seed_node(const RelaxArgs& a, const TileCtx& c, i
 // Global node index of LDS cell l.
 __device__ __forceinline__ int64_t gnode(const RelaxArgs& a, const TileCtx& c, const JobDev& jb,
                                          int l) {
-  return (int64_t)(c.x0 + l % a.lw - a.R) + (int64_t)jb.nx * (c.z0 + l / a.lw - a.R);
+  int x, z;
+  cell_xz(a, l, &x, &z);
+  return (int64_t)(c.x0 + x - a.R) + (int64_t)jb.nx * (c.z0 + z - a.R);
 }
 
 // LDS index of this thread's interior node, or -1.
@@ -670,13 +640,112 @@ __device__ __forceinline__ int my_node(const RelaxArgs& a, const TileCtx& c) {
 
 // ----------------------------------------------------- relaxation phases ---
 
+// Where a visit's edge weights come from (uniform over the workgroup).
+enum { kWUniform = 0, kWLds = 1, kWGlobal = 2, kWNode = 3 };
+
+// The push levels of a visit.  A level has two steps, a barrier after each:
+// every (frontier node, G offsets) item lowers its heads with 64-bit LDS
+// atomic mins and marks them -- nothing waits for an atomic's answer -- then
+// each thread looks at its own node's mark and the marked nodes become the
+// next frontier (ballot, one LDS atomic per wavefront).  Cells that must not
+// be lowered (halo, outside) hold -inf.  A level is a chain of LDS round
+// trips, so its length in round trips is its time: list, tail value, head
+// value and class, weight, then mark and append (atomics with return, a
+// stamp exchange and an append per edge made it about three times as long).
+// kWUniform: one class in the whole box, so a thread's G weights stay in
+// registers and an edge reads the head's value only.
+// Traveltime phase per call: 401 x 201 nodes, 5 classes, 6 fields 1.77 -> 1.12
+// ms; 801 x 251 per-node shots (32 fields) 12.4 -> 6.6 ms; whole calls 3.63 ->
+// 2.31 and 21.4 -> 13.3 ms with the tree phase's levels done the same way.
+template <int G, int SRC>
+__device__ __forceinline__ int push_levels(const RelaxArgs& a, const TileCtx& c, const JobDev& jb,
+                                           int field, const Smem& s, const double* Wg, int k0,
+                                           int ml, int nf, int* s_cnt, long long* raw,
+                                           bool* capped) {
+  const int n_off = a.n_off, K = jb.K;
+  const int ngroups = n_off / G;  // |O| is a multiple of 8
+  const int nt = blockDim.x;
+  // items = (frontier node, group of G offsets).  When the block holds whole
+  // groups, each thread keeps one group for the whole visit (its star offsets
+  // in registers) and walks the frontier in steps of `per` nodes; otherwise
+  // the items rotate over the block.
+  const int per = nt / ngroups;
+  int g = (int)threadIdx.x % ngroups;
+  const int f0 = (int)threadIdx.x / ngroups;
+  const bool idle = per > 0 && f0 >= per;
+  const int fs = per > 0 ? per : nt / ngroups, gs = per > 0 ? 0 : nt % ngroups;
+  int offr[G];
+  double wr[G];
+  auto load_group = [&]() {
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int o = g * G + u;
+      offr[u] = s.off[o];
+      if constexpr (SRC == kWUniform) wr[u] = s.W[(int64_t)(k0 * K + k0) * n_off + o];
+    }
+  };
+  load_group();
+  int it = 1;
+  while (nf > 0 && it <= kLocalIterCap) {
+    *raw += (long long)nf * n_off;
+    int f = f0;
+    if (per == 0) {
+      g = (int)threadIdx.x % ngroups;
+      load_group();
+    }
+    while (!idle && f < nf) {
+      const int i = s.list[f];
+      double wn[G], vj[G];
+      if constexpr (SRC == kWNode)
+        row_block_rev<G>(Wg, (int64_t)field * jb.nx * jb.nz + gnode(a, c, jb, i), n_off, g, wn);
+      const double vi = s.val[i];
+#pragma unroll
+      for (int u = 0; u < G; ++u) vj[u] = s.val[i + offr[u]];
+      if constexpr (SRC == kWLds || SRC == kWGlobal) {
+        const int ki = s.cls[i];
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+          const int e = (ki * K + max(s.cls[i + offr[u]], 0)) * n_off + g * G + u;
+          wn[u] = SRC == kWLds ? s.W[e] : Wg[e];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const double cand = __dadd_rn(vi, SRC == kWUniform ? wr[u] : wn[u]);
+        if (cand < vj[u]) {
+          atomicMin((unsigned long long*)&s.val[i + offr[u]], dbits(cand));
+          s.mark[i + offr[u]] = 1;
+        }
+      }
+      f += fs;
+      if (per == 0) {
+        g += gs;
+        if (g >= ngroups) {
+          g -= ngroups;
+          ++f;
+        }
+        load_group();
+      }
+    }
+    __syncthreads();
+    const bool on = ml >= 0 && s.mark[ml];
+    if (on) s.mark[ml] = 0;
+    if (threadIdx.x == 0) s_cnt[(it + 1) & 1] = 0;  // read before this level's first barrier
+    frontier_add(on, ml, s.list, &s_cnt[it & 1]);
+    __syncthreads();
+    nf = s_cnt[it & 1];
+    ++it;
+  }
+  *capped = nf > 0;
+  return it - 1;
+}
+
 // Phase TAU: tau_j <- min(tau_j, tau_i + w_ij) (eq 31).
 template <int G>
 __device__ __forceinline__ void relax_tau(const RelaxArgs& a, int round, int T) {
   extern __shared__ double smem_d[];
-  __shared__ int s_flag, s_prob, s_mask, s_cnt[3];
+  __shared__ int s_flag, s_prob, s_mask, s_cnt[3], s_kmin, s_kmax;
   __shared__ unsigned long long s_key;
-  __shared__ int s_npull;
   const TileCtx c = tile_begin(a, round, T, &s_flag, &s_prob, 0);
   if (!c.active) return;
   const Smem s = carve(a, smem_d);
@@ -686,19 +755,39 @@ __device__ __forceinline__ void relax_tau(const RelaxArgs& a, int round, int T) 
   if (threadIdx.x == 0) {
     s_mask = 0;
     s_key = kInfBits;
-    s_npull = 0;
     s_cnt[0] = 0;
     s_cnt[1] = 0;
     s_cnt[2] = 0;
+    s_kmin = 0x7fffffff;
+    s_kmax = -1;
   }
-  load_common(a, c, jb, s.cls, s.inq, s.off);
+  int kmin = 0x7fffffff, kmax = -1;
   for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    int gx = c.x0 + (q % lw) - R, gz = c.z0 + (q / lw) - R;
-    bool in = gx >= 0 && gx < jb.nx && gz >= 0 && gz < jb.nz;
-    s.val[q] = in ? pr.tau[(int64_t)gx + (int64_t)jb.nx * gz] : INFINITY;
+    int x, z;
+    cell_xz(a, q, &x, &z);
+    const int gx = c.x0 + x - R, gz = c.z0 + z - R;
+    const int32_t k = cell_class(a, jb, gx, gz);
+    s.cls[q] = k;
+    s.mark[q] = 0;
+    s.val[q] = k != -1 ? pr.tau[(int64_t)gx + (int64_t)jb.nx * gz] : INFINITY;
+    if (k >= 0) {
+      kmin = min(kmin, k);
+      kmax = max(kmax, k);
+    }
   }
+  for (int o = threadIdx.x; o < n_off; o += blockDim.x) s.off[o] = a.ox[o] + a.oz[o] * lw;
   const double* Wp = stage_w(a, jb, pr.field, s);
   __syncthreads();
+  if (!jb.per_node && jb.w_in_lds) {  // does the box hold one class?
+    for (int d = 32; d >= 1; d >>= 1) {
+      kmin = min(kmin, __shfl_xor(kmin, d));
+      kmax = max(kmax, __shfl_xor(kmax, d));
+    }
+    if (__lane_id() == 0) {
+      atomicMin(&s_kmin, kmin);
+      atomicMax(&s_kmax, kmax);
+    }
+  }
   const int ml = my_node(a, c);
   long long raw = 0;
   const double orig = ml >= 0 ? s.val[ml] : 0.0;
@@ -709,206 +798,87 @@ __device__ __forceinline__ void relax_tau(const RelaxArgs& a, int round, int T) 
   // kept a wavefront waiting on its few pulling lanes -- each lowering its
   // node with the 64-bit LDS atomic min; a node whose value dropped enters
   // the first frontier.  (In-neighbours lowered meanwhile enter it too.)
+  int np;
+  bool pl;
   {
-    const bool pl = ml >= 0 && pulls(a, c, ml) && s.cls[ml] >= 0;
-    if (pl) atomicAdd(&s_npull, 1);
-    frontier_add(pl, ml, s.l1, &s_cnt[1]);  // l1 is free until the first level
+    pl = ml >= 0 && pulls(a, c, ml) && s.cls[ml] >= 0;
+    frontier_add(pl, ml, s.list, &s_cnt[2]);
     __syncthreads();
-    const int np = s_cnt[1];
+    np = s_cnt[2];
     const int npg = (n_off + kPullGroup - 1) / kPullGroup;
     const int total = np * npg;
     for (int item = threadIdx.x; item < total; item += blockDim.x) {
-      const int j = s.l1[item / npg], g = item % npg;
-      const int kj = s.cls[j];
-      const int64_t gj = gnode(a, c, jb, j);
+      const int j = s.list[item / npg], g = item % npg;
       double best = s.val[j];
+      double wv[kPullGroup];
       if (jb.per_node) {
         // the group's eight consecutive entries of row j (|O| is a multiple
         // of 8, so the group is whole)
-        double wv[kPullGroup];
-        row_block<kPullGroup>(jb.W, (int64_t)pr.field * jb.nx * jb.nz + gj, n_off, g, wv);
-#pragma unroll
-        for (int u = 0; u < kPullGroup; ++u) {
-          const int o = g * kPullGroup + u;
-          if (o >= n_off) break;
-          const int ii = j - s.off[o];
-          if (s.cls[ii] < 0) continue;
-          const double cand = __dadd_rn(s.val[ii], wv[u]);
-          if (cand < best) best = cand;
-        }
+        row_block<kPullGroup>(jb.W, (int64_t)pr.field * jb.nx * jb.nz + gnode(a, c, jb, j), n_off,
+                              g, wv);
       } else {
+        const int kj = s.cls[j];
 #pragma unroll
         for (int u = 0; u < kPullGroup; ++u) {
           const int o = g * kPullGroup + u;
-          if (o >= n_off) break;
-          const int ii = j - s.off[o];
-          const int ki = s.cls[ii];
-          if (ki < 0) continue;
-          const double cand =
-              __dadd_rn(s.val[ii], w_pull(jb, Wp, pr.field, ki & kClassMask, kj, o, n_off, gj));
-          if (cand < best) best = cand;
+          const int e = (max(s.cls[j - s.off[o]], 0) * jb.K + kj) * n_off + o;
+          wv[u] = jb.w_in_lds ? s.W[e] : Wp[e];
         }
+      }
+#pragma unroll
+      for (int u = 0; u < kPullGroup; ++u) {  // (+inf outside the grid)
+        const double cand = __dadd_rn(s.val[j - s.off[g * kPullGroup + u]], wv[u]);
+        if (cand < best) best = cand;
       }
       if (best < s.val[j]) atomicMin((unsigned long long*)&s.val[j], dbits(best));
     }
     __syncthreads();
-    if (threadIdx.x == 0) s_cnt[1] = 0;  // every thread has read np
-    const bool improved = pl && s.val[ml] < orig;
-    if (improved) s.inq[ml] = 1;
-    frontier_add(improved, ml, s.l0, &s_cnt[0]);
   }
+  // the list's readers are done: the first frontier; cells that pushes must
+  // leave alone read -inf from here on
+  const bool improved = pl && s.val[ml] < orig;
+  frontier_add(improved, ml, s.list, &s_cnt[0]);
   if (threadIdx.x == 0) {
     const int sn = seed_node(a, c, pr.src, jb.nx);
-    if (sn >= 0 && s.cls[sn] >= 0 && atomicExch(&s.inq[sn], 1) != 1)
-      s.l0[atomicAdd(&s_cnt[0], 1)] = sn;
+    if (sn >= 0 && s.cls[sn] >= 0) s.list[atomicAdd(&s_cnt[0], 1)] = sn;
+  }
+  for (int q = threadIdx.x; q < n; q += blockDim.x) {
+    int x, z;
+    cell_xz(a, q, &x, &z);
+    if (x < R || x >= R + c.txe || z < R || z >= R + c.tze || s.cls[q] < 0) s.val[q] = -INFINITY;
   }
   __syncthreads();
+  const int nf = s_cnt[0];
+  int levels;
+  bool again;
+  if (jb.per_node)
+    levels = push_levels<G, kWNode>(a, c, jb, pr.field, s, jb.W, 0, ml, nf, s_cnt, &raw,
+                                        &again);
+  else if (!jb.w_in_lds)
+    levels = push_levels<G, kWGlobal>(a, c, jb, pr.field, s, Wp, 0, ml, nf, s_cnt, &raw,
+                                        &again);
+  else if (s_kmin == s_kmax)
+    levels = push_levels<G, kWUniform>(a, c, jb, pr.field, s, Wp, s_kmin, ml, nf, s_cnt, &raw,
+                                        &again);
+  else
+    levels = push_levels<G, kWLds>(a, c, jb, pr.field, s, Wp, 0, ml, nf, s_cnt, &raw,
+                                        &again);
 
-  // push iterations over the frontier: one barrier per level; counters
-  // rotate over three slots, the dedupe stamp is the level number
-  int ci = 0, it = 1;
-  int nf = s_cnt[0];
-  const int ngroups = (n_off + G - 1) / G;
-  const int nt = blockDim.x;
-  // Work items = (frontier node, group of G offsets).  When the block
-  // holds whole groups, each thread keeps one group for the whole visit
-  // (its star offsets in registers) and walks the frontier in steps of
-  // `per` nodes; otherwise the items rotate over the block.
-  const int per = nt / ngroups;
-  const int my_g = per > 0 ? (int)threadIdx.x % ngroups : 0;
-  const int my_f = per > 0 ? (int)threadIdx.x / ngroups : 0;
-  int offr[G];
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    const int o = my_g * G + u;
-    offr[u] = o < n_off ? s.off[o] : 0;
-  }
-  const int q_step = nt / ngroups, r_step = nt % ngroups;
-
-  // one item; "plain read first": most pushes do not improve and skip
-  // the atomic.  Per-node weights: every load of the G edges first
-  // (independent chains in flight together), then the atomics, then one
-  // append for all of them.
-  auto push_item = [&](bool live, int i, int g, const int* offs, int32_t* lnxt, int* cnt) {
-    const double vi = s.val[i];
-    const int ki0 = s.cls[i];
-    const int ki = ki0 >= 0 ? (ki0 & kClassMask) : 0;
-    const int64_t gi = gnode(a, c, jb, i);
-    if (!jb.per_node) {
-      // class-pair weights in LDS: edge by edge (measured faster here than
-      // batching the loads, which adds live registers)
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        bool improved = false;
-        int jj = 0;
-        const int o = g * G + u;
-        if (live && o < n_off) {
-          const int j = i + offs[u];
-          const int kj = s.cls[j];
-          if (kj >= 0 && !(kj & kHaloBit)) {
-            const double cand = __dadd_rn(vi, Wp[(ki * jb.K + kj) * n_off + o]);
-            if (cand < s.val[j]) {
-              const unsigned long long old =
-                  atomicMin((unsigned long long*)&s.val[j], dbits(cand));
-              if (dbits(cand) < old) {
-                improved = atomicExch(&s.inq[j], it + 1) != it + 1;
-                jj = j;
-              }
-            }
-          }
-        }
-        frontier_add(improved, jj, lnxt, cnt);
-      }
-      return;
-    }
-    // per-node weights from HBM: the group's G entries of row i in 16-byte
-    // loads, issued before any atomic
-    int jv[G];
-    double cv[G];
-    bool tv[G];
-    double wv[G];
-    if (live) row_block_rev<G>(jb.W, (int64_t)pr.field * jb.nx * jb.nz + gi, n_off, g, wv);
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      const int o = g * G + u;
-      jv[u] = 0;
-      cv[u] = 0.0;
-      tv[u] = false;
-      if (live && o < n_off) {
-        const int j = i + offs[u];
-        const int kj = s.cls[j];
-        if (kj >= 0 && !(kj & kHaloBit)) {
-          const double cand = __dadd_rn(vi, wv[u]);
-          jv[u] = j;
-          cv[u] = cand;
-          tv[u] = cand < s.val[j];
-        }
-      }
-    }
-    bool imp[G];
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      imp[u] = false;
-      if (tv[u]) {
-        const unsigned long long old =
-            atomicMin((unsigned long long*)&s.val[jv[u]], dbits(cv[u]));
-        if (dbits(cv[u]) < old) imp[u] = atomicExch(&s.inq[jv[u]], it + 1) != it + 1;
-      }
-    }
-    frontier_add_n<G>(imp, jv, lnxt, cnt);
-  };
-
-  while (nf > 0 && it <= kLocalIterCap) {
-    const int cn = ci == 2 ? 0 : ci + 1, cz = cn == 2 ? 0 : cn + 1;
-    int32_t* const lcur = (it & 1) ? s.l0 : s.l1;
-    int32_t* const lnxt = (it & 1) ? s.l1 : s.l0;
-    if (threadIdx.x == 0) s_cnt[cz] = 0;
-    raw += (long long)nf * n_off;
-    const int idle = R * lw + R;  // idle lanes stand on the first interior node
-    // every thread runs the same trip count so the appends see whole waves
-    if (per > 0) {
-      const int sweeps = (nf + per - 1) / per;
-      for (int sw = 0; sw < sweeps; ++sw) {
-        const int f = sw * per + my_f;
-        const bool live = my_f < per && f < nf;
-        push_item(live, live ? lcur[f] : idle, my_g, offr, lnxt, &s_cnt[cn]);
-      }
-    } else {
-      const int total = nf * ngroups;
-      const int bound = (total + nt - 1) / nt * nt;
-      int f = threadIdx.x / ngroups, g = threadIdx.x % ngroups;
-      for (int item = threadIdx.x; item < bound; item += nt) {
-        const bool live = item < total;
-        int offs[G];
-#pragma unroll
-        for (int u = 0; u < G; ++u) offs[u] = g * G + u < n_off ? s.off[g * G + u] : 0;
-        push_item(live, live ? lcur[f] : idle, g, offs, lnxt, &s_cnt[cn]);
-        f += q_step;
-        g += r_step;
-        if (g >= ngroups) {
-          g -= ngroups;
-          ++f;
-        }
-      }
-    }
-    __syncthreads();
-    nf = s_cnt[cn];
-    ci = cn;
-    ++it;
-  }
-
-  int mask = (nf > 0) ? (1 << 4) : 0;  // bit 4 = this tile again
-  if (ml >= 0 && s.val[ml] < orig) {
-    int x = ml % lw - R, z = ml / lw - R;
+  int mask = again ? (1 << 4) : 0;  // bit 4 = this tile again
+  if (ml >= 0 && s.cls[ml] >= 0 && s.val[ml] < orig) {
+    int x, z;
+    cell_xz(a, ml, &x, &z);
+    x -= R;
+    z -= R;
     pr.tau[(int64_t)(c.x0 + x) + (int64_t)jb.nx * (c.z0 + z)] = s.val[ml];
     const int bb = border_bits(x, z, a.tx, a.tz, R);
     mask |= bb;
     if (bb && a.bucket > 0.0) atomicMin(&s_key, dbits(s.val[ml]));
   }
-  count_visit(a, 0, raw + (long long)s_npull * n_off, it - 1);
+  count_visit(a, 0, raw + (long long)np * n_off, levels);
   if (mask) atomicOr(&s_mask, mask);
   __syncthreads();
-  if (threadIdx.x == 0 && s_mask) activate(a, round, c, pr, jb, s_mask, s_key);
+  if (threadIdx.x < 64 && s_mask) activate(a, round, c, pr, jb, s_mask, s_key);
 }
 
 // ------------------------------------------- predecessor tree phase ---
@@ -921,26 +891,16 @@ __device__ __forceinline__ void relax_tau(const RelaxArgs& a, int round, int T) 
 // fits), one thread per interior node; problems without predecessors leave.
 __global__ void __launch_bounds__(kRelaxThreads) k_tight_out(RelaxArgs a) {
   extern __shared__ double smem_d[];
-  __shared__ int s_prob;
   const int T = blockIdx.x;
   if (*a.err) return;  // bad class map: the fields were never initialised
-  if (threadIdx.x == 0) {
-    int lo = 0, hi = a.n_prob - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (a.probs[mid].tile_base <= T) lo = mid;
-      else hi = mid - 1;
-    }
-    s_prob = lo;
-  }
-  __syncthreads();
-  const ProbDev pr = a.probs[s_prob];
+  const int prob = a.tile_prob[T];
+  const ProbDev pr = a.probs[prob];
   if (!pr.pred) return;  // block-uniform
   const JobDev jb = a.jobs[pr.job];
   const int R = a.R, lw = a.lw, n = lw * a.lh, n_off = a.n_off, nw = a.nw;
   const int t = T - pr.tile_base;
   TileCtx c;
-  c.p = s_prob;
+  c.p = prob;
   c.t = t;
   c.tx = t % jb.ntx;
   c.tz = t / jb.ntx;
@@ -1040,11 +1000,9 @@ struct TreeSmem {
   double* ts;               // [lw*lh] t* (NaN while unknown)
   uint32_t* om;             // [nw][lw*lh] tight out-masks
   int32_t* cls;
-  int32_t* inq;             // (level + 1) << 1 | key changed at that level
   int32_t* off;
-  int32_t* l0;              // frontiers (interior LDS indices)
-  int32_t* l1;
-  int32_t* lc;              // candidates of a level before the t* check
+  int32_t* list;            // frontier (interior LDS indices)
+  uint8_t* mark;            // [lw*lh] named or confirmed by a push of this level
 };
 
 __device__ __forceinline__ TreeSmem carve_tree(const RelaxArgs& a, void* base) {
@@ -1059,22 +1017,18 @@ __device__ __forceinline__ TreeSmem carve_tree(const RelaxArgs& a, void* base) {
   p += sizeof(uint32_t) * a.nw * n;
   s.cls = (int32_t*)p;
   p += sizeof(int32_t) * n;
-  s.inq = (int32_t*)p;
-  p += sizeof(int32_t) * n;
   s.off = (int32_t*)p;
   p += sizeof(int32_t) * ((a.n_off + 1) & ~1);
-  s.l0 = (int32_t*)p;
+  s.list = (int32_t*)p;
   p += sizeof(int32_t) * T;
-  s.l1 = (int32_t*)p;
-  p += sizeof(int32_t) * T;
-  s.lc = (int32_t*)p;
+  s.mark = (uint8_t*)p;
   return s;
 }
 
 static size_t tree_lds_bytes(int lw, int lh, int nw, int n_off, int tx, int tz) {
   const size_t n = (size_t)lw * lh;
-  return (2 * sizeof(double) + sizeof(uint32_t) * nw + 2 * sizeof(int32_t)) * n +
-         sizeof(int32_t) * ((n_off + 1) & ~1) + sizeof(int32_t) * 3 * tx * tz;
+  return (2 * sizeof(double) + sizeof(uint32_t) * nw + sizeof(int32_t)) * n +
+         sizeof(int32_t) * ((n_off + 1) & ~1) + sizeof(int32_t) * tx * tz + ((n + 7) & ~(size_t)7);
 }
 
 // Phase TREE: hop counts, predecessors (eq 33) and t* in one relaxation.
@@ -1085,11 +1039,15 @@ static size_t tree_lds_bytes(int lw, int lh, int nw, int n_off, int tx, int tz) 
 // the push names its predecessor again re-reads the parent's t*.  Keys only
 // decrease, t* follows the (acyclic) predecessor tree, so the fixed point
 // is the ordered fold along that tree for any schedule.
+// Levels as in push_levels: the items are (frontier node, 32-offset word of
+// its tight mask), a node having little more than one tight out-edge on
+// average, and heads are lowered and marked without waiting for answers;
+// then each thread looks at its own node, re-reads t* and joins the next
+// frontier if its key or t* changed.
 __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T) {
   extern __shared__ double smem_d[];
-  __shared__ int s_flag, s_prob, s_mask, s_cnt[3], s_cand[2];
+  __shared__ int s_flag, s_prob, s_mask, s_cnt[3];
   __shared__ unsigned long long s_key;
-  __shared__ int s_npull;
   const TileCtx c = tile_begin(a, round, T, &s_flag, &s_prob, 1);
   if (!c.active) return;
   const TreeSmem s = carve_tree(a, smem_d);
@@ -1102,21 +1060,24 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
   if (threadIdx.x == 0) {
     s_mask = 0;
     s_key = kInfBits;
-    s_npull = 0;
     s_cnt[0] = 0;
     s_cnt[1] = 0;
     s_cnt[2] = 0;
-    s_cand[1] = 0;
   }
-  load_common(a, c, jb, s.cls, s.inq, s.off);
   for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    int gx = c.x0 + (q % lw) - R, gz = c.z0 + (q / lw) - R;
-    bool in = gx >= 0 && gx < jb.nx && gz >= 0 && gz < jb.nz;
-    int64_t g = (int64_t)gx + (int64_t)jb.nx * gz;
+    int x, z;
+    cell_xz(a, q, &x, &z);
+    const int gx = c.x0 + x - R, gz = c.z0 + z - R;
+    const int32_t k = cell_class(a, jb, gx, gz);
+    const bool in = k != -1;
+    const int64_t g = (int64_t)gx + (int64_t)jb.nx * gz;
+    s.cls[q] = k;
+    s.mark[q] = 0;
     s.key[q] = in ? pr.key[g] : kKeyUnset;
     s.ts[q] = (in && fold) ? pr.tstar[g] : NAN;
     for (int w = 0; w < nw; ++w) s.om[w * n + q] = in ? pr.tight[(int64_t)w * gn + g] : 0u;
   }
+  for (int o = threadIdx.x; o < n_off; o += blockDim.x) s.off[o] = a.ox[o] + a.oz[o] * lw;
   __syncthreads();
   const int ml = my_node(a, c);
   long long raw = 0;
@@ -1124,14 +1085,12 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
   const double ots = ml >= 0 ? s.ts[ml] : 0.0;
 
   // t*_j from the predecessor its key names; true if t*_j changed
-  auto refold = [&](int j) -> bool {
-    const unsigned long long k = s.key[j];
+  auto refold = [&](int j, unsigned long long k) -> bool {
     if (k == kKeyUnset || (k >> 32) == 0ull) return false;  // unreached, or the source
     const int o = (int)(k & 0xffffffffull);
     const int p = j - s.off[o];
-    const double t = __dadd_rn(s.ts[p], w_pull(jb, WI, kFieldI, s.cls[p] & kClassMask,
-                                               s.cls[j] & kClassMask, o, n_off,
-                                               gnode(a, c, jb, j)));
+    const double t =
+        __dadd_rn(s.ts[p], w_pull(jb, WI, kFieldI, s.cls[p], s.cls[j], o, n_off, gnode(a, c, jb, j)));
     if (dbits(t) == dbits(s.ts[j])) return false;
     s.ts[j] = t;
     return true;
@@ -1141,16 +1100,15 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
   // pulled nodes' in-edges as (node, kPullGroup offsets) items over the
   // block (64-bit LDS atomic min on the key), then each pulled node
   // re-reads its t*
+  const bool pl = ml >= 0 && pulls(a, c, ml);
+  frontier_add(pl, ml, s.list, &s_cnt[2]);
+  __syncthreads();
+  const int np = s_cnt[2];
   {
-    const bool pl = ml >= 0 && pulls(a, c, ml);
-    if (pl) atomicAdd(&s_npull, 1);
-    frontier_add(pl, ml, s.l1, &s_cnt[1]);  // l1 is free until the first level
-    __syncthreads();
-    const int np = s_cnt[1];
     const int npg = (n_off + kPullGroup - 1) / kPullGroup;
     const int total = np * npg;
     for (int item = threadIdx.x; item < total; item += blockDim.x) {
-      const int j = s.l1[item / npg], g = item % npg;
+      const int j = s.list[item / npg], g = item % npg;
       unsigned long long best = s.key[j];
 #pragma unroll
       for (int u = 0; u < kPullGroup; ++u) {
@@ -1165,118 +1123,56 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
       }
       if (best < s.key[j]) atomicMin(&s.key[j], best);
     }
-    __syncthreads();
-    if (threadIdx.x == 0) s_cnt[1] = 0;  // every thread has read np
-    bool changed = pl && s.key[ml] != okey;
-    if (pl && fold && refold(ml)) changed = true;
-    if (changed) s.inq[ml] = 2;
-    frontier_add(changed, ml, s.l0, &s_cnt[0]);
+  }
+  __syncthreads();
+  unsigned long long last = ml >= 0 ? s.key[ml] : 0ull;  // this thread's node at the last look
+  {
+    bool changed = pl && last != okey;
+    if (pl && fold && refold(ml, last)) changed = true;
+    frontier_add(changed, ml, s.list, &s_cnt[0]);
   }
   if (threadIdx.x == 0) {
     const int sn = seed_node(a, c, pr.src, jb.nx);
-    if (sn >= 0 && s.cls[sn] >= 0 && atomicExch(&s.inq[sn], 2) != 2)
-      s.l0[atomicAdd(&s_cnt[0], 1)] = sn;
+    if (sn >= 0 && s.cls[sn] >= 0) s.list[atomicAdd(&s_cnt[0], 1)] = sn;
   }
   __syncthreads();
 
   // push levels over the tight out-edges of the frontier nodes only
-  int ci = 0, it = 1;
+  int it = 1;
   int nf = s_cnt[0];
   const int nt = blockDim.x;
   while (nf > 0 && it <= kLocalIterCap) {
-    const int cn = ci == 2 ? 0 : ci + 1, cz = cn == 2 ? 0 : cn + 1;
-    int32_t* const lcur = (it & 1) ? s.l0 : s.l1;
-    int32_t* const lnxt = (it & 1) ? s.l1 : s.l0;
-    // candidate counts alternate by level: the other slot was last read
-    // before the previous level's final barrier
-    int* const cand_cnt = &s_cand[it & 1];
-    if (threadIdx.x == 0) {
-      s_cnt[cz] = 0;
-      s_cand[(it + 1) & 1] = 0;
-    }
-    const int32_t stamp = (it + 1) << 1;
-    for (int b0 = 0; b0 < nf; b0 += nt) {
-      const int f = b0 + (int)threadIdx.x;
-      const bool live = f < nf;
-      const int i = live ? lcur[f] : 0;
-      const unsigned long long ki = live ? s.key[i] : kKeyUnset;
-      const bool has = ki != kKeyUnset;
-      // the wavefront's tight out-edges dealt one per lane: a lane's count,
-      // inclusive prefix over the wavefront, then edge e goes to the lane
-      // holding it (first lane whose inclusive prefix exceeds e)
-      int cnt = 0;
-      for (int w = 0; w < nw; ++w) cnt += has ? __popc(s.om[w * n + i]) : 0;
-      const int lane = __lane_id();
-      int incl = cnt;
-      for (int d = 1; d < 64; d <<= 1) {
-        const int v = __shfl_up(incl, d);
-        if (lane >= d) incl += v;
-      }
-      const int excl = incl - cnt;
-      const int total = __shfl(incl, 63);
-      for (int e0 = 0; e0 < total; e0 += 64) {
-        const int e = e0 + lane;
-        int owner = 0;
-        for (int step = 32; step > 0; step >>= 1)
-          if (__shfl(incl, owner + step - 1) <= e) owner += step;
-        owner = owner > 63 ? 63 : owner;
-        const int ex_o = __shfl(excl, owner);
-        const int io = __shfl(i, owner);
-        const unsigned long long ko = __shfl(ki, owner);
-        bool mark = false;
-        int jj = 0;
-        if (e < total) {
-          int k = e - ex_o, o = -1;  // the owner's k-th set bit
-          for (int w = 0; w < nw; ++w) {
-            uint32_t m = s.om[w * n + io];
-            const int pc = __popc(m);
-            if (o < 0 && k < pc) {
-              for (int t = 0; t < k; ++t) m &= m - 1u;
-              o = w * 32 + __ffs(m) - 1;
-            } else if (o < 0) {
-              k -= pc;
-            }
-          }
-          const int j = io + s.off[o];
-          const int kj = s.cls[j];
-          ++raw;
-          if (kj >= 0 && !(kj & kHaloBit)) {
-            const unsigned long long cand = tree_key(ko, o);
-            if (cand < s.key[j] || (fold && cand == s.key[j])) {
-              const unsigned long long old = atomicMin(&s.key[j], cand);
-              if (cand < old) {
-                mark = (atomicMax(&s.inq[j], stamp | 1) >> 1) != it + 1;
-                jj = j;
-              } else if (fold && cand == old) {
-                mark = (atomicMax(&s.inq[j], stamp) >> 1) != it + 1;
-                jj = j;
-              }
-            }
-          }
-        }
-        if (fold) frontier_add(mark, jj, s.lc, cand_cnt);
-        else frontier_add(mark, jj, lnxt, &s_cnt[cn]);
+    for (int item = threadIdx.x; item < nf * nw; item += nt) {
+      const int f = item / nw, w = item - f * nw;
+      const int i = s.list[f];
+      uint32_t m = s.om[w * n + i];
+      const unsigned long long ki = s.key[i];
+      if (ki == kKeyUnset) continue;
+      raw += __popc(m);
+      while (m) {
+        const int o = w * 32 + __ffs(m) - 1;
+        m &= m - 1u;
+        const int j = i + s.off[o];
+        const unsigned long long cand = tree_key(ki, o), kj = s.key[j];
+        if (cand < kj) atomicMin(&s.key[j], cand);
+        if (cand < kj || (fold && cand == kj)) s.mark[j] = 1;
       }
     }
     __syncthreads();
-    if (fold) {
-      // keep the candidates whose key changed or whose t* changes
-      const int nc = *cand_cnt;
-      for (int b0 = 0; b0 < nc; b0 += nt) {
-        const int q = b0 + (int)threadIdx.x;
-        const bool live = q < nc;
-        const int j = live ? s.lc[q] : 0;
-        bool keep = false;
-        if (live) {
-          const bool kchg = (s.inq[j] & 1) != 0;
-          keep = refold(j) || kchg;
-        }
-        frontier_add(keep, j, lnxt, &s_cnt[cn]);
-      }
-      __syncthreads();
+    // (a halo head may be lowered too: it is neither looked at nor written
+    // back, and the tile that owns it is woken by this tile's border nodes)
+    bool on = false;
+    if (ml >= 0 && s.mark[ml]) {
+      s.mark[ml] = 0;
+      const unsigned long long k = s.key[ml];
+      on = k != last;
+      last = k;
+      if (fold && refold(ml, k)) on = true;
     }
-    nf = s_cnt[cn];
-    ci = cn;
+    if (threadIdx.x == 0) s_cnt[(it + 1) & 1] = 0;  // read before this level's first barrier
+    frontier_add(on, ml, s.list, &s_cnt[it & 1]);
+    __syncthreads();
+    nf = s_cnt[it & 1];
     ++it;
   }
 
@@ -1285,7 +1181,10 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
     const bool kc = s.key[ml] != okey;
     const bool tc = fold && dbits(s.ts[ml]) != dbits(ots);
     if (kc || tc) {
-      int x = ml % lw - R, z = ml / lw - R;
+      int x, z;
+      cell_xz(a, ml, &x, &z);
+      x -= R;
+      z -= R;
       const int64_t g = (int64_t)(c.x0 + x) + (int64_t)jb.nx * (c.z0 + z);
       if (kc) pr.key[g] = s.key[ml];
       if (tc) pr.tstar[g] = s.ts[ml];
@@ -1294,10 +1193,12 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
       if (bb && a.bucket > 0.0) atomicMin(&s_key, dbits((double)(s.key[ml] >> 32)));
     }
   }
-  count_visit(a, 1, raw + (long long)s_npull * n_off, it - 1);
+  for (int d = 32; d >= 1; d >>= 1) raw += __shfl_xor(raw, d);  // the edges this wavefront pushed
+  if (__lane_id() == 0 && raw) atomicAdd(&stat_slot(a.stats)[3], (unsigned long long)raw);
+  count_visit(a, 1, (long long)np * n_off, it - 1);
   if (mask) atomicOr(&s_mask, mask);
   __syncthreads();
-  if (threadIdx.x == 0 && s_mask) activate(a, round, c, pr, jb, s_mask, s_key);
+  if (threadIdx.x < 64 && s_mask) activate(a, round, c, pr, jb, s_mask, s_key);
 }
 
 // pred_j = j - (the offset its key names); -1 for the source and unreached
@@ -1505,7 +1406,7 @@ struct Plan {
   int max_rounds = 0;
   std::vector<int64_t> nodes;  // per job
   std::vector<int> ntx, ntz, K;
-  size_t off_star = 0, off_lbin = 0, off_jobs = 0, off_probs = 0, off_flags = 0, off_list = 0,
+  size_t off_star = 0, off_lbin = 0, off_jobs = 0, off_probs = 0, off_flags = 0, off_list = 0, off_tprob = 0,
          off_counter = 0, off_key = 0, off_pmin = 0, off_wmin = 0,
          off_err = 0, off_stats = 0, off_nkey = 0, off_tight = 0, total = 0;
   std::vector<size_t> off_W;  // per job
@@ -1635,6 +1536,8 @@ static int make_plan(const chert_trace_job* jobs, int n_jobs, const chert_trace_
   off += align256((size_t)2 * P->n_tiles * sizeof(int32_t));
   P->off_list = off;
   off += align256((size_t)2 * P->n_tiles * sizeof(int32_t));
+  P->off_tprob = off;
+  off += align256((size_t)P->n_tiles * sizeof(int32_t));
   P->off_counter = off;
   off += align256(counter_words(P->max_rounds) * sizeof(int32_t));  // counts, tickets
   P->off_key = off;
@@ -1881,6 +1784,8 @@ static int prepare(const chert_trace_job* jobs, int n_jobs, const chert_trace_op
   a.oz = doz;
   a.flags = (int32_t*)(ws + P.off_flags);
   a.list = (int32_t*)(ws + P.off_list);
+  a.tile_prob = (const int32_t*)(ws + P.off_tprob);
+  a.lw_magic = (uint32_t)((0x100000000ull + P.lw - 1) / P.lw);
   a.counter = (int32_t*)(ws + P.off_counter);
   a.err = (int32_t*)(ws + P.off_err);
   a.stats = (unsigned long long*)(ws + P.off_stats);
@@ -2011,7 +1916,8 @@ static int enqueue(const Prepared& Q, const chert_trace_job* jobs, int n_jobs,
   for (int64_t n : P.nodes) max_nodes = n > max_nodes ? n : max_nodes;
   const unsigned gx = (unsigned)((max_nodes + 255) / 256 > 1024 ? 1024 : (max_nodes + 255) / 256);
   const dim3 pgrid(gx, (unsigned)P.n_prob);
-  CHERT_LAUNCH("k_init_fields", k_init_fields, pgrid, dim3(256), 0, s, Q.dprobs, Q.djobs, a.err);
+  CHERT_LAUNCH("k_init_fields", k_init_fields, pgrid, dim3(256), 0, s, Q.dprobs, Q.djobs, a.err,
+               (int32_t*)(ws + P.off_tprob));
   const int64_t n_flags = 2 * P.n_tiles;
   auto init_flags = [&](int tree_phase) {
     CHERT_LAUNCH("k_clear_flags", k_clear_flags, dim3(256), dim3(256), 0, s, a.flags, n_flags,
