@@ -81,25 +81,58 @@ int star_columns(const chert_cache_desc* d, const int32_t* bin, int n_off, int32
   return CHERT_OK;
 }
 
-void fibonacci(int N, double* f) {
+// The Fibonacci direction closest to the unit vector u: the largest dot
+// product f . u, evaluated as f_x u_x + f_y u_y + f_z u_z on the directions
+//   f_i = (r cos(i ga), r sin(i ga), z), z = 1 - (2 i + 1) / N, r = sqrt(1 - z^2),
+// ga = pi (3 - sqrt 5), the lowest index among equals -- what a search over all
+// N gives.
+// Directions within an angle delta of u have a polar angle within delta of
+// u's, which is a run of indices (z falls linearly with the index), and an
+// azimuth within 2 asin(sin(delta / 2) / sqrt(r r_u)) of u's (haversine), so
+// only those are evaluated: ~450 azimuths and a handful of dot products at N =
+// 41,253 instead of N (a 3D trace at radius 3 spent 7.9 of 22.7 ms in that
+// search, a block trace 1.1 ms on the directions' upload).  If the best one found lies within delta nothing
+// outside can beat it; else delta doubles.
+int fib_nearest(int N, const double* u) {
   const double ga = M_PI * (3.0 - sqrt(5.0));
-  for (int i = 0; i < N; ++i) {
-    const double z = 1.0 - (2.0 * i + 1.0) / N;
-    const double r = sqrt(1.0 - z * z);
-    const double ph = i * ga;
-    f[3 * i] = r * cos(ph);
-    f[3 * i + 1] = r * sin(ph);
-    f[3 * i + 2] = z;
+  const double uz = u[2] > 1.0 ? 1.0 : (u[2] < -1.0 ? -1.0 : u[2]);
+  const double th = acos(uz), ru = sin(th), phi = atan2(u[1], u[0]) / (2.0 * M_PI);
+  for (double delta = 2.2 / sqrt((double)N);; delta *= 2.0) {
+    const bool all = delta > 0.5;  // (few directions)
+    const double zhi = all || th - delta <= 0.0 ? 1.0 : cos(th - delta);
+    const double zlo = all || th + delta >= M_PI ? -1.0 : cos(th + delta);
+    // z_i = 1 - (2 i + 1) / N within [zlo, zhi], a few indices to spare
+    int i0 = (int)floor(0.5 * (N * (1.0 - zhi) - 1.0)) - 2;
+    int i1 = (int)ceil(0.5 * (N * (1.0 - zlo) - 1.0)) + 2;
+    i0 = i0 < 0 ? 0 : i0;
+    i1 = i1 > N - 1 ? N - 1 : i1;
+    int best = -1;
+    double bd = -2.0;
+    for (int i = i0; i <= i1; ++i) {
+      const double z = 1.0 - (2.0 * i + 1.0) / N;
+      const double r = sqrt(1.0 - z * z);
+      if (!all) {
+        // azimuth difference in turns; sin(x) <= x gives the test without
+        // trigonometry: outside delta if sin(pi t)^2 r r_u > sin(delta / 2)^2
+        double t = i * (ga / (2.0 * M_PI)) - phi;
+        t -= floor(t + 0.5);
+        const double at = fabs(t) - 1e-9;
+        // sin(pi t) >= 2 t on [0, 1/2]
+        if (at > 0.0 && 4.0 * at * at * r * ru > 0.2501 * delta * delta) continue;
+      }
+      const double ph = i * ga;
+      const double d = r * cos(ph) * u[0] + r * sin(ph) * u[1] + z * u[2];
+      if (d > bd) {
+        bd = d;
+        best = i;
+      }
+    }
+    if (best >= 0 && (all || bd >= cos(delta) + 1e-12)) return best;
   }
 }
 
 int star_3d(int R, double hx, double hy, double hz, int N, int32_t* ox, int32_t* oy, int32_t* oz,
             double* L, int32_t* bin) {
-  std::vector<double> f;
-  if (ox) {
-    f.resize(3 * (size_t)N);
-    fibonacci(N, f.data());
-  }
   int n = 0;
   for (int y = -R; y <= R; ++y)
     for (int z = -R; z <= R; ++z)
@@ -108,21 +141,12 @@ int star_3d(int R, double hx, double hy, double hz, int N, int32_t* ox, int32_t*
         if (ox) {
           const double dx = x * hx, dy = y * hy, dz = z * hz;
           const double len = sqrt(dx * dx + dz * dz + dy * dy);  // eq 27 in 3D
-          const double u0 = dx / len, u1 = dy / len, u2 = dz / len;
-          int best = 0;
-          double bd = -2.0;
-          for (int i = 0; i < N; ++i) {  // nearest tabulated direction
-            const double dd = f[3 * i] * u0 + f[3 * i + 1] * u1 + f[3 * i + 2] * u2;
-            if (dd > bd) {
-              bd = dd;
-              best = i;
-            }
-          }
+          const double u[3] = {dx / len, dy / len, dz / len};
           ox[n] = x;
           oy[n] = y;
           oz[n] = z;
           L[n] = len;
-          bin[n] = best;
+          bin[n] = fib_nearest(N, u);
         }
         ++n;
       }

@@ -837,54 +837,6 @@ __global__ void __launch_bounds__(kLvlThreads) k_cell_level(CellArgs a, int L) {
 
 __global__ void k_cell_zero(int32_t* x) { *x = 0; }
 
-// 3D segment columns: one workgroup per offset o, the Fibonacci direction
-// with the largest dot product f . u_o (IEEE operations in the order of the
-// definition, no contraction), the lowest index among equals: each thread
-// keeps its first strict maximum over a strided pass, then the waves and
-// the workgroup merge (larger dot first, lower index on a tie), which is the
-// sequential rule.
-constexpr int kFibThreads = 1024;
-__global__ void __launch_bounds__(kFibThreads) k_fib_nearest(const double* f, int N,
-                                                             const double* u, int n_off,
-                                                             int32_t* col) {
-  __shared__ double s_d[kFibThreads / 64];
-  __shared__ int s_i[kFibThreads / 64];
-  const int o = blockIdx.x;  // grid = n_off
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const double u0 = u[3 * o], u1 = u[3 * o + 1], u2 = u[3 * o + 2];
-  double bd = -2.0;
-  int bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < N; i += kFibThreads) {
-    const double d = __dadd_rn(__dadd_rn(__dmul_rn(f[3 * i], u0), __dmul_rn(f[3 * i + 1], u1)),
-                               __dmul_rn(f[3 * i + 2], u2));
-    if (d > bd) {
-      bd = d;
-      bi = i;
-    }
-  }
-  for (int w = 32; w > 0; w >>= 1) {
-    const double od = __shfl_xor(bd, w);
-    const int oi = __shfl_xor(bi, w);
-    if (od > bd || (od == bd && oi < bi)) {
-      bd = od;
-      bi = oi;
-    }
-  }
-  if (lane == 0) {
-    s_d[wv] = bd;
-    s_i[wv] = bi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < kFibThreads / 64; ++w)
-      if (s_d[w] > bd || (s_d[w] == bd && s_i[w] < bi)) {
-        bd = s_d[w];
-        bi = s_i[w];
-      }
-    col[o] = bi;
-  }
-}
-
 // ---------------------------------------------------------------- plan ----
 
 // MSPM, round r: the class of each corner of each listed cell (the solve
@@ -977,7 +929,7 @@ struct CellPlan {
   int64_t n = 0, C = 0, K = 0;
   int fields[2] = {0, 0};
   bool slow = false;
-  size_t off_tab = 0, off_geo = 0, off_W = 0, off_best = 0, off_ctl = 0, off_src = 0,
+  size_t off_tab = 0, off_slot = 0, off_W = 0, off_best = 0, off_ctl = 0, off_src = 0,
          off_act = 0, off_key = 0, off_list = 0, off_hop = 0, off_bfs = 0, off_bid = 0,
          off_kt = 0, off_vt = 0, off_jobs = 0, off_part = 0, total = 0;
 };
@@ -1069,8 +1021,8 @@ int cell_plan(const CellSrc& w, int64_t n_classes, const CellGeo& G, int32_t mod
   P->off_tab = off;  // L (double), ox, oz, col, canon (int32), psi (double)
   off += al256((size_t)s2 * (sizeof(double) + 4 * sizeof(int32_t)) +
                (size_t)P->n_canon * sizeof(double) + 8);
-  P->off_geo = off;  // 3D: unit vectors [n_off][3], Fibonacci directions [N][3], slots [64]
-  if (G.dim == 3) off += al256((size_t)3 * (s2 + P->N) * sizeof(double) + 64 * sizeof(int32_t));
+  P->off_slot = off;  // 3D: slots [64]
+  if (G.dim == 3) off += al256(64 * sizeof(int32_t));
   P->off_W = off;
   if (!w.mspm) off += al256((size_t)2 * n_classes * n_classes * s2 * sizeof(double));
   P->off_best = off;
@@ -1142,14 +1094,12 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   // a stand-in offset keeps the lookups finite), lengths (eq 27), columns;
   // MSPM: canonical offsets (direction angle in [0, pi)) and their exact
   // global ray angles.  3D: offsets (dx, dy, dz) in [-cn, cn]^3, lengths and
-  // unit vectors (the columns come from k_fib_nearest), and the block's face
-  // points as slots.
+  // columns (the closest Fibonacci direction), and the block's face points as
+  // slots.
   std::vector<int32_t> tab((size_t)s2 * 4);
   std::vector<double> L((size_t)s2), psi((size_t)P.n_canon), Lc((size_t)P.n_canon);
-  std::vector<double> geo;
   std::vector<int32_t> slots;
   if (P.dim == 3) {
-    geo.assign((size_t)3 * (s2 + P.N), 0.0);
     for (int dz = -cn; dz <= cn; ++dz)
       for (int dy = -cn; dy <= cn; ++dy)
         for (int dx = -cn; dx <= cn; ++dx) {
@@ -1160,17 +1110,14 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
           tab[3 * s2 + q] = -1;
           if (dx == 0 && dy == 0 && dz == 0) {  // never a segment
             L[q] = 0.0;
-            geo[3 * q + 2] = 1.0;
             continue;
           }
           const double ex = dx * G.hx, ey = dy * G.hy, ez = dz * G.hz;
           const double len = sqrt(ex * ex + ez * ez + ey * ey);  // eq 27 in 3D
           L[q] = len;
-          geo[3 * q] = ex / len;
-          geo[3 * q + 1] = ey / len;
-          geo[3 * q + 2] = ez / len;
+          const double u[3] = {ex / len, ey / len, ez / len};
+          tab[2 * s2 + q] = fib_nearest(P.N, u);
         }
-    fibonacci(P.N, geo.data() + 3 * (size_t)s2);
     for (int z = 0; z <= cn; ++z)
       for (int y = 0; y <= cn; ++y)
         for (int x = 0; x <= cn; ++x)
@@ -1221,18 +1168,12 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
                        hipMemcpyHostToDevice, s);
   if (e == hipSuccess && w.mspm)
     e = hipMemcpyAsync(dpsi, psi.data(), psi.size() * sizeof(double), hipMemcpyHostToDevice, s);
-  double* dgeo = (double*)(ws + P.off_geo);
-  int32_t* dslot = (int32_t*)(dgeo + 3 * ((size_t)s2 + P.N));
-  if (e == hipSuccess && P.dim == 3)
-    e = hipMemcpyAsync(dgeo, geo.data(), geo.size() * sizeof(double), hipMemcpyHostToDevice, s);
+  int32_t* dslot = (int32_t*)(ws + P.off_slot);
   if (e == hipSuccess && P.dim == 3)
     e = hipMemcpyAsync(dslot, slots.data(), slots.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                        s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // host buffers are locals
   if (e != hipSuccess) return fail(CHERT_ERR_HIP, hipGetErrorString(e));
-  if (P.dim == 3)  // the closest Fibonacci direction of every offset
-    CHERT_LAUNCH("k_fib_nearest", k_fib_nearest, dim3((unsigned)s2), dim3(kFibThreads), 0, s,
-                 dgeo + 3 * (size_t)s2, P.N, dgeo, s2, dtab + 2 * s2);
 
   uint8_t* ctl = ws + P.off_ctl;
   CellArgs a{};

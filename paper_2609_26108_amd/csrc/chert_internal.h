@@ -58,10 +58,10 @@ int star_2d(int R, double hx, double hz, int n_dirs, int32_t* ox, int32_t* oz, d
 // direction, half-plane tie rounding); also for non-primitive offsets.
 int32_t star_bin_2d(int x, int z, double hx, double hz, int n_dirs);
 
-// Fibonacci ray directions f[3 N] (x, y, z) and the 3D forward star: offsets
-// with max norm <= R, gcd 1, ordered by (oy, oz, ox); lengths; bins = the
-// nearest Fibonacci direction (largest dot product, lowest index on ties).
-void fibonacci(int N, double* f);
+// The Fibonacci ray direction of N closest to the unit vector u (largest dot
+// product, lowest index on ties), and the 3D forward star: offsets with max
+// norm <= R, gcd 1, ordered by (oy, oz, ox); lengths; bins = that direction.
+int fib_nearest(int N, const double* u);
 int star_3d(int R, double hx, double hy, double hz, int N, int32_t* ox, int32_t* oy, int32_t* oz,
             double* L, int32_t* bin);
 
