@@ -8,6 +8,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace chert {
@@ -28,6 +29,23 @@ __host__ __device__ inline size_t tick_offset(int max_rounds) {
 }
 __host__ __device__ inline size_t counter_words(int max_rounds) {
   return tick_offset(max_rounds) + 2 * kTickWords;  // per-round launches: by round parity
+}
+
+// Workgroups per compute unit for a persistent grid, all of whose workgroups
+// must be resident: LDS is handed out in granules of 1280
+// bytes, which the query does not round up to (at 23.2 KB it answers seven
+// workgroups per compute unit where six fit), so two granules are added for
+// the rounding and the kernel's own few static words.
+constexpr size_t kLdsGranule = 1280;
+template <class Kern>
+inline hipError_t resident_per_cu(int* per_cu, Kern kern, int threads, size_t dynamic) {
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kern, threads,
+                                                              dynamic + 2 * kLdsGranule);
+  if (e == hipSuccess && *per_cu < 1) {  // within two granules of all of it: one workgroup
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kern, threads, dynamic);
+    if (*per_cu > 1) *per_cu = 1;
+  }
+  return e;
 }
 
 struct PersistArgs {

@@ -1635,7 +1635,7 @@ static int persist_grid(const void* kern, int threads, size_t lds, int64_t n_til
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds);
+    e = resident_per_cu(&per_cu, kern, threads, lds);
   if (e != hipSuccess) return fail(CHERT_ERR_HIP, hipGetErrorString(e));
   if (per_cu < 1) return fail(CHERT_ERR_HIP, "relaxation kernel does not fit on a compute unit");
   int64_t g = (int64_t)per_cu * cus;
