@@ -1483,7 +1483,7 @@ def run_cells(args):
             torch.cuda.synchronize()
             prof = C.chert_prof_read()
             C.chert_prof_enable(False)
-            relax_s = prof.get("k_cell_relax", (0, 0.0))[1] * 1e-3
+            relax_s = prof.get("k_cell_march", (0, 0.0))[1] * 1e-3
             row[str(mode)] = {"s": ts, "rounds": st.rounds[0], "bfs_levels": st.rounds[1],
                               "cell_visits": st.tile_visits[0],
                               "pair_relaxations": st.edge_relaxations[0],
@@ -1533,7 +1533,7 @@ def run_cells(args):
                 C.chert_trace_cells(desc, cache, K, cg, mode, bsrc,
                                     C.trace_opts(outs, bucket_width=o_bw, stats=st), t["tr"],
                                     t["ti"], t["ts"], t["pp"], t["pa"], tws, stream=stream)
-            ks, kp, kn = _batch_relax_profile(C, torch, call, "k_cell_relax")
+            ks, kp, kn = _batch_relax_profile(C, torch, call, "k_cell_march")
             rk_s += ks
             rk_p += kp
             rk_n += kn
@@ -1552,7 +1552,7 @@ def run_cells(args):
     ach = 2.0 * dom["relax_kernel_pairs"] / max(dom["relax_kernel_s"], 1e-12) / 1e12
     res["roofline"] = {"bound": "alu", "achieved": ach, "peak": FP64_VALU_PEAK_TOPS,
                        "unit": "TFLOP/s", "frac": ach / FP64_VALU_PEAK_TOPS, "traffic": None,
-                       "kernel": "k_cell_relax",
+                       "kernel": "k_cell_march",
                        "avg_launch_us": 1e6 * dom["relax_kernel_s"] / max(dom["relax_kernel_launches"], 1)}
     if not args.no_cpu:
         import oracle as O

@@ -17,6 +17,11 @@
 // round holds many cells).  The fixed point is the network's shortest-path
 // traveltimes whatever the schedule.
 //
+// 2D cached networks whose cells' keys fit in LDS run all rounds of a problem
+// in one workgroup (k_cell_march), several cells per wave, and the BFS below
+// likewise (k_cell_tree): a round there is a few microseconds of LDS work
+// instead of two launches whose loads all miss the caches.
+//
 // Predecessors and t*: level-synchronous BFS over tight segments
 // (tau_i + w_ij == tau_j) from the source, one launch per level, threads
 // over (node, boundary slot) pairs: pred_j = the tight neighbour one
@@ -133,7 +138,8 @@ struct CellArgs {
   int ns, n_off;       // boundary nodes per cell; segment offsets (side^dim)
   int64_t n, C;
   const int32_t* cls;  // lattice -> class
-  const int32_t* slot; // 3D: [ns] local point of slot s, lx | ly << 8 | lz << 16
+  const int32_t* slot; // 3D: [ns] local point of slot s, lx | ly << 8 | lz << 16; then at
+                       // 64 + (lz (cn + 1) + ly) (cn + 1) + lx the slot of a face point
   const double* W;     // [2][K][K][n_off]
   double* tau[2];      // per field slot: rows [n_src][n]
   int field_of[2];     // field slot -> 0 (propagation) or 1 (attenuation)
@@ -154,6 +160,9 @@ struct CellArgs {
   int32_t* bnd;        // [3][P] end of level L in slot L % 3
   int32_t* cnt;        // [3][P] nodes appended during level L in slot L % 3
   int32_t* alive;      // most BFS levels over the problems
+  unsigned long long* mask;  // [P][C][ns] tight heads of each cell's slots (k_cell_tight)
+  unsigned long long* tkey;  // [P][n] hop << 32 | predecessor (k_cell_tree; then hop, bid: null)
+  int32_t* march;      // [0] most rounds of a problem, [1] problems that hit the cap
   int32_t* pred[2];    // per field slot, rows [n_src][n] (nullable)
   double* tstar;       // rows [n_src][n] for the propagation slot (nullable)
   int tree_mask;       // bit fi: problems of field slot fi need the tree
@@ -358,13 +367,15 @@ __global__ void k_cell_fill(CellArgs a) {
   double* t = a.tau[fi] + (int64_t)s * a.n;
   int32_t* pr = a.pred[fi] ? a.pred[fi] + (int64_t)s * a.n : nullptr;
   double* ts = (a.tstar && a.field_of[fi] == 0) ? a.tstar + (int64_t)s * a.n : nullptr;
-  int32_t* hp = a.hop + (int64_t)p * a.n;
-  int32_t* bd = a.bid + (int64_t)p * a.n;
+  int32_t* hp = a.hop ? a.hop + (int64_t)p * a.n : nullptr;
+  int32_t* bd = a.hop ? a.bid + (int64_t)p * a.n : nullptr;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
        i += (int64_t)gridDim.x * blockDim.x) {
     t[i] = INFINITY;
-    hp[i] = -1;
-    bd[i] = 0x7fffffff;
+    if (hp) {
+      hp[i] = -1;
+      bd[i] = 0x7fffffff;
+    }
     if (pr) pr[i] = -1;
     if (ts) ts[i] = INFINITY;
   }
@@ -388,6 +399,7 @@ __global__ void k_cell_fill(CellArgs a) {
     if (threadIdx.x < 2) a.count[threadIdx.x] = 0;
     if (threadIdx.x < 4) a.stats[threadIdx.x] = 0;
     if (threadIdx.x == 3) *a.alive = 0;
+    if (threadIdx.x >= 4 && threadIdx.x < 6) a.march[threadIdx.x - 4] = 0;
   }
 }
 
@@ -407,7 +419,7 @@ __global__ void k_cell_seed(CellArgs a) {
   }
   // level 0 of the BFS: the source alone (end of "level -1" = 0, one node)
   if ((a.tree_mask >> fi) & 1) {
-    a.hop[(int64_t)p * a.n + src] = 0;
+    if (a.hop) a.hop[(int64_t)p * a.n + src] = 0;
     a.bfs[(int64_t)p * a.n] = (int32_t)src;
     if (a.tstar && a.field_of[fi] == 0) a.tstar[(int64_t)s * a.n + src] = 0.0;
   }
@@ -835,6 +847,413 @@ __global__ void __launch_bounds__(kLvlThreads) k_cell_level(CellArgs a, int L) {
   if (threadIdx.x == 0 && s_any) atomicMax(a.alive, L + 2);
 }
 
+// ------------------------------------- one workgroup per problem (2D) ---
+constexpr int kMarchThreads = 1024;
+constexpr size_t kTightTable = 48 * 1024;  // class-pair table k_cell_tight stages
+constexpr size_t kMarchLds = 156 * 1024;  // most LDS its dynamic part may take
+constexpr int kMarchWaves = kMarchThreads / 64;
+
+// LDS of k_cell_march: the field's class-pair table (table_n doubles, 0: read
+// from L2), the cells' keys, each wave's traveltimes and weight-row bases, the
+// round's list.
+size_t march_lds(int64_t table_n, int64_t C) {
+  return (size_t)table_n * sizeof(double) + (size_t)C * sizeof(unsigned long long) +
+         kMarchThreads * (sizeof(double) + sizeof(int32_t)) + (size_t)((C + 3) & ~3LL) * sizeof(uint16_t);
+}
+
+// All traveltime rounds of one problem (blockIdx.x) in one workgroup.  A
+// round takes the woken cells (key < inf; when ordered, within the width of
+// the smallest key) and visits them, 64 / ns cells per wave, a lane per
+// boundary node: Jacobi passes over the cell's ordered pairs until none of the
+// wave's cells changes, weights from the class-pair table (the segment offset
+// is a difference of lattice codes, so a pair's entry is a lane's base plus
+// the tail's), then the improved nodes are lowered and the neighbouring
+// cells' keys with them.  Same fixed point as the launches per round.
+// 16 sources on 80 x 40 cells of 5 x 5, both fields: 4.1 -> 1.4 ms.
+// NR > 0: cells of at most NR boundary nodes; a lane's weights stay in NR
+// registers from the visit's first pass on, so a later pass is ns broadcasts.
+template <bool WLDS, int NR>
+__global__ void __launch_bounds__(kMarchThreads) k_cell_march(CellArgs a, int max_rounds) {
+  extern __shared__ double s_w[];
+  __shared__ unsigned long long s_min[2];
+  __shared__ int s_cnt[2];
+  __shared__ unsigned long long s_stat[3];
+  const int p = blockIdx.x;
+  const int fi = p / a.n_src, f = a.field_of[fi];
+  const int cn = a.cn, ns = 4 * cn, K = a.K, C = (int)a.C, side = a.side;
+  const int s2 = a.n_off;
+  const int table_n = K * K * s2;
+  unsigned long long* key = (unsigned long long*)(s_w + (WLDS ? table_n : 0));
+  double* s_t = (double*)(key + C);
+  int32_t* s_b = (int32_t*)(s_t + kMarchThreads);
+  uint16_t* list = (uint16_t*)(s_b + kMarchThreads);
+  const double* Wg = a.W + (int64_t)f * table_n;
+  double* tau = tau_row(a, p);
+  if constexpr (WLDS)
+    for (int q = threadIdx.x; q < table_n; q += blockDim.x) s_w[q] = Wg[q];
+  for (int c = threadIdx.x; c < C; c += blockDim.x) key[c] = kInfBits;
+  if (threadIdx.x < 2) {
+    s_min[threadIdx.x] = kInfBits;
+    s_cnt[threadIdx.x] = 0;
+  }
+  if (threadIdx.x < 3) s_stat[threadIdx.x] = 0ull;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int64_t src = a.src[p - fi * a.n_src];
+    int cs[4];
+    const int nc = cells_of((int)(src % a.NX), (int)(src / a.NX), cn, a.ncx, a.ncz, cs);
+    for (int q = 0; q < nc; ++q) key[cs[q]] = 0ull;
+  }
+  const double w = a.bucket > 0.0 ? a.bucket * a.wmin[f] : INFINITY;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int cpw = 64 / ns;  // cells a wave visits side by side
+  const int g = lane / ns, sl = lane - g * ns;
+  int lx, lz;
+  slot_xy(sl, cn, lx, lz);
+  const int code = lz * side + lx;
+  double* const t_w = s_t + wave * 64 + (g < cpw ? g * ns : 0);
+  int32_t* const b_w = s_b + wave * 64 + (g < cpw ? g * ns : 0);
+  unsigned long long visits = 0, pairs = 0, passes_all = 0;
+  int r = 0;
+  for (;; ++r) {
+    __syncthreads();  // the keys of the last round's wakes
+    // the smallest key, then the cells within the width of it
+    unsigned long long lo = kInfBits;
+    for (int c = threadIdx.x; c < C; c += blockDim.x) lo = min(lo, key[c]);
+    for (int d = 32; d >= 1; d >>= 1) lo = min(lo, __shfl_xor(lo, d));
+    if (lane == 0 && lo != kInfBits) atomicMin(&s_min[r & 1], lo);
+    __syncthreads();
+    lo = s_min[r & 1];
+    if (lo == kInfBits || r >= max_rounds) break;  // workgroup-uniform
+    const double lim = __longlong_as_double((long long)lo) + w;
+    for (int c0 = 0; c0 < C; c0 += blockDim.x) {
+      const int c = c0 + threadIdx.x;
+      const unsigned long long k = c < C ? key[c] : kInfBits;
+      const bool take = k != kInfBits && __longlong_as_double((long long)k) <= lim;
+      const unsigned long long m = __ballot(take);
+      if (!m) continue;
+      int pos = 0;
+      if (lane == 0) pos = atomicAdd(&s_cnt[r & 1], __popcll(m));
+      pos = __shfl(pos, 0);
+      if (take) {
+        list[pos + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)c;
+        key[c] = kInfBits;
+      }
+    }
+    __syncthreads();
+    const int count = s_cnt[r & 1];
+    if (threadIdx.x == 0) {  // read before this round's last barrier
+      s_cnt[(r + 1) & 1] = 0;
+      s_min[(r + 1) & 1] = kInfBits;
+    }
+    for (int it0 = wave * cpw; it0 < count; it0 += kMarchWaves * cpw) {
+      const int it = it0 + g;
+      const bool on = g < cpw && it < count;
+      const int c = on ? list[it] : 0;
+      const int x0 = (c % a.ncx) * cn, z0 = (c / a.ncx) * cn;
+      const int64_t node = (int64_t)(x0 + lx) + (int64_t)a.NX * (z0 + lz);
+      double t = INFINITY;
+      int k = 0;
+      if (on) {
+        t = __hip_atomic_load(&tau[node], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        k = a.cls[node];
+      }
+      const double t0 = t;
+      // entry of the pair (a -> this lane): W[ka][k][code - code_a + centre]
+      const int mine = k * s2 + code + cn * side + cn;
+      if (on) b_w[sl] = k * K * s2 - code;
+      int passes = 0;
+      double wr[NR > 0 ? NR : 1];
+      for (;;) {
+        if (on) t_w[sl] = t;
+        wave_sync_lds();
+        double best = t;
+        if constexpr (NR > 0) {
+          if (passes == 0) {
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+              wr[u] = INFINITY;
+              if (u < ns && on && u != sl) {
+                const int e = b_w[u] + mine;
+                wr[u] = WLDS ? s_w[e] : Wg[e];
+              }
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < NR; ++u)
+            if (u < ns) {  // uniform
+              const double cand = t_w[u] + wr[u];
+              if (cand < best) best = cand;
+            }
+        } else {
+          for (int sa = 0; sa < ns; sa += 4) {  // (ns is a multiple of 4)
+            double ta[4], wv[4];
+            int e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              ta[u] = t_w[sa + u];
+              e[u] = b_w[sa + u] + mine;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) wv[u] = on ? (WLDS ? s_w[e[u]] : Wg[e[u]]) : 0.0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const double cand = ta[u] + wv[u];
+              if (sa + u != sl && cand < best) best = cand;
+            }
+          }
+        }
+        ++passes;
+        const bool ch = on && best < t;
+        if (on) t = best;
+        wave_sync_lds();  // every lane has read the pass's values
+        if (!__ballot(ch)) break;
+      }
+      if (on && sl == 0) {
+        ++visits;
+        pairs += (unsigned long long)passes * ns * (ns - 1);
+        passes_all += passes;
+      }
+      if (on && t < t0) {
+        const unsigned long long nb = dbits(t);
+        __hip_atomic_fetch_min((unsigned long long*)&tau[node], nb, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        // the other cells this node lies on, woken with its new value
+        const int cx = c % a.ncx, cz = c / a.ncx;
+        const int ex = lx == 0 ? -1 : (lx == cn ? 1 : 0), ez = lz == 0 ? -1 : (lz == cn ? 1 : 0);
+        const bool hx = ex != 0 && cx + ex >= 0 && cx + ex < a.ncx;
+        const bool hz = ez != 0 && cz + ez >= 0 && cz + ez < a.ncz;
+        if (hx) atomicMin(&key[c + ex], nb);
+        if (hz) atomicMin(&key[c + ez * a.ncx], nb);
+        if (hx && hz) atomicMin(&key[c + ez * a.ncx + ex], nb);
+      }
+    }
+  }
+  if (visits) {
+    atomicAdd(&s_stat[0], visits);
+    atomicAdd(&s_stat[1], pairs);
+    atomicAdd(&s_stat[2], passes_all);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 0; i < 3; ++i) atomicAdd(&a.stats[i], s_stat[i]);
+    atomicMax(&a.march[0], r);
+    if (s_min[r & 1] != kInfBits) atomicAdd(&a.march[1], 1);  // the round cap
+  }
+}
+
+// Tight segments of every cell once the traveltimes are final: bit b of
+// mask[(problem, cell)][slot i] is set when tau_i + w(i -> b) == tau_b.  Waves
+// of 64 / ns cells, a lane per head; a pass over the tails turns each tail's
+// ballot into its row.  (WLDS: the field's class-pair table staged in LDS.)
+template <bool MSPM, bool D3, bool WLDS>
+__global__ void __launch_bounds__(kCellThreads) k_cell_tight(CellArgs a) {
+  static_assert(!MSPM || (!D3 && !WLDS), "MSPM runs on the 2D cell network, without a table");
+  extern __shared__ double s_w[];
+  __shared__ double s_t[kCellThreads];
+  __shared__ int32_t s_b[kCellThreads];
+  const int p = blockIdx.y, fi = p / a.n_src;
+  if (!((a.tree_mask >> fi) & 1)) return;
+  const int f = a.field_of[fi];
+  const int cn = a.cn, ns = D3 ? a.ns : 4 * cn, K = a.K, side = a.side, s2 = a.n_off;
+  const double* Wg = MSPM ? nullptr : a.W + (int64_t)f * K * K * s2;
+  if constexpr (WLDS) {
+    for (int q = threadIdx.x; q < K * K * s2; q += blockDim.x) s_w[q] = Wg[q];
+    __syncthreads();
+  }
+  const double* tau = tau_row(a, p);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int cpw = 64 / ns, g = lane / ns, sl = lane - g * ns;
+  int lx = 0, ly = 0, lz = 0;
+  if (g < cpw) slot_pos<D3>(a, sl, lx, ly, lz);
+  const int code = D3 ? (lz * side + ly) * side + lx : lz * side + lx;
+  const int centre = D3 ? (cn * side + cn) * side + cn : cn * side + cn;
+  double* const t_w = s_t + wave * 64 + (g < cpw ? g * ns : 0);
+  int32_t* const b_w = s_b + wave * 64 + (g < cpw ? g * ns : 0);
+  const unsigned long long row_bits = ns < 64 ? (1ull << ns) - 1ull : ~0ull;
+  const int64_t step = (int64_t)gridDim.x * kCellWaves * cpw;
+  for (int64_t c0 = ((int64_t)blockIdx.x * kCellWaves + wave) * cpw; c0 < a.C; c0 += step) {
+    const int64_t c = c0 + g;
+    const bool on = g < cpw && c < a.C;
+    int x0 = 0, y0 = 0, z0 = 0;
+    double t = INFINITY;
+    int k = 0;
+    int64_t node = 0;
+    if (on) {
+      cell_origin<D3>(a, (int)c, x0, y0, z0);
+      node = node_at(a, x0 + lx, y0 + ly, z0 + lz);
+      t = tau[node];
+      if constexpr (!MSPM) k = a.cls[node];
+      t_w[sl] = t;
+      b_w[sl] = MSPM ? (lx | lz << 16) : k * K * s2 - code;
+    }
+    wave_sync_lds();
+    const int mine = k * s2 + code + centre;
+    unsigned long long row = 0ull;
+    for (int sa = 0; sa < ns; ++sa) {
+      bool tight = false;
+      if (on && sa != sl && t < INFINITY) {
+        double w;
+        if constexpr (MSPM) {
+          const int q = b_w[sa];
+          w = seg_weight<true, false>(a, f, (int)c, node_at(a, x0 + (q & 0xffff), 0, z0 + (q >> 16)),
+                                      node);
+        } else {
+          const int e = b_w[sa] + mine;
+          w = WLDS ? s_w[e] : Wg[e];
+        }
+        tight = t_w[sa] + w == t;
+      }
+      const unsigned long long m = __ballot(tight);
+      if (sa == sl) row = g < cpw ? (m >> (g * ns)) & row_bits : 0ull;
+    }
+    if (on) a.mask[((int64_t)p * a.C + c) * ns + sl] = row;
+    wave_sync_lds();  // LDS reused by the wave's next cells
+  }
+}
+
+// slot of a boundary point of a cell (block)
+template <bool D3>
+__device__ __forceinline__ int slot_index(const CellArgs& a, int lx, int ly, int lz) {
+  const int cn = a.cn;
+  if constexpr (D3) return a.slot[64 + (lz * (cn + 1) + ly) * (cn + 1) + lx];
+  if (lz == 0 && lx < cn) return lx;
+  if (lx == cn && lz < cn) return cn + lz;
+  return lz == cn && lx > 0 ? 3 * cn - lx : 4 * cn - lz;
+}
+
+// The BFS over tight segments of one problem (blockIdx.x) in one workgroup.
+// A node's key is (hop << 32 | tail): items (node of the level, cell it lies
+// on) put that cell's tight heads into a queue in LDS; after a barrier the
+// (head, tail) pairs are dealt evenly, each lowering its head's key to (L + 1,
+// tail) with one returning atomic min -- whoever finds the key unset appends
+// the head to the next level, and the smallest tail of the level above is the
+// predecessor that stays.  Meanwhile other threads take the level's own keys,
+// final since the last level, as predecessors and fold t*.  Every step of that
+// chain is a memory round trip, so the keys are cleared by this workgroup
+// (they then sit in its L2), the level's nodes and t*'s weight table are in
+// LDS, and a thread loads four items' rows before it queues any (walking its
+// heads one returning atomic after the other, a lane with ten of them held its
+// wave for ten round trips).
+// 80 x 40 cells, 16 sources, both fields, 256 levels: 4.2 (a launch per level)
+// -> 1.0 ms; 18 x 18 x 4 blocks, 4 sources, 40 levels: 1.2 -> 0.8 ms.
+constexpr int kTreeList = 4096;   // nodes of a level kept in LDS (the rest in bfs)
+constexpr int kTreeQueue = 6144;  // pairs queued at a time (the rest are taken at once)
+template <bool MSPM, bool D3>
+__global__ void __launch_bounds__(kMarchThreads) k_cell_tree(CellArgs a, int table_n) {
+  static_assert(!(MSPM && D3), "MSPM runs on the 2D cell network");
+  constexpr int kCells = D3 ? 8 : 4;  // cells (blocks) a node can lie on
+  constexpr int kItems = 4;
+  extern __shared__ double s_w[];  // [table_n] the attenuation field's class-pair table
+  __shared__ int32_t s_list[2][kTreeList];
+  __shared__ int2 s_queue[kTreeQueue];
+  __shared__ int s_cnt[2], s_np;
+  const int p = blockIdx.x;
+  const int fi = p / a.n_src, s = p - fi * a.n_src;
+  if (!((a.tree_mask >> fi) & 1)) return;
+  const int ns = D3 ? a.ns : 4 * a.cn, cn = a.cn, K = a.K, s2 = a.n_off;
+  unsigned long long* key = a.tkey + (int64_t)p * a.n;
+  int32_t* bfs = a.bfs + (int64_t)p * a.n;
+  int32_t* pred = a.pred[fi] ? a.pred[fi] + (int64_t)s * a.n : nullptr;
+  double* ts = (a.tstar && a.field_of[fi] == 0) ? a.tstar + (int64_t)s * a.n : nullptr;
+  const unsigned long long* mask = a.mask + (int64_t)p * a.C * ns;
+  const int64_t src = a.src[s];
+  for (int64_t i = threadIdx.x; i < a.n; i += blockDim.x) key[i] = i == src ? 0ull : ~0ull;
+  if (ts)
+    for (int q = threadIdx.x; q < table_n; q += blockDim.x) s_w[q] = a.W[(int64_t)K * K * s2 + q];
+  if (threadIdx.x < 2) s_cnt[threadIdx.x] = 0;
+  if (threadIdx.x == 0) {
+    s_list[0][0] = (int32_t)src;
+    s_np = 0;
+  }
+  int start = 0, nf = 1, L = 0;  // bfs[start + q]: node q of the level
+  __syncthreads();
+  for (; nf > 0; ++L) {
+    const int32_t* cur = s_list[L & 1];
+    int32_t* nxt = s_list[(L + 1) & 1];
+    const int work = nf * kCells;
+    auto take = [&](int v, int j) {
+      const unsigned long long mine = ((unsigned long long)(L + 1) << 32) | (unsigned)j;
+      if (__hip_atomic_fetch_min(&key[v], mine, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP) != ~0ull)
+        return;
+      const int i = atomicAdd(&s_cnt[L & 1], 1);
+      if (i < kTreeList) nxt[i] = v;
+      else bfs[start + nf + i] = v;
+    };
+    for (int t0 = 0; t0 < work; t0 += kItems * blockDim.x) {
+      unsigned long long m[kItems];
+      int org[kItems][3], node[kItems];
+#pragma unroll
+      for (int u = 0; u < kItems; ++u) {
+        const int t = t0 + u * (int)blockDim.x + (int)threadIdx.x;
+        m[u] = 0ull;
+        if (t >= work) continue;
+        const int i = t / kCells, q = t % kCells;
+        const int j = i < kTreeList ? cur[i] : bfs[start + i];
+        int jx, jy, jz;
+        node_xyz<D3>(a, j, jx, jy, jz);
+        // the q-th of the node's cells: the upper or the lower one per axis
+        int cx = jx / cn, cy = D3 ? jy / cn : 0, cz = jz / cn;
+        const bool bx = jx == cx * cn, by = D3 && jy == cy * cn, bz = jz == cz * cn;
+        if (((q & 1) && !bz) || ((q & 2) && !bx) || ((q & 4) && !by)) continue;
+        cz -= q & 1;
+        cx -= (q >> 1) & 1;
+        cy -= (q >> 2) & 1;
+        if (cx < 0 || cy < 0 || cz < 0 || cx >= a.ncx || cy >= a.ncy || cz >= a.ncz) continue;
+        org[u][0] = cx * cn;
+        org[u][1] = cy * cn;
+        org[u][2] = cz * cn;
+        node[u] = j;
+        const int64_t c = cx + (int64_t)a.ncx * (D3 ? cy + (int64_t)a.ncy * cz : cz);
+        m[u] = mask[c * ns + slot_index<D3>(a, jx - org[u][0], jy - org[u][1], jz - org[u][2])];
+      }
+#pragma unroll
+      for (int u = 0; u < kItems; ++u) {
+        if (!m[u]) continue;
+        int at = atomicAdd(&s_np, __popcll(m[u]));
+        for (; m[u]; m[u] &= m[u] - 1ull, ++at) {
+          int lx, ly, lz;
+          slot_pos<D3>(a, __builtin_ctzll(m[u]), lx, ly, lz);
+          const int v = (int)node_at(a, org[u][0] + lx, org[u][1] + ly, org[u][2] + lz);
+          if (at < kTreeQueue) s_queue[at] = make_int2(v, node[u]);
+          else take(v, node[u]);
+        }
+      }
+    }
+    __syncthreads();
+    const int np = s_np < kTreeQueue ? s_np : kTreeQueue;
+    for (int q = threadIdx.x; q < np; q += blockDim.x) take(s_queue[q].x, s_queue[q].y);
+    // this level's predecessors and t*, from the last threads on
+    for (int q = blockDim.x - 1 - threadIdx.x; L > 0 && q < nf; q += blockDim.x) {
+      const int64_t j = q < kTreeList ? cur[q] : bfs[start + q];
+      const int64_t b = (int64_t)(__hip_atomic_load(&key[j], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP) & 0xffffffffull);
+      if (pred) pred[j] = (int32_t)b;
+      if (!ts) continue;
+      double w;
+      if (!MSPM && table_n) {
+        int ix, iy, iz, jx, jy, jz;
+        node_xyz<D3>(a, b, ix, iy, iz);
+        node_xyz<D3>(a, j, jx, jy, jz);
+        w = s_w[(a.cls[b] * K + a.cls[j]) * s2 + off_of<D3>(a, jx - ix, jy - iy, jz - iz)];
+      } else {
+        w = seg_weight<MSPM, D3>(a, 1, MSPM ? common_cell(a, b, j) : 0, b, j);
+      }
+      ts[j] = ts[b] + w;
+    }
+    __syncthreads();
+    start += nf;
+    nf = s_cnt[L & 1];
+    if (threadIdx.x == 0) {  // read before this barrier
+      s_cnt[(L + 1) & 1] = 0;
+      s_np = 0;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) atomicMax(a.alive, L);  // levels 0 .. L - 1 hold nodes
+}
+
 __global__ void k_cell_zero(int32_t* x) { *x = 0; }
 
 // ---------------------------------------------------------------- plan ----
@@ -930,9 +1349,17 @@ struct CellPlan {
   int fields[2] = {0, 0};
   bool slow = false;
   size_t off_tab = 0, off_slot = 0, off_W = 0, off_best = 0, off_ctl = 0, off_src = 0,
-         off_act = 0, off_key = 0, off_list = 0, off_hop = 0, off_bfs = 0, off_bid = 0,
+         off_act = 0, off_key = 0, off_list = 0, off_hop = 0, off_mask = 0, off_bfs = 0,
          off_kt = 0, off_vt = 0, off_jobs = 0, off_part = 0, total = 0;
 };
+
+// Lattice points up to which one workgroup runs a problem's BFS: its levels
+// are then narrow enough for 1024 threads (beyond, a launch per level over
+// many workgroups catches up).
+constexpr int64_t kTreeNodes = 1 << 20;
+bool single_tree(const CellPlan& P, uint32_t outs) {
+  return (outs & (CHERT_OUT_PRED_P | CHERT_OUT_PRED_A)) && P.n <= kTreeNodes;
+}
 
 int cell_plan(const CellSrc& w, int64_t n_classes, const CellGeo& G, int32_t mode,
               const int64_t* src, int32_t n_src, const chert_trace_opts* o, CellPlan* P) {
@@ -1021,8 +1448,8 @@ int cell_plan(const CellSrc& w, int64_t n_classes, const CellGeo& G, int32_t mod
   P->off_tab = off;  // L (double), ox, oz, col, canon (int32), psi (double)
   off += al256((size_t)s2 * (sizeof(double) + 4 * sizeof(int32_t)) +
                (size_t)P->n_canon * sizeof(double) + 8);
-  P->off_slot = off;  // 3D: slots [64]
-  if (G.dim == 3) off += al256(64 * sizeof(int32_t));
+  P->off_slot = off;  // 3D: slots [64], slots by point [(cn + 1)^3 <= 64]
+  if (G.dim == 3) off += al256(128 * sizeof(int32_t));
   P->off_W = off;
   if (!w.mspm) off += al256((size_t)2 * n_classes * n_classes * s2 * sizeof(double));
   P->off_best = off;
@@ -1046,11 +1473,12 @@ int cell_plan(const CellSrc& w, int64_t n_classes, const CellGeo& G, int32_t mod
   off += al256((size_t)P->n_prob * P->C * sizeof(unsigned long long));
   P->off_list = off;
   off += al256((size_t)P->n_prob * P->C * sizeof(int32_t));
-  P->off_hop = off;
-  off += al256((size_t)P->n_prob * P->n * sizeof(int32_t));
+  P->off_hop = off;  // k_cell_tree: keys; else hop and bid
+  off += 2 * al256((size_t)P->n_prob * P->n * sizeof(int32_t));
+  P->off_mask = off;
+  if (single_tree(*P, outs))
+    off += al256((size_t)P->n_prob * P->C * P->ns * sizeof(unsigned long long));
   P->off_bfs = off;
-  off += al256((size_t)P->n_prob * P->n * sizeof(int32_t));
-  P->off_bid = off;
   off += al256((size_t)P->n_prob * P->n * sizeof(int32_t));
   P->total = off;
   return CHERT_OK;
@@ -1124,6 +1552,10 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
           if (x == 0 || y == 0 || z == 0 || x == cn || y == cn || z == cn)
             slots.push_back(x | (y << 8) | (z << 16));
     if ((int)slots.size() != P.ns) return fail(CHERT_ERR_INVALID_ARG, "block slot count");
+    slots.resize(128, 0);
+    for (int q = 0; q < P.ns; ++q)
+      slots[64 + ((slots[q] >> 16) * (cn + 1) + ((slots[q] >> 8) & 255)) * (cn + 1) +
+            (slots[q] & 255)] = q;
   }
   for (int dz = -cn; dz <= cn && P.dim == 2; ++dz)
     for (int dx = -cn; dx <= cn; ++dx) {
@@ -1198,6 +1630,7 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   a.count = (int32_t*)ctl;
   int32_t* err = (int32_t*)(ctl + 8);
   a.alive = (int32_t*)(ctl + 12);
+  a.march = (int32_t*)(ctl + 64);
   a.stats = (unsigned long long*)(ctl + 16);
   a.part = (unsigned long long*)(ws + P.off_part);
   double* wmin = (double*)(ctl + 48);
@@ -1208,9 +1641,11 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   a.active = (int32_t*)(ws + P.off_act);
   a.key = (unsigned long long*)(ws + P.off_key);
   a.list = (int32_t*)(ws + P.off_list);
-  a.hop = (int32_t*)(ws + P.off_hop);
   a.bfs = (int32_t*)(ws + P.off_bfs);
-  a.bid = (int32_t*)(ws + P.off_bid);
+  const bool tree1 = single_tree(P, outs);
+  a.hop = tree1 ? nullptr : (int32_t*)(ws + P.off_hop);
+  a.bid = (int32_t*)(ws + P.off_hop + al256((size_t)P.n_prob * P.n * sizeof(int32_t)));
+  a.tkey = (unsigned long long*)(ws + P.off_hop);
   a.bucket = o->bucket_width;
   a.tree_mask = 0;
   for (int fi = 0; fi < P.nfs; ++fi) {
@@ -1293,6 +1728,22 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   const unsigned gp = (unsigned)((P.n_prob + 255) / 256);
   CHERT_LAUNCH("k_cell_seed", k_cell_seed, dim3(gp), dim3(256), 0, s, a);
 
+  // 2D: one workgroup per problem for all rounds, its cells' keys in LDS (not
+  // with an abort word, which the host polls between launches)
+  int64_t table_n = P.K * P.K * s2;
+  if (march_lds(table_n, P.C) > kMarchLds) table_n = 0;
+  const bool march = P.dim == 2 && !w.mspm && !o->abort_flag_host && P.C <= 65535 &&
+                     march_lds(table_n, P.C) <= kMarchLds;
+  a.mask = (unsigned long long*)(ws + P.off_mask);
+  void (*km)(CellArgs, int) =
+      P.ns <= 16 ? (table_n ? k_cell_march<true, 16> : k_cell_march<false, 16>)
+      : P.ns <= 24 ? (table_n ? k_cell_march<true, 24> : k_cell_march<false, 24>)
+      : P.ns <= 32 ? (table_n ? k_cell_march<true, 32> : k_cell_march<false, 32>)
+                   : (table_n ? k_cell_march<true, 0> : k_cell_march<false, 0>);
+  if (march)
+    CHERT_LAUNCH("k_cell_march", km, dim3((unsigned)P.n_prob), dim3(kMarchThreads), march_lds(table_n, P.C), s, a,
+                 P.max_rounds);
+
   // traveltime rounds, the host checking the round's list size every group
   const int64_t items = (int64_t)P.n_prob * P.C;
   const unsigned gsel = (unsigned)((items + 255) / 256 > 2048 ? 2048 : (items + 255) / 256);
@@ -1312,7 +1763,7 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   const unsigned gjobs = (unsigned)((4 * items + 255) / 256 > 1024 ? 1024 : (4 * items + 255) / 256);
   const int64_t gsolve = 4 * items > 16384 ? 16384 : 4 * items;
   int rounds = -1;
-  for (int r = 0; r < P.max_rounds && rounds < 0;) {
+  for (int r = 0; r < P.max_rounds && rounds < 0 && !march;) {
     const int group = r < 16 ? 16 : 32;
     const int nb = r + group > P.max_rounds ? P.max_rounds - r : group;
     for (int q = 0; q < nb; ++q) {
@@ -1342,12 +1793,45 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
       return fail(CHERT_ERR_ABORTED, "aborted by the caller");
     if (cnt == 0) rounds = r;
   }
-  if (rounds < 0) return fail(CHERT_ERR_NO_CONVERGENCE, "round cap reached");
+  if (rounds < 0 && !march) return fail(CHERT_ERR_NO_CONVERGENCE, "round cap reached");
 
-  // predecessors and t*: one launch per level, the host checking between
-  // groups of levels
+  // predecessors and t*: in one workgroup per problem, or one launch per
+  // level, the host checking between groups of levels
   int levels = 0;
-  if (a.tree_mask) {
+  if (a.tree_mask && tree1) {
+    const size_t tw = (size_t)P.K * P.K * s2 * sizeof(double);
+    const bool wl = !w.mspm && tw <= kTightTable;
+    void (*kt)(CellArgs) =
+        w.mspm ? k_cell_tight<true, false, false>
+               : (P.dim == 3 ? (wl ? k_cell_tight<false, true, true> : k_cell_tight<false, true, false>)
+                             : (wl ? k_cell_tight<false, false, true>
+                                   : k_cell_tight<false, false, false>));
+    const int64_t per = kCellWaves * (64 / P.ns);  // cells a workgroup takes at a time
+    const int64_t want = 2048 / P.n_prob > 0 ? 2048 / P.n_prob : 1;
+    const int64_t have = (P.C + per - 1) / per;
+    CHERT_LAUNCH("k_cell_tight", kt, dim3((unsigned)(have < want ? have : want), (unsigned)P.n_prob),
+                 dim3(kCellThreads), wl ? tw : 0, s, a);
+    CHERT_LAUNCH("k_cell_tree",
+                 (w.mspm ? k_cell_tree<true, false>
+                         : (P.dim == 3 ? k_cell_tree<false, true> : k_cell_tree<false, false>)),
+                 dim3((unsigned)P.n_prob), dim3(kMarchThreads), wl ? tw : 0, s, a,
+                 wl ? (int)(tw / sizeof(double)) : 0);
+  }
+  if (march || (a.tree_mask && tree1)) {
+    int32_t alive = 0, done[2] = {0, 0};
+    e = hipMemcpyAsync(&alive, a.alive, sizeof(alive), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(done, a.march, sizeof(done), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = hipGetLastError();
+    if (e != hipSuccess) return fail(CHERT_ERR_HIP, hipGetErrorString(e));
+    if (o->abort_flag_host && *o->abort_flag_host)
+      return fail(CHERT_ERR_ABORTED, "aborted by the caller");
+    if (tree1 && a.tree_mask) levels = alive;
+    if (march) rounds = done[0];
+    if (done[1]) return fail(CHERT_ERR_NO_CONVERGENCE, "round cap reached");
+  }
+  if (a.tree_mask && !tree1) {
     // few workgroups per problem: each reserves its staged appends with one
     // atomic per flush
     unsigned gx = (unsigned)(1024 / P.n_prob);
