@@ -459,6 +459,8 @@ constexpr double kFoldMargin = 2.0 * kPi / 180.0;   // guard band around a fold
 constexpr int kFoldBins = 720;                      // 0.5-degree ray-angle bins
 constexpr int kFoldWords = (kFoldBins + 31) / 32;
 constexpr double kWarmSlope = 0.05;                 // accepted roots: slope at least this
+constexpr int kWarmParts = 64;                      // most lists of fold directions
+constexpr int kLenStride = 16;                      // their lengths: a 128-byte line each
 
 // a bracket of a fold direction's windowed table: sweep sample j and the
 // (theta_I, ray angle) pairs at j and j + 1
@@ -473,13 +475,16 @@ struct WarmArgs {
   float2* pred;                 // [jobs][n_solve] (theta_R - psi, theta_I)
   int32_t* fb_list;             // jobs for the plain path
   int32_t* fb_len;
-  int32_t* win_list;            // jobs with directions near a fold (k_warm_window)
-  int32_t* win_len;
-  int4* dirs;                   // fold directions: (job, sidx, first bracket, brackets)
-  int32_t* dir_len;
+  int32_t* win;                 // [jobs] 1: directions near a fold, for k_warm_window
+  // Fold directions and their brackets, in `parts` lists of dir_cap and br_cap
+  // entries each (a workgroup appends to list blockIdx mod parts: returning
+  // atomics on one address serialise across the chip); len[part]: entries,
+  // directions << 32 | brackets, a 128-byte line each.
+  int parts;
+  unsigned long long* len;
+  int4* dirs;                   // (job, sidx, first bracket, brackets)
   int64_t dir_cap;
-  WinBracket* brs;              // their brackets, in scan order per direction
-  int32_t* br_len;
+  WinBracket* brs;              // in scan order per direction
   int64_t br_cap;
   unsigned long long* stats;    // CHERT_WARM_NSTATS counters (folded from shard)
   unsigned long long* shard;    // [kStatSlots][16] per-slot partial counters
@@ -519,9 +524,11 @@ __device__ __forceinline__ int fold_bin(double psi) {
 }
 
 // sweep samples whose theta_R the elastic map sends within kFoldMargin of
-// psi_star (either half of the circle), plus one sample on each side
-__device__ __forceinline__ void mark_window(const SolveArgs& a, const double* psi, double psi_star,
-                                            uint32_t* mask) {
+// psi_star (either half of the circle), plus one sample on each side; samples
+// of the second half count as the first-half ones they are images of (h stored
+// samples, h = n_sweep where there are no images)
+__device__ __forceinline__ void mark_window(const SolveArgs& a, int h, const double* psi,
+                                            double psi_star, uint32_t* mask) {
   const double dth = kTwoPi / a.n_sweep;
   for (int j = threadIdx.x; j < kProxyN; j += blockDim.x) {
     const double pa = psi[j];
@@ -530,15 +537,15 @@ __device__ __forceinline__ void mark_window(const SolveArgs& a, const double* ps
     const double lo = fmin(pa, pa + dp) - kFoldMargin;
     const double width = fabs(dp) + 2.0 * kFoldMargin;
     for (int half = 0; half < 2; ++half) {
-      double off = fmod(psi_star - half * kPi - lo, kTwoPi);
-      if (off < 0.0) off += kTwoPi;
-      if (off > width) continue;
+      const double off = psi_star - half * kPi - lo;
+      if (off - kTwoPi * floor(off * (1.0 / kTwoPi)) > width) continue;
       const double ta = (j + 0.5) * (kPi / kProxyN) + half * kPi;
       const double tb = ta + kPi / kProxyN;
       const int i0 = (int)floor(ta / dth - 0.5) - 1;
       const int i1 = (int)ceil(tb / dth - 0.5) + 1;
       for (int i = i0; i <= i1; ++i) {
-        const int q = ((i % a.n_sweep) + a.n_sweep) % a.n_sweep;
+        int q = i < 0 ? i + a.n_sweep : (i >= a.n_sweep ? i - a.n_sweep : i);
+        if (q >= h) q -= h;
         atomicOr(&mask[q >> 5], 1u << (q & 31));
       }
     }
@@ -596,7 +603,7 @@ __device__ __forceinline__ Medium elastic_of(const Medium& m) {
 // left 24 lanes idle): every direction away from a fold is polished from
 // its prediction.  A job with a rejected direction goes to the plain path
 // (fb_list); a job whose other directions all passed and that has
-// directions near a fold goes to k_warm_window (win_list).  Small static
+// directions near a fold is flagged for k_warm_window.  Small static
 // LDS only, so occupancy is set by registers.
 constexpr int kWarmSolveThreads = 256;
 constexpr int kWarmSolveJobs = 16;  // most jobs a workgroup holds
@@ -700,13 +707,12 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
   }
   if (reject) s_rej[qs] = 1;
   __syncthreads();
-  if (work && l == 0) {
+  if (on && l == 0) {
     if (s_rej[qs]) {
       atomicAdd(&s_cnt[1], 1u);
       w.fb_list[atomicAdd(w.fb_len, 1)] = (int32_t)job;
-    } else if (s_nflag[qs] > 0) {
-      w.win_list[atomicAdd(w.win_len, 1)] = (int32_t)job;
     }
+    w.win[job] = !s_rej[qs] && s_nflag[qs] > 0;
   }
   __syncthreads();
   for (int i = threadIdx.x; i < CHERT_WARM_NSTATS; i += blockDim.x)
@@ -719,90 +725,89 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
 // read as NaN and so never bracket; the search is the plain one wherever the
 // viscoelastic map stays within kFoldMargin of the elastic one, which is
 // checked on every evaluated sample (half the margin; otherwise, or beyond
-// kWinCap samples, the job goes to the plain path).  One wavefront per
-// listed job, grid-strided; the marked samples are kept compact in LDS.
+// kWinCap samples, the job goes to the plain path).  One wavefront per job
+// (unflagged jobs leave at once); the marked samples are kept compact in LDS,
+// the second half of the sweep as the image of the first.  A job reserves its
+// room in the lists of directions and brackets with one returning atomic (two
+// per direction on one counter for the whole chip took most of the kernel:
+// 80,601 nodes, 1.68 -> 0.73 ms).
 constexpr int kWinCap = 512;
 // room for fold directions and their brackets, per job on average (more: the
 // job is redone by the plain path)
 constexpr int64_t kDirsPerJob = 4, kBracketsPerJob = 8;
-__global__ void __launch_bounds__(64) k_warm_window(WarmArgs w) {
+__global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) {
   extern __shared__ double2 s_ent[];  // [kWinCap] (theta_I, psi); then idx, pos
   int16_t* s_idx = reinterpret_cast<int16_t*>(s_ent + kWinCap);  // [kWinCap]
   __shared__ double s_psi[kProxyN];
   __shared__ uint32_t s_fold[kFoldWords];
   __shared__ uint32_t s_mask[kMaxSweep / 32];
   __shared__ int16_t s_flag[kMaxSubset / 2];
+  __shared__ uint16_t s_nbr[kMaxSubset / 2];
   __shared__ int s_all, s_nflag, s_bad;
 
   const SolveArgs& a = w.so;
   const int lane = threadIdx.x;
-  int16_t* s_pos = s_idx + kWinCap;  // [n_sweep]
-  const int n_words = (a.n_sweep + 31) / 32;
-  const int n_list = *w.win_len;
-  unsigned long long samples = 0, guard = 0;
-  for (int q = blockIdx.x; q < n_list; q += gridDim.x) {
-    const int64_t job = w.win_list[q];
-    const int64_t k = job % a.n_classes;
-    const int mode = a.modes[job / a.n_classes];
-    const chert_class c = a.classes[k];
-    const Medium m = load_medium(c);
-    const Medium me = elastic_of(m);
-    __syncthreads();  // the previous job is done with the shared arrays
-    if (lane < kFoldWords) s_fold[lane] = 0;
-    if (lane == 0) {
-      s_all = 0;
-      s_nflag = 0;
-      s_bad = 0;
+  const int64_t job = blockIdx.x;
+  if (job >= n_jobs || !w.win[job]) return;  // wavefront-uniform
+  const int h = sweep_stored(a.n_sweep);
+  int16_t* s_pos = s_idx + kWinCap;  // [h]
+  const int n_words = (h + 31) / 32;
+  const int64_t k = job % a.n_classes;
+  const int mode = a.modes[job / a.n_classes];
+  const chert_class c = a.classes[k];
+  const Medium m = load_medium(c);
+  const Medium me = elastic_of(m);
+  if (lane < kFoldWords) s_fold[lane] = 0;
+  if (lane == 0) {
+    s_all = 0;
+    s_nflag = 0;
+    s_bad = 0;
+  }
+  for (int i = lane; i < h; i += 64) s_pos[i] = -1;
+  for (int i = lane; i < n_words; i += 64) s_mask[i] = 0u;
+  __syncthreads();
+  proxy_folds(me, mode, a.kernel, true, lane, 64, s_psi, s_fold, &s_all);
+  for (int sidx = lane; sidx < a.n_solve; sidx += 64) {
+    int d, col, pcol;
+    dir_cols(a, sidx, &d, &col, &pcol);
+    const int fb = fold_bin(dir_psi(a, d, m.tilt));
+    if ((s_fold[fb >> 5] >> (fb & 31)) & 1u) s_flag[atomicAdd(&s_nflag, 1)] = (int16_t)sidx;
+  }
+  __syncthreads();
+  const int nflag = s_nflag;
+  auto target = [&](int f) {
+    int d, col, pcol;
+    dir_cols(a, s_flag[f], &d, &col, &pcol);
+    return dir_psi(a, d, m.tilt);
+  };
+  for (int f = 0; f < nflag; ++f) mark_window(a, h, s_psi, target(f), s_mask);
+  __syncthreads();
+  // marked samples in ascending order: one mask word per lane, prefix sum
+  // of the word populations across the wavefront
+  int nl = 0;
+  for (int base = 0; base < n_words; base += 64) {
+    const int wd = base + lane;
+    uint32_t bits = wd < n_words ? s_mask[wd] : 0u;
+    const int cnt = __popc(bits);
+    int incl = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
     }
-    for (int i = lane; i < a.n_sweep; i += 64) s_pos[i] = -1;
-    for (int i = lane; i < n_words; i += 64) s_mask[i] = 0u;
-    __syncthreads();
-    proxy_folds(me, mode, a.kernel, true, lane, 64, s_psi, s_fold, &s_all);
-    for (int sidx = lane; sidx < a.n_solve; sidx += 64) {
-      int d, col, pcol;
-      dir_cols(a, sidx, &d, &col, &pcol);
-      const int fb = fold_bin(dir_psi(a, d, m.tilt));
-      if ((s_fold[fb >> 5] >> (fb & 31)) & 1u) s_flag[atomicAdd(&s_nflag, 1)] = (int16_t)sidx;
-    }
-    __syncthreads();
-    const int nflag = s_nflag;
-    for (int f = 0; f < nflag; ++f) {
-      int d, col, pcol;
-      dir_cols(a, s_flag[f], &d, &col, &pcol);
-      mark_window(a, s_psi, dir_psi(a, d, m.tilt), s_mask);
-    }
-    __syncthreads();
-    // marked samples in ascending order: one mask word per lane, prefix sum
-    // of the word populations across the wavefront
-    int nl = 0;
-    for (int base = 0; base < n_words; base += 64) {
-      const int wd = base + lane;
-      uint32_t bits = wd < n_words ? s_mask[wd] : 0u;
-      const int cnt = __popc(bits);
-      int incl = cnt;
-      for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off);
-        if (lane >= off) incl += v;
+    int slot = nl + incl - cnt;
+    while (bits) {
+      const int b = __builtin_ctz(bits);
+      bits &= bits - 1u;
+      if (slot < kWinCap) {
+        s_idx[slot] = (int16_t)(wd * 32 + b);
+        s_pos[wd * 32 + b] = (int16_t)slot;
       }
-      int slot = nl + incl - cnt;
-      while (bits) {
-        const int b = __builtin_ctz(bits);
-        bits &= bits - 1u;
-        if (slot < kWinCap) {
-          s_idx[slot] = (int16_t)(wd * 32 + b);
-          s_pos[wd * 32 + b] = (int16_t)slot;
-        }
-        ++slot;
-      }
-      nl += __shfl(incl, 63);
+      ++slot;
     }
-    if (nl > kWinCap) {  // wavefront-uniform
-      if (lane == 0) {
-        ++guard;
-        w.fb_list[atomicAdd(w.fb_len, 1)] = (int32_t)job;
-      }
-      continue;
-    }
+    nl += __shfl(incl, 63);
+  }
+  bool bad = nl > kWinCap;  // wavefront-uniform
+  if (!bad) {
     __syncthreads();
     for (int t = lane; t < nl; t += 64) {
       const int i = s_idx[t];
@@ -813,89 +818,102 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w) {
       if (theta_imag_sc(m, mode, a.kernel, sr, cr, &thI)) {
         const double psi = ray_angle_sc(m, mode, a.kernel, sr, cr, thI);
         if (isfinite(psi)) out = make_double2(thI, psi);
-        const double pe = ray_angle(energy_velocity_t(me, mode, a.kernel, Trig{sr, cr, 0.0, 1.0}));
+        const double pe = ray_angle_sc(me, mode, a.kernel, sr, cr, 0.0);
         if (!(fabs(wrap_pi(psi - pe)) <= 0.5 * kFoldMargin)) s_bad = 1;
       }
       s_ent[t] = out;
     }
-    samples += (unsigned long long)nl;
     __syncthreads();
-    if (!s_bad) {
-      // every bracket of every fold direction goes to the flat refinement
-      // (k_warm_fold): one record per direction, its brackets contiguous in
-      // scan order.  All lanes scan the table for one direction at a time.
-      const WindowTable tab{s_pos, s_ent};
-      const auto holds = [&](int j, double psi) {
-        return is_bracket(tab.at(j), tab.at(j + 1 == a.n_sweep ? 0 : j + 1), psi);
-      };
-      for (int f = 0; f < nflag; ++f) {
-        int d, col, pcol;
-        const int sidx = s_flag[f];
-        dir_cols(a, sidx, &d, &col, &pcol);
-        const double psi_star = dir_psi(a, d, m.tilt);
-        int nbr = 0;
-        for (int base = 0; base < nl; base += 64)
-          nbr += __popcll(__ballot(base + lane < nl &&
-                                   holds(s_idx[base + lane], psi_star)));
-        int rec = 0, first = 0;
-        if (lane == 0) {
-          rec = atomicAdd(w.dir_len, 1);
-          first = atomicAdd(w.br_len, nbr);
-        }
-        rec = __shfl(rec, 0);
-        first = __shfl(first, 0);
-        if (rec >= w.dir_cap || (int64_t)first + nbr > w.br_cap) {
-          if (lane == 0 && rec < w.dir_cap) w.dirs[rec] = make_int4(-1, 0, 0, 0);
-          s_bad = 1;  // no room: the job is redone below
-          break;      // wavefront-uniform
-        }
-        int q = first;
+    bad = s_bad != 0;
+  }
+  if (!bad) {
+    // every bracket of every fold direction goes to the flat refinement
+    // (k_warm_fold): one record per direction, its brackets contiguous in
+    // scan order.  All lanes scan the table for one direction at a time.
+    const WindowTable tab{s_pos, s_ent, h};
+    const int spans = h < a.n_sweep ? 2 : 1;
+    const auto next = [&](int j) { return j + 1 == a.n_sweep ? 0 : j + 1; };
+    int total = 0;
+    for (int f = 0; f < nflag; ++f) {
+      const double psi_star = target(f);
+      int nbr = 0;
+      for (int sp = 0; sp < spans; ++sp)
         for (int base = 0; base < nl; base += 64) {
-          const bool br = base + lane < nl &&
-                          holds(s_idx[base + lane], psi_star);
-          const unsigned long long mask = __ballot(br);
-          if (br) {
-            const int jj = s_idx[base + lane];
+          const int jj = base + lane < nl ? s_idx[base + lane] + sp * h : 0;
+          nbr += __popcll(__ballot(base + lane < nl &&
+                                   is_bracket(tab.at(jj), tab.at(next(jj)), psi_star)));
+        }
+      if (lane == 0) s_nbr[f] = (uint16_t)nbr;
+      total += nbr;
+    }
+    const int part = (int)(job % w.parts);
+    unsigned long long at = 0;
+    if (lane == 0)
+      at = atomicAdd(&w.len[part * kLenStride],
+                     ((unsigned long long)nflag << 32) + (unsigned long long)total);
+    int rec = __shfl((int)(at >> 32), 0), first = __shfl((int)(at & 0xffffffffull), 0);
+    int4* dirs = w.dirs + (int64_t)part * w.dir_cap;
+    WinBracket* brs = w.brs + (int64_t)part * w.br_cap;
+    if ((int64_t)rec + nflag > w.dir_cap || (int64_t)first + total > w.br_cap) {
+      // no room: the reserved records hold nothing, the job is redone below
+      for (int f = lane; f < nflag; f += 64)
+        if (rec + f < w.dir_cap) dirs[rec + f] = make_int4(-1, 0, 0, 0);
+      bad = true;
+    } else {
+      __syncthreads();  // s_nbr
+      for (int f = 0; f < nflag; ++f) {
+        const double psi_star = target(f);
+        int q = first;
+        for (int sp = 0; sp < spans; ++sp)
+          for (int base = 0; base < nl; base += 64) {
+            const int jj = base + lane < nl ? s_idx[base + lane] + sp * h : 0;
             WinBracket b;
             b.sa = tab.at(jj);
-            b.sb = tab.at(jj + 1 == a.n_sweep ? 0 : jj + 1);
+            b.sb = tab.at(next(jj));
             b.j = jj;
-            w.brs[q + __popcll(mask & ((1ull << lane) - 1ull))] = b;
+            const bool br = base + lane < nl && is_bracket(b.sa, b.sb, psi_star);
+            const unsigned long long mask = __ballot(br);
+            if (br) brs[q + __popcll(mask & ((1ull << lane) - 1ull))] = b;
+            q += __popcll(mask);
           }
-          q += __popcll(mask);
-        }
-        if (lane == 0) w.dirs[rec] = make_int4((int)job, sidx, first, nbr);
+        if (lane == 0) dirs[rec + f] = make_int4((int)job, s_flag[f], first, s_nbr[f]);
+        first = q;
       }
-      __syncthreads();
     }
-    if (s_bad && lane == 0) {  // guard failed or no room: the plain path redoes the job
-      ++guard;
-      w.fb_list[atomicAdd(w.fb_len, 1)] = (int32_t)job;
-    }
+    if (lane == 0) atomicAdd(&stat_slot(w.shard)[8], (unsigned long long)nl);
   }
-  if (lane == 0 && samples) atomicAdd(&stat_slot(w.shard)[8], samples);
-  if (lane == 0 && guard) {
-    atomicAdd(&stat_slot(w.shard)[9], guard);
-    atomicAdd(&stat_slot(w.shard)[1], guard);
+  if (bad && lane == 0) {  // guard failed or no room: the plain path redoes the job
+    w.fb_list[atomicAdd(w.fb_len, 1)] = (int32_t)job;
+    atomicAdd(&stat_slot(w.shard)[9], 1ull);
+    atomicAdd(&stat_slot(w.shard)[1], 1ull);
   }
 }
 
-// Fold directions across all window jobs, one lane each: refine the
-// direction's brackets in scan order and keep the plain search's choice
-// (the fold of refine_bracket), then store the entry and its copy.
+// Fold directions across all window jobs (list blockIdx.y), four lanes each:
+// a direction's brackets are refined side by side and its first lane folds
+// the roots in scan order, the plain search's choice, then stores the entry
+// and its copy.  (The kernel lasts as long as its slowest bracket, one whose
+// Newton step fails and is bisected.)
+constexpr int kFoldLanes = 4, kFoldDirs = 64 / kFoldLanes;
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_warm_fold(WarmArgs w) {
+  __shared__ SolveCand s_c[kFoldDirs][kFoldLanes * kSolveSlots];
   const SolveArgs& a = w.so;
-  const int64_t n = *w.dir_len < w.dir_cap ? *w.dir_len : w.dir_cap;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int4 r = w.dirs[t];
-    if (r.x < 0) continue;
-    const int64_t job = r.x;
+  const int part = blockIdx.y;
+  const int64_t len = (int64_t)(w.len[part * kLenStride] >> 32);
+  const int64_t n = len < w.dir_cap ? len : w.dir_cap;
+  const int4* dirs = w.dirs + (int64_t)part * w.dir_cap;
+  const WinBracket* brs = w.brs + (int64_t)part * w.br_cap;
+  const int dl = threadIdx.x / kFoldLanes, q = threadIdx.x % kFoldLanes;
+  constexpr int kBatch = kFoldLanes * kSolveSlots;
+  for (int64_t t0 = (int64_t)blockIdx.x * kFoldDirs; t0 < n; t0 += (int64_t)gridDim.x * kFoldDirs) {
+    const int64_t t = t0 + dl;
+    const int4 r = t < n ? dirs[t] : make_int4(-1, 0, 0, 0);
+    const bool valid = r.x >= 0;
+    const int64_t job = valid ? r.x : 0;
     const int64_t k = job % a.n_classes;
     const int mode = a.modes[job / a.n_classes];
     const chert_class c = a.classes[k];
-    const int64_t row = ((int64_t)mode * a.n_classes + k) * a.n_cols;
     const Medium m = load_medium(c);
     const bool el = theta_i_zero(m, mode);
     int d, col, pcol;
@@ -903,11 +921,27 @@ k_warm_fold(WarmArgs w) {
     const double psi_star = dir_psi(a, d, m.tilt);
     bool found = false, ill = false;
     Entry best{};
-    for (int b = 0; b < r.w; ++b) {
-      const WinBracket br = w.brs[r.z + b];
-      refine_bracket_at(a, m, mode, br.j, br.sa, br.sb, psi_star, el, &found, &ill, &best);
+    for (int b0 = 0; __any(valid && b0 < r.w); b0 += kBatch) {
+      for (int i = 0; i < kSolveSlots; ++i) {
+        const int b = b0 + i * kFoldLanes + q;
+        if (!valid || b >= r.w) continue;
+        const WinBracket br = brs[r.z + b];
+        SolveCand& sc = s_c[dl][i * kFoldLanes + q];
+        bool cill = false;
+        sc.ok = bracket_root(a, m, mode, br.j, br.sa, br.sb, psi_star, el, &sc.e, &cill) ? 1 : 0;
+        sc.ill = cill ? 1 : 0;
+      }
+      __syncthreads();
+      if (valid && q == 0)
+        for (int i = 0; i < kBatch && b0 + i < r.w; ++i) {
+          const SolveCand& sc = s_c[dl][i];
+          if (sc.ok) fold_choice(sc.e, sc.ill != 0, psi_star, a.resid_tol, &found, &ill, &best);
+        }
+      __syncthreads();
     }
-    store_pair(a, row, col, pcol, best, m.tilt, solve_status(found, ill, best));
+    if (valid && q == 0)
+      store_pair(a, ((int64_t)mode * a.n_classes + k) * a.n_cols, col, pcol, best, m.tilt,
+                 solve_status(found, ill, best));
   }
 }
 
@@ -1095,7 +1129,8 @@ __global__ void __launch_bounds__(64) k_warm3_solve(Warm3Args w, int64_t n_rows)
 
 // the plain sweep-and-bracket search for the listed directions, one lane
 // each, from the job's sweep table (read through the caches); grid-strided
-__global__ void __launch_bounds__(64) k_warm3_plain(Warm3Args w) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_warm3_plain(Warm3Args w) {
   __shared__ int s_br[64 * kMaxBr];
   const SolveArgs& a = w.so;
   const int n = *w.fb_len, h = sweep_stored(a.n_sweep);
@@ -1118,11 +1153,10 @@ __global__ void __launch_bounds__(64) k_warm3_plain(Warm3Args w) {
   }
 }
 
-__global__ void k_warm_zero(int32_t* fb_len, int32_t* win_len, unsigned long long* shard) {
+__global__ void k_warm_zero(int32_t* fb_len, unsigned long long* len, int parts,
+                            unsigned long long* shard) {
   if (threadIdx.x == 0) *fb_len = 0;
-  if (threadIdx.x == 1) *win_len = 0;
-  if (threadIdx.x == 2) win_len[1] = 0;  // fold directions
-  if (threadIdx.x == 3) win_len[2] = 0;  // their brackets
+  for (int i = threadIdx.x; i < parts; i += blockDim.x) len[i * kLenStride] = 0ull;
   for (int i = threadIdx.x; i < kStatSlots * kStatSlotU64; i += blockDim.x) shard[i] = 0ull;
 }
 
@@ -1484,8 +1518,9 @@ extern "C" size_t chert_build_cache_surrogate_workspace_bytes(const chert_cache_
   const SolveArgs so = solve_args(d, nullptr, n_classes, nullptr, lay, nullptr);
   const size_t jobs = (size_t)n_jobs_of(d, n_classes);
   return al256(jobs * so.n_solve * sizeof(float2)) + 2 * al256(jobs * sizeof(int32_t)) + 256 +
-         al256(jobs * kDirsPerJob * sizeof(int4)) + al256(jobs * kBracketsPerJob * sizeof(WinBracket)) +
-         al256(kStatBytes);
+         kWarmParts * kLenStride * sizeof(unsigned long long) +
+         al256((jobs + kWarmParts) * kDirsPerJob * sizeof(int4)) +
+         al256((jobs + kWarmParts) * kBracketsPerJob * sizeof(WinBracket)) + al256(kStatBytes);
 }
 
 extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
@@ -1530,8 +1565,8 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
     CHERT_LAUNCH("k_write_header", k_write_header, dim3(1), dim3(64), 0, s, cache, d->dim,
                  d->n_dirs, d->mode_mask, d->kernel, d->n_sweep, d->n_subset, n_classes,
                  d->sampling);
-    CHERT_LAUNCH("k_warm_zero", k_warm_zero, dim3(1), dim3(256), 0, s, w.fb_len, w.fb_len + 1,
-                 w.shard);
+    CHERT_LAUNCH("k_warm_zero", k_warm_zero, dim3(1), dim3(256), 0, s, w.fb_len,
+                 (unsigned long long*)nullptr, 0, w.shard);
     if (rows > 0) {
       SweepArgs sa{};
       sa.classes = classes_dev;
@@ -1568,17 +1603,18 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
   w.blob = blob_dev;
   w.pred = (float2*)ws;
   w.fb_list = (int32_t*)(ws + al256(rows * sizeof(float2)));
-  w.win_list = (int32_t*)(ws + al256(rows * sizeof(float2)) + al256(jobs * sizeof(int32_t)));
+  w.win = (int32_t*)(ws + al256(rows * sizeof(float2)) + al256(jobs * sizeof(int32_t)));
   w.fb_len = (int32_t*)(ws + al256(rows * sizeof(float2)) + 2 * al256(jobs * sizeof(int32_t)));
-  w.win_len = w.fb_len + 1;
-  w.dir_len = w.fb_len + 2;
-  w.br_len = w.fb_len + 3;
   {
-    uint8_t* tail = ws + al256(rows * sizeof(float2)) + 2 * al256(jobs * sizeof(int32_t)) + 256;
-    w.dir_cap = jobs * kDirsPerJob;
+    uint8_t* tail = (uint8_t*)w.fb_len + 256;
+    w.len = (unsigned long long*)tail;
+    tail += kWarmParts * kLenStride * sizeof(unsigned long long);
+    // one list for small builds, so that an uneven share does not run out
+    w.parts = (int)(jobs / 1024 < 1 ? 1 : (jobs / 1024 > kWarmParts ? kWarmParts : jobs / 1024));
+    w.dir_cap = (jobs + w.parts - 1) / w.parts * kDirsPerJob;
     w.dirs = (int4*)tail;
-    w.br_cap = jobs * kBracketsPerJob;
-    w.brs = (WinBracket*)(tail + al256(jobs * kDirsPerJob * sizeof(int4)));
+    w.br_cap = (jobs + w.parts - 1) / w.parts * kBracketsPerJob;
+    w.brs = (WinBracket*)(tail + al256((jobs + kWarmParts) * kDirsPerJob * sizeof(int4)));
   }
   w.stats = stats_dev ? (unsigned long long*)stats_dev : (unsigned long long*)(w.fb_len + 16);
   w.shard = (unsigned long long*)(ws + chert_build_cache_surrogate_workspace_bytes(d, n_classes) -
@@ -1588,7 +1624,7 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
   CHERT_LAUNCH("k_write_header", k_write_header, dim3(1), dim3(64), 0, s, cache, d->dim,
                d->n_dirs, d->mode_mask, d->kernel, d->n_sweep, d->n_subset, n_classes,
                  d->sampling);
-  CHERT_LAUNCH("k_warm_zero", k_warm_zero, dim3(1), dim3(256), 0, s, w.fb_len, w.win_len,
+  CHERT_LAUNCH("k_warm_zero", k_warm_zero, dim3(1), dim3(256), 0, s, w.fb_len, w.len, w.parts,
                w.shard);
   if (jobs > 0 && rows > 0) {
     const int64_t blocks = (rows + mlp::kInferRows - 1) / mlp::kInferRows;
@@ -1599,11 +1635,13 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
     CHERT_LAUNCH("k_warm_solve", k_warm_solve, dim3((unsigned)((jobs + per - 1) / per)),
                  dim3(kWarmSolveThreads), 0, s, w, jobs);
     const int64_t grid = jobs < 4096 ? jobs : 4096;
-    CHERT_LAUNCH("k_warm_window", k_warm_window, dim3((unsigned)grid), dim3(64),
+    CHERT_LAUNCH("k_warm_window", k_warm_window, dim3((unsigned)jobs), dim3(64),
                  kWinCap * (sizeof(double2) + sizeof(int16_t)) +
-                     (size_t)d->n_sweep * sizeof(int16_t), s, w);
-    const int64_t fgrid = (w.dir_cap + 63) / 64 < 8192 ? (w.dir_cap + 63) / 64 : 8192;
-    CHERT_LAUNCH("k_warm_fold", k_warm_fold, dim3((unsigned)fgrid), dim3(64), 0, s, w);
+                     (size_t)sweep_stored(d->n_sweep) * sizeof(int16_t), s, w, jobs);
+    const int64_t fneed = (w.dir_cap + kFoldDirs - 1) / kFoldDirs, fmost = 16384 / w.parts;
+    CHERT_LAUNCH("k_warm_fold", k_warm_fold,
+                 dim3((unsigned)(fneed < fmost ? fneed : fmost), (unsigned)w.parts), dim3(64), 0, s,
+                 w);
     CHERT_LAUNCH("k_build_fused", k_build_fused, dim3((unsigned)grid), dim3(kNodeThreads),
                  (size_t)d->n_sweep * sizeof(double2), s, w.so, (const int32_t*)w.fb_list,
                  (const int32_t*)w.fb_len, jobs);

@@ -248,15 +248,18 @@ __device__ __forceinline__ double2 sweep_sample(const Medium& m, int mode, int k
   return make_double2(0.0, NAN);
 }
 
-// A windowed table holds the marked samples in ascending order (slot q is
-// sample idx[q], pos[j] is the slot of sample j or -1) and reads every other
-// sample as NaN.
+// A windowed table holds the marked ones of the h stored samples in ascending
+// order (pos[j] is the slot of sample j or -1) and reads every other sample as
+// NaN; the second half of the sweep is the image of the first, as above.
 struct WindowTable {
   const int16_t* pos;
   const double2* ent;
+  int h;
   __device__ __forceinline__ double2 at(int j) const {
-    const int p = pos[j];
-    return p < 0 ? make_double2(0.0, NAN) : ent[p];
+    const int p = pos[j < h ? j : j - h];
+    if (p < 0) return make_double2(0.0, NAN);
+    const double2 v = ent[p];
+    return j < h ? v : make_double2(v.x, wrap_pi(v.y + kPi));
   }
 };
 
