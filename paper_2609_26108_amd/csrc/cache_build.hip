@@ -326,10 +326,16 @@ k_solve(SolveArgs a) {
   store_pair(a, row, col, pcol, best, blocked ? 0.0 : m.tilt, st);
 }
 
-// Fused path (many classes, e.g. one per node): one workgroup per
-// (mode, class) sweeps theta_R into LDS, then solves that class's
-// directions; no sweep table in HBM.
-constexpr int kNodeThreads = 256;
+// Fused path (many classes, e.g. one per node): one wavefront per
+// (mode, class) sweeps half of theta_R into LDS, then solves that class's
+// directions; no sweep table in HBM.  One wavefront: a job has some 40
+// directions, so of 256 threads 216 were idle in the solves (10,201 nodes x 2
+// modes: 7.7 ms with 256 and all samples, 6.2 with 128 and half of them, 5.2
+// with 64).  Its directions test every interval, without k_solve's chunk
+// ranges (1.2 ms there): the surrogate-started build is held by its tests to a
+// quarter of this one's time (9,600 nodes: 0.46 ms against 2.6, 0.65 with the
+// ranges), and both are wanted.
+constexpr int kNodeThreads = 64;
 __global__ void __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)))
 k_build_fused(SolveArgs a, const int32_t* list,
                                                               const int32_t* list_len,
@@ -356,10 +362,11 @@ k_build_fused(SolveArgs a, const int32_t* list,
     }
     const Medium m = load_medium(c);
     __syncthreads();  // the previous job's solves are done with the table
-    for (int j = threadIdx.x; j < a.n_sweep; j += blockDim.x)
+    const int h = sweep_stored(a.n_sweep);
+    for (int j = threadIdx.x; j < h; j += blockDim.x)
       tab_lds[j] = sweep_sample(m, mode, a.kernel, a.n_sweep, j);
     __syncthreads();
-    const SweepTable tab{tab_lds, nullptr, a.n_sweep, a.n_sweep};
+    const SweepTable tab{tab_lds, nullptr, a.n_sweep, h};
     for (int sidx = threadIdx.x; sidx < a.n_solve; sidx += blockDim.x) {
       int d, col, pcol;
       dir_cols(a, sidx, &d, &col, &pcol);
@@ -476,6 +483,7 @@ struct WarmArgs {
   int32_t* fb_list;             // jobs for the plain path
   int32_t* fb_len;
   int32_t* win;                 // [jobs] 1: directions near a fold, for k_warm_window
+  uint32_t* fold;               // [jobs][kFoldWords] fold bins (until k_warm_window: in brs)
   // Fold directions and their brackets, in `parts` lists of dir_cap and br_cap
   // entries each (a workgroup appends to list blockIdx mod parts: returning
   // atomics on one address serialise across the chip); len[part]: entries,
@@ -491,29 +499,47 @@ struct WarmArgs {
   double resid_tol;
 };
 
-// surrogate predictions for every (job, solved direction): kInferRows per
-// workgroup
-__global__ void __launch_bounds__(mlp::kThreads) k_warm_predict(WarmArgs w, int64_t n_rows) {
+// Predictions of one workgroup: kInferRows (job, solved direction) rows.
+// Wavefront w stages inputs 4 w .. 4 w + 3 of the rows, a row per lane: one
+// wavefront staging all sixteen (six FP64 divisions and two sincos a row) kept
+// the other three waiting.  target(s, class): target ray angle of direction s.
+// Row -> (job, direction) from one 64-bit division per workgroup.
+template <class Target>
+__device__ __forceinline__ void predict_rows(const SolveArgs& a, const void* blob, float2* pred,
+                                             int64_t n_rows, Target target) {
+  static_assert(mlp::kInferRows == 64 && mlp::kThreads == 256, "a row per lane, a part per wave");
   __shared__ mlp::InferTile t;
-  const SolveArgs& a = w.so;
-  const mlp::Net n = mlp::net_of(w.blob);
+  const mlp::Net n = mlp::net_of(blob);
   const int64_t base = (int64_t)blockIdx.x * mlp::kInferRows;
-  for (int r = threadIdx.x; r < mlp::kInferRows; r += blockDim.x) {
-    const int64_t e = base + r;
-    float f[mlp::kIn] = {};
-    if (e < n_rows) {
-      const int64_t job = e / a.n_solve;
-      const int sidx = (int)(e % a.n_solve);
-      const chert_class c = a.classes[job % a.n_classes];
-      int d, col, pcol;
-      dir_cols(a, sidx, &d, &col, &pcol);
-      mlp::features(c, a.modes[job / a.n_classes], dir_psi(a, d, c.tilt), f);
+  const int r = threadIdx.x & 63;
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t job0 = base / a.n_solve;
+  const uint32_t off = (uint32_t)(base - job0 * a.n_solve) + r;
+  const bool pad = base + r >= n_rows;
+  float f[4] = {};
+  if (!pad) {
+    int64_t k = job0 + off / (uint32_t)a.n_solve;
+    int mi = 0;
+    while (k >= a.n_classes) {
+      k -= a.n_classes;
+      ++mi;
     }
-    mlp::stage_row(n, t.x, r, f, e >= n_rows);
+    const chert_class c = a.classes[k];
+    mlp::feature_part(c, a.modes[mi], part == 3 ? target((int)(off % (uint32_t)a.n_solve), c) : 0.0,
+                      part, f);
   }
+  mlp::stage_part(n, t.x, r, part, f, pad);
   __syncthreads();
-  mlp::forward_infer(n, t, [&](int r, int col, float v) {
-    if (col < 2 && base + r < n_rows) (&w.pred[base + r].x)[col] = v;
+  mlp::forward_infer(n, t, [&](int row, int col, float v) {
+    if (col < 2 && base + row < n_rows) (&pred[base + row].x)[col] = v;
+  });
+}
+
+__global__ void __launch_bounds__(mlp::kThreads) k_warm_predict(WarmArgs w, int64_t n_rows) {
+  predict_rows(w.so, w.blob, w.pred, n_rows, [&](int s, const chert_class& c) {
+    int d, col, pcol;
+    dir_cols(w.so, s, &d, &col, &pcol);
+    return dir_psi(w.so, d, c.tilt);
   });
 }
 
@@ -523,22 +549,39 @@ __device__ __forceinline__ int fold_bin(double psi) {
   return b < 0 ? b + kFoldBins : b;
 }
 
-// sweep samples whose theta_R the elastic map sends within kFoldMargin of
-// psi_star (either half of the circle), plus one sample on each side; samples
-// of the second half count as the first-half ones they are images of (h stored
-// samples, h = n_sweep where there are no images)
+__device__ __forceinline__ double lane_value(double v, int lane) {  // uniform lane
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// sweep samples whose theta_R the elastic map sends within kFoldMargin of one
+// of nf targets (lane f holds target f; either half of the circle), plus one
+// sample on each side; samples of the second half count as the first-half
+// ones they are images of (h stored samples, h = n_sweep where there are no
+// images).  An elastic interval's samples do not depend on the target, so they
+// are marked once.
 __device__ __forceinline__ void mark_window(const SolveArgs& a, int h, const double* psi,
-                                            double psi_star, uint32_t* mask) {
+                                            double tgt, int nf, uint32_t* mask) {
   const double dth = kTwoPi / a.n_sweep;
-  for (int j = threadIdx.x; j < kProxyN; j += blockDim.x) {
+  for (int j0 = 0; j0 < kProxyN; j0 += 64) {
+    const int j = j0 + (int)threadIdx.x < kProxyN ? j0 + threadIdx.x : kProxyN - 1;
     const double pa = psi[j];
     const double pb = j + 1 < kProxyN ? psi[j + 1] : psi[0] + kPi;
     const double dp = wrap_pi(pb - pa);
     const double lo = fmin(pa, pa + dp) - kFoldMargin;
     const double width = fabs(dp) + 2.0 * kFoldMargin;
+    bool hit[2] = {false, false};
+    for (int f = 0; f < nf; ++f) {
+      const double psi_star = lane_value(tgt, f);
+      for (int half = 0; half < 2; ++half) {
+        const double off = psi_star - half * kPi - lo;
+        hit[half] |= !(off - kTwoPi * floor(off * (1.0 / kTwoPi)) > width);
+      }
+    }
     for (int half = 0; half < 2; ++half) {
-      const double off = psi_star - half * kPi - lo;
-      if (off - kTwoPi * floor(off * (1.0 / kTwoPi)) > width) continue;
+      if (!hit[half] || j0 + (int)threadIdx.x >= kProxyN) continue;
       const double ta = (j + 0.5) * (kPi / kProxyN) + half * kPi;
       const double tb = ta + kPi / kProxyN;
       const int i0 = (int)floor(ta / dth - 0.5) - 1;
@@ -554,21 +597,23 @@ __device__ __forceinline__ void mark_window(const SolveArgs& a, int h, const dou
 
 // Elastic stand-in of the ray-angle map psi(theta_R) on [0, pi) (the other
 // half is its centrosymmetric image): folds and near-folds within the margin
-// mark ray-angle bins where the map may have several branches.  All 64 lanes;
-// s_fold and *s_all must be cleared (and a barrier passed) before the call;
-// ends with a barrier.
-// `work`: this lane takes part, as lane l of the L serving this job; every
-// thread of the workgroup calls it (it holds two workgroup barriers)
-__device__ __forceinline__ void proxy_folds(const Medium& me, int mode, int kernel, bool work,
-                                            int l, int L, double* s_psi, uint32_t* s_fold,
-                                            int* s_all) {
-  for (int j = l; work && j < kProxyN; j += L) {
-    double sr, cr;  // real angle: sinh 0 = 0, cosh 0 = 1
-    sincos((j + 0.5) * (kPi / kProxyN), &sr, &cr);
-    s_psi[j] = ray_angle(energy_velocity_t(me, mode, kernel, Trig{sr, cr, 0.0, 1.0}));
+// mark ray-angle bins where the map may have several branches.  One wavefront
+// (the workgroup); tr: its lanes' sample angles.  s_fold and *s_all must be
+// cleared (and a barrier passed) before the call; `work` is uniform; ends with
+// a barrier.
+constexpr int kProxyLane = (kProxyN + 63) / 64;  // samples per lane
+__device__ __forceinline__ void proxy_trig(double2* tr) {
+  for (int i = 0; i < kProxyLane; ++i)
+    sincos((threadIdx.x + 64 * i + 0.5) * (kPi / kProxyN), &tr[i].x, &tr[i].y);
+}
+__device__ __forceinline__ void proxy_folds(const Medium& m, int mode, bool work, const double2* tr,
+                                            double* s_psi, uint32_t* s_fold, int* s_all) {
+  for (int i = 0; work && i < kProxyLane; ++i) {
+    const int j = threadIdx.x + 64 * i;
+    if (j < kProxyN) s_psi[j] = ray_angle_elastic(m, mode, tr[i].x, tr[i].y);
   }
   __syncthreads();
-  for (int j = l; work && j < kProxyN; j += L) {
+  for (int j = threadIdx.x; work && j < kProxyN; j += 64) {
     const double pa = s_psi[j];
     const double pb = j + 1 < kProxyN ? s_psi[j + 1] : s_psi[0] + kPi;
     if (!isfinite(pa) || !isfinite(pb)) {
@@ -591,11 +636,36 @@ __device__ __forceinline__ void proxy_folds(const Medium& me, int mode, int kern
   __syncthreads();
 }
 
-__device__ __forceinline__ Medium elastic_of(const Medium& m) {
-  Medium me = m;
-  me.a11.im = me.a13.im = me.a33.im = me.a44.im = me.a66.im = 0.0;
-  me.elastic_ps = me.elastic_sh = true;
-  return me;
+// Fold bins of each job's elastic ray-angle map (all of them, and the spare
+// bits of the last word, if the map is not finite everywhere); a wavefront per
+// job, each wavefront taking several so that the sample angles' sines are
+// computed once.  A kernel of its own: inside k_warm_solve it ran at that
+// kernel's register count.
+static_assert(kFoldBins < 32 * kFoldWords, "the last word's top bit says the map is not finite");
+constexpr int kFoldGrid = 8192;
+__global__ void __launch_bounds__(64) k_warm_folds(SolveArgs a, uint32_t* fold,
+                                                   unsigned long long* shard, int64_t n_jobs) {
+  __shared__ double s_psi[kProxyN];
+  __shared__ uint32_t s_fold[kFoldWords];
+  __shared__ int s_all;
+  double2 tr[kProxyLane];
+  proxy_trig(tr);
+  unsigned done = 0;
+  for (int64_t job = blockIdx.x; job < n_jobs; job += gridDim.x, ++done) {
+    int64_t k = job;
+    int mi = 0;
+    for (; k >= a.n_classes; k -= a.n_classes) ++mi;
+    const chert_class c = a.classes[k];
+    const int mode = a.modes[mi];
+    __syncthreads();  // the previous job's words are read
+    if (threadIdx.x < kFoldWords) s_fold[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) s_all = 0;
+    __syncthreads();
+    proxy_folds(load_medium(c), mode, !class_block(c, mode), tr, s_psi, s_fold, &s_all);
+    if (threadIdx.x < kFoldWords)
+      fold[job * kFoldWords + threadIdx.x] = s_all ? ~0u : s_fold[threadIdx.x];
+  }
+  if (threadIdx.x == 0 && done) atomicAdd(&stat_slot(shard)[0], (unsigned long long)done);
 }
 
 // Several (mode, class) jobs per workgroup, L = min(n_solve, 64) lanes each
@@ -615,9 +685,8 @@ __host__ __device__ inline int warm_jobs(int n_solve) {
 
 __global__ void __launch_bounds__(kWarmSolveThreads) __attribute__((amdgpu_waves_per_eu(2)))
 k_warm_solve(WarmArgs w, int64_t n_jobs) {
-  __shared__ double s_psi[kWarmSolveJobs][kProxyN];
   __shared__ uint32_t s_fold[kWarmSolveJobs][kFoldWords];
-  __shared__ int s_all[kWarmSolveJobs], s_nflag[kWarmSolveJobs], s_rej[kWarmSolveJobs];
+  __shared__ int s_nflag[kWarmSolveJobs], s_rej[kWarmSolveJobs];
   __shared__ uint32_t s_cnt[CHERT_WARM_NSTATS];
 
   const SolveArgs& a = w.so;
@@ -627,10 +696,11 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
   const bool on = q < J && job < n_jobs;  // this lane serves a job
   const int qs = q < J ? q : 0;           // its LDS slot (idle lanes: any)
   for (int i = threadIdx.x; i < CHERT_WARM_NSTATS; i += blockDim.x) s_cnt[i] = 0;
-  for (int i = threadIdx.x; i < kWarmSolveJobs * kFoldWords; i += blockDim.x)
-    (&s_fold[0][0])[i] = 0;
+  const int64_t job0 = (int64_t)blockIdx.x * J;
+  const int n_fold = (int)(n_jobs - job0 < J ? n_jobs - job0 : J) * kFoldWords;
+  for (int i = threadIdx.x; i < n_fold; i += blockDim.x)
+    (&s_fold[0][0])[i] = w.fold[job0 * kFoldWords + i];
   if (threadIdx.x < kWarmSolveJobs) {
-    s_all[threadIdx.x] = 0;
     s_nflag[threadIdx.x] = 0;
     s_rej[threadIdx.x] = 0;
   }
@@ -640,8 +710,7 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
   const int64_t row = ((int64_t)mode * a.n_classes + k) * a.n_cols;
   const int32_t blocked = on ? class_block(c, mode) : 0;
   const bool work = on && !blocked;
-  __syncthreads();  // LDS cleared
-  if (on && l == 0) atomicAdd(&s_cnt[0], 1u);
+  __syncthreads();  // LDS set
   if (on && blocked) {
     Entry none{};
     none.V = NAN;
@@ -653,7 +722,7 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
   }
   const Medium m = load_medium(c);
   const bool el = theta_i_zero(m, mode);
-  proxy_folds(elastic_of(m), mode, a.kernel, work, l, L, s_psi[qs], s_fold[qs], &s_all[qs]);
+  const bool all = s_fold[qs][kFoldWords - 1] >> 31;  // elastic map not finite
 
   bool reject = false;
   for (int sidx = l; work && sidx < a.n_solve; sidx += L) {
@@ -662,7 +731,7 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
     const double psi_star = dir_psi(a, d, m.tilt);
     atomicAdd(&s_cnt[2], 1u);
     const int fb = fold_bin(psi_star);
-    if (s_all[qs]) {
+    if (all) {
       reject = true;
       continue;
     }
@@ -689,7 +758,7 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
       reject = true;
       continue;
     }
-    x = fmod(x, kTwoPi);
+    if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
     if (x < 0.0) x += kTwoPi;
     const Vel v = energy_velocity(m, mode, a.kernel, x, y);
     Entry e;
@@ -735,7 +804,8 @@ constexpr int kWinCap = 512;
 // room for fold directions and their brackets, per job on average (more: the
 // job is redone by the plain path)
 constexpr int64_t kDirsPerJob = 4, kBracketsPerJob = 8;
-__global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+k_warm_window(WarmArgs w, int64_t n_jobs) {
   extern __shared__ double2 s_ent[];  // [kWinCap] (theta_I, psi); then idx, pos
   int16_t* s_idx = reinterpret_cast<int16_t*>(s_ent + kWinCap);  // [kWinCap]
   __shared__ double s_psi[kProxyN];
@@ -756,7 +826,6 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
   const int mode = a.modes[job / a.n_classes];
   const chert_class c = a.classes[k];
   const Medium m = load_medium(c);
-  const Medium me = elastic_of(m);
   if (lane < kFoldWords) s_fold[lane] = 0;
   if (lane == 0) {
     s_all = 0;
@@ -766,7 +835,9 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
   for (int i = lane; i < h; i += 64) s_pos[i] = -1;
   for (int i = lane; i < n_words; i += 64) s_mask[i] = 0u;
   __syncthreads();
-  proxy_folds(me, mode, a.kernel, true, lane, 64, s_psi, s_fold, &s_all);
+  double2 tr[kProxyLane];
+  proxy_trig(tr);
+  proxy_folds(m, mode, true, tr, s_psi, s_fold, &s_all);
   for (int sidx = lane; sidx < a.n_solve; sidx += 64) {
     int d, col, pcol;
     dir_cols(a, sidx, &d, &col, &pcol);
@@ -780,7 +851,9 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
     dir_cols(a, s_flag[f], &d, &col, &pcol);
     return dir_psi(a, d, m.tilt);
   };
-  for (int f = 0; f < nflag; ++f) mark_window(a, h, s_psi, target(f), s_mask);
+  for (int f0 = 0; f0 < nflag; f0 += 64)
+    mark_window(a, h, s_psi, f0 + lane < nflag ? target(f0 + lane) : 0.0,
+                nflag - f0 < 64 ? nflag - f0 : 64, s_mask);
   __syncthreads();
   // marked samples in ascending order: one mask word per lane, prefix sum
   // of the word populations across the wavefront
@@ -818,7 +891,7 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
       if (theta_imag_sc(m, mode, a.kernel, sr, cr, &thI)) {
         const double psi = ray_angle_sc(m, mode, a.kernel, sr, cr, thI);
         if (isfinite(psi)) out = make_double2(thI, psi);
-        const double pe = ray_angle_sc(me, mode, a.kernel, sr, cr, 0.0);
+        const double pe = ray_angle_elastic(m, mode, sr, cr);
         if (!(fabs(wrap_pi(psi - pe)) <= 0.5 * kFoldMargin)) s_bad = 1;
       }
       s_ent[t] = out;
@@ -829,22 +902,35 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
   if (!bad) {
     // every bracket of every fold direction goes to the flat refinement
     // (k_warm_fold): one record per direction, its brackets contiguous in
-    // scan order.  All lanes scan the table for one direction at a time.
+    // scan order.  A lane holds one interval of the table and tests it against
+    // every direction (lane f holds direction f0 + f's target and count).
     const WindowTable tab{s_pos, s_ent, h};
     const int spans = h < a.n_sweep ? 2 : 1;
-    const auto next = [&](int j) { return j + 1 == a.n_sweep ? 0 : j + 1; };
-    int total = 0;
-    for (int f = 0; f < nflag; ++f) {
-      const double psi_star = target(f);
-      int nbr = 0;
+    const auto scan = [&](int f0, auto&& hit) {
+      const double tgt = f0 + lane < nflag ? target(f0 + lane) : 0.0;
+      const int nf = nflag - f0 < 64 ? nflag - f0 : 64;
       for (int sp = 0; sp < spans; ++sp)
         for (int base = 0; base < nl; base += 64) {
-          const int jj = base + lane < nl ? s_idx[base + lane] + sp * h : 0;
-          nbr += __popcll(__ballot(base + lane < nl &&
-                                   is_bracket(tab.at(jj), tab.at(next(jj)), psi_star)));
+          const bool on = base + lane < nl;
+          WinBracket b;
+          b.j = on ? s_idx[base + lane] + sp * h : 0;
+          b.sa = tab.at(b.j);
+          b.sb = tab.at(b.j + 1 == a.n_sweep ? 0 : b.j + 1);
+          for (int f = 0; f < nf; ++f) {
+            const unsigned long long mask =
+                __ballot(on && is_bracket(b.sa, b.sb, lane_value(tgt, f)));
+            if (mask) hit(f, mask, b);
+          }
         }
-      if (lane == 0) s_nbr[f] = (uint16_t)nbr;
-      total += nbr;
+    };
+    int total = 0;
+    for (int f0 = 0; f0 < nflag; f0 += 64) {
+      int nbr = 0;
+      scan(f0, [&](int f, unsigned long long mask, const WinBracket&) {
+        total += __popcll(mask);
+        if (lane == f) nbr += __popcll(mask);
+      });
+      if (f0 + lane < nflag) s_nbr[f0 + lane] = (uint16_t)nbr;
     }
     const int part = (int)(job % w.parts);
     unsigned long long at = 0;
@@ -860,24 +946,21 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
         if (rec + f < w.dir_cap) dirs[rec + f] = make_int4(-1, 0, 0, 0);
       bad = true;
     } else {
-      __syncthreads();  // s_nbr
-      for (int f = 0; f < nflag; ++f) {
-        const double psi_star = target(f);
-        int q = first;
-        for (int sp = 0; sp < spans; ++sp)
-          for (int base = 0; base < nl; base += 64) {
-            const int jj = base + lane < nl ? s_idx[base + lane] + sp * h : 0;
-            WinBracket b;
-            b.sa = tab.at(jj);
-            b.sb = tab.at(next(jj));
-            b.j = jj;
-            const bool br = base + lane < nl && is_bracket(b.sa, b.sb, psi_star);
-            const unsigned long long mask = __ballot(br);
-            if (br) brs[q + __popcll(mask & ((1ull << lane) - 1ull))] = b;
-            q += __popcll(mask);
-          }
-        if (lane == 0) dirs[rec + f] = make_int4((int)job, s_flag[f], first, s_nbr[f]);
-        first = q;
+      for (int f0 = 0; f0 < nflag; f0 += 64) {
+        const int mine = f0 + lane < nflag ? s_nbr[f0 + lane] : 0;
+        int incl = mine;
+        for (int off = 1; off < 64; off <<= 1) {
+          const int v = __shfl_up(incl, off);
+          if (lane >= off) incl += v;
+        }
+        int q = first + incl - mine;  // next slot of direction f0 + lane
+        if (f0 + lane < nflag) dirs[rec + f0 + lane] = make_int4((int)job, s_flag[f0 + lane], q, mine);
+        first += __shfl(incl, 63);
+        scan(f0, [&](int f, unsigned long long mask, const WinBracket& b) {
+          const int to = __builtin_amdgcn_readlane(q, f) + __popcll(mask & ((1ull << lane) - 1ull));
+          if ((mask >> lane) & 1ull) brs[to] = b;
+          if (lane == f) q += __popcll(mask);
+        });
       }
     }
     if (lane == 0) atomicAdd(&stat_slot(w.shard)[8], (unsigned long long)nl);
@@ -887,6 +970,90 @@ __global__ void __launch_bounds__(64) k_warm_window(WarmArgs w, int64_t n_jobs) 
     atomicAdd(&stat_slot(w.shard)[9], 1ull);
     atomicAdd(&stat_slot(w.shard)[1], 1ull);
   }
+}
+
+// The bisection of bisect_root with kBisectLanes lanes of a wavefront on one
+// bracket (the group's lanes pass the same arguments): lane i evaluates node i
+// of the next four levels' interval tree, whose midpoints are the serial ones,
+// so the decisions and the result are the same in a quarter of the serial
+// steps.  A chain of some 45 evaluations of the nested solve in one lane set
+// the duration of the kernels that use it.
+constexpr int kBisectLanes = 16;
+__device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int kernel,
+                                                  double psi_star, const Bracket& b, int iters,
+                                                  double* xo, double* yo) {
+  const int lane = threadIdx.x & 63, node = lane % kBisectLanes + 1;
+  const int base = lane - (node - 1), depth = 31 - __builtin_clz(node);
+  double lo = b.ta, hi = b.tb;
+  const bool neg_lo = b.fa < 0.0;
+  int it = 0;
+  while (it < iters && hi - lo > 1e-14) {
+    double l = lo, h = hi;
+    for (int q = depth - 1; q >= 0; --q) {
+      const double mid = 0.5 * (l + h);
+      if ((node >> q) & 1) l = mid;
+      else h = mid;
+    }
+    bool ok = false, right = false;
+    if (node < kBisectLanes) {
+      double thI, sr, cr;
+      sincos(0.5 * (l + h), &sr, &cr);
+      ok = theta_imag_sc(m, mode, kernel, sr, cr, &thI);
+      if (ok) right = (wrap_pi(ray_angle_sc(m, mode, kernel, sr, cr, thI) - psi_star) < 0.0) == neg_lo;
+    }
+    const uint32_t oks = (uint32_t)(__ballot(ok) >> base), rights = (uint32_t)(__ballot(right) >> base);
+    for (int id = 1; id < kBisectLanes && it < iters && hi - lo > 1e-14; ++it) {
+      if (!((oks >> (id - 1)) & 1u)) return false;
+      const double mid = 0.5 * (lo + hi);
+      const int r = (rights >> (id - 1)) & 1u;
+      if (r) lo = mid;
+      else hi = mid;
+      id = 2 * id + r;
+    }
+  }
+  const double x = 0.5 * (lo + hi);
+  double y;
+  if (!theta_imag(m, mode, kernel, x, &y)) return false;
+  *xo = x;
+  *yo = y;
+  return true;
+}
+
+// Bisect the brackets of all lanes with `need` (every lane of the wavefront
+// calls it): kBisectLanes lanes each, 64 / kBisectLanes at a time.  job(src)
+// gives the medium and mode of lane src's bracket.  True where the lane's own
+// bracket got its root.
+template <class Job>
+__device__ __forceinline__ bool bisect_roots(const SolveParams& a, bool need, const Bracket& br,
+                                             double psi_star, double* x, double* y, Job job) {
+  constexpr int kGroups = 64 / kBisectLanes;
+  const int lane = threadIdx.x & 63, grp = lane / kBisectLanes;
+  unsigned long long mask = __ballot(need);
+  int rank = __popcll(mask & ((1ull << lane) - 1ull));
+  bool got = false;
+  for (; mask; rank -= kGroups) {
+    unsigned long long rest = mask;
+    for (int g = 0; g < grp && rest; ++g) rest &= rest - 1ull;
+    for (int g = 0; g < kGroups && mask; ++g) mask &= mask - 1ull;
+    const int src = rest ? __builtin_ctzll(rest) : 0;
+    const Bracket b{__shfl(br.ta, src), __shfl(br.tb, src), __shfl(br.fa, src), 0.0};
+    const double psi = __shfl(psi_star, src);
+    int mode;
+    const Medium m = job(src, &mode);
+    double xs = 0.0, ys = 0.0;
+    int ok = 0;
+    if (rest) ok = bisect_root_lanes(m, mode, a.kernel, psi, b, a.bisect_iters, &xs, &ys) ? 1 : 0;
+    const int from = rank >= 0 && rank < kGroups ? rank * kBisectLanes : lane;
+    ok = __shfl(ok, from);
+    xs = __shfl(xs, from);
+    ys = __shfl(ys, from);
+    if (need && rank >= 0 && rank < kGroups && ok) {
+      *x = xs;
+      *y = ys;
+      got = true;
+    }
+  }
+  return got;
 }
 
 // Fold directions across all window jobs (list blockIdx.y), four lanes each:
@@ -923,13 +1090,30 @@ k_warm_fold(WarmArgs w) {
     Entry best{};
     for (int b0 = 0; __any(valid && b0 < r.w); b0 += kBatch) {
       for (int i = 0; i < kSolveSlots; ++i) {
-        const int b = b0 + i * kFoldLanes + q;
-        if (!valid || b >= r.w) continue;
-        const WinBracket br = brs[r.z + b];
-        SolveCand& sc = s_c[dl][i * kFoldLanes + q];
-        bool cill = false;
-        sc.ok = bracket_root(a, m, mode, br.j, br.sa, br.sb, psi_star, el, &sc.e, &cill) ? 1 : 0;
-        sc.ill = cill ? 1 : 0;
+        const int bi = b0 + i * kFoldLanes + q;
+        const bool has = valid && bi < r.w;
+        if (!__any(has)) break;
+        double x = 0.0, y = 0.0;
+        Bracket br{};
+        bool ok = false;
+        if (has) {
+          const WinBracket wb = brs[r.z + bi];
+          br = bracket_at(a, wb.j, wb.sa, wb.sb, psi_star);
+          ok = bracket_newton(a, m, mode, br, wb.sa.x, wb.sb.x, psi_star, el, &x, &y);
+        }
+        const int k32 = (int)k, md32 = mode;
+        if (bisect_roots(a, has && !ok, br, psi_star, &x, &y, [&](int src, int* md) {
+              *md = __shfl(md32, src);
+              return load_medium(a.classes[__shfl(k32, src)]);
+            }))
+          ok = true;
+        if (has) {
+          SolveCand& sc = s_c[dl][i * kFoldLanes + q];
+          bool ill = false;
+          if (ok) bracket_entry(a, m, mode, br, psi_star, el, x, y, &sc.e, &ill);
+          sc.ok = ok ? 1 : 0;
+          sc.ill = ill ? 1 : 0;
+        }
       }
       __syncthreads();
       if (valid && q == 0)
@@ -1013,46 +1197,8 @@ __device__ __forceinline__ double warm3_target(const SolveArgs& a, int s, const 
 }
 
 __global__ void __launch_bounds__(mlp::kThreads) k_warm3_predict(Warm3Args w, int64_t n_rows) {
-  __shared__ mlp::InferTile t;
-  const SolveArgs& a = w.so;
-  const mlp::Net n = mlp::net_of(w.blob);
-  const int64_t base = (int64_t)blockIdx.x * mlp::kInferRows;
-  for (int r = threadIdx.x; r < mlp::kInferRows; r += blockDim.x) {
-    const int64_t e = base + r;
-    float f[mlp::kIn] = {};
-    if (e < n_rows) {
-      const int64_t job = e / a.n_solve;
-      const int s = (int)(e % a.n_solve);
-      const chert_class c = a.classes[job % a.n_classes];
-      mlp::features(c, a.modes[job / a.n_classes], warm3_target(a, s, c), f);
-    }
-    mlp::stage_row(n, t.x, r, f, e >= n_rows);
-  }
-  __syncthreads();
-  mlp::forward_infer(n, t, [&](int r, int col, float v) {
-    if (col < 2 && base + r < n_rows) (&w.pred[base + r].x)[col] = v;
-  });
-}
-
-// fold bins of each job's elastic ray-angle map (all bins if the map is not
-// finite everywhere); one wavefront per job
-__global__ void __launch_bounds__(64) k_warm3_folds(Warm3Args w) {
-  __shared__ double s_psi[kProxyN];
-  __shared__ uint32_t s_fold[kFoldWords];
-  __shared__ int s_all;
-  const SolveArgs& a = w.so;
-  const int64_t job = blockIdx.x;
-  const chert_class c = a.classes[job % a.n_classes];
-  const int mode = a.modes[job / a.n_classes];
-  if (threadIdx.x < kFoldWords) s_fold[threadIdx.x] = 0u;
-  if (threadIdx.x == 0) s_all = 0;
-  __syncthreads();
-  proxy_folds(elastic_of(load_medium(c)), mode, a.kernel, !class_block(c, mode), threadIdx.x, 64,
-              s_psi, s_fold, &s_all);
-  __syncthreads();
-  if (threadIdx.x < kFoldWords)
-    w.fold[job * kFoldWords + threadIdx.x] = s_all ? ~0u : s_fold[threadIdx.x];
-  if (threadIdx.x == 0) atomicAdd(&stat_slot(w.shard)[0], 1ull);
+  predict_rows(w.so, w.blob, w.pred, n_rows,
+               [&](int s, const chert_class& c) { return warm3_target(w.so, s, c); });
 }
 
 // one lane per (job, direction): Newton polish from the prediction and the
@@ -1098,7 +1244,7 @@ __global__ void __launch_bounds__(64) k_warm3_solve(Warm3Args w, int64_t n_rows)
         cnt[6] = 1;
         plain = true;
       } else {
-        x = fmod(x, kTwoPi);
+        if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
         if (x < 0.0) x += kTwoPi;
         const Vel v = energy_velocity(m, mode, a.kernel, x, y);
         Entry en;
@@ -1465,7 +1611,7 @@ static int build_cache(const chert_cache_desc* d, const chert_class* classes_dev
       CHERT_LAUNCH("k_build_slow", k_build_slow, dim3((unsigned)blocks), dim3(256), 0, s, so);
   } else if (jobs >= kFusedJobs && d->dim != 3) {
     CHERT_LAUNCH("k_build_fused", k_build_fused, dim3((unsigned)jobs), dim3(kNodeThreads),
-                 (size_t)d->n_sweep * sizeof(double2), s, so, (const int32_t*)nullptr,
+                 (size_t)sweep_stored(d->n_sweep) * sizeof(double2), s, so, (const int32_t*)nullptr,
                  (const int32_t*)nullptr, jobs);
   } else if (jobs > 0) {
     SweepArgs sa{};
@@ -1579,7 +1725,9 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
       const int64_t total = jobs * sweep_stored(d->n_sweep);
       const int64_t sb = (total + 63) / 64 > 65536 ? 65536 : (total + 63) / 64;
       CHERT_LAUNCH("k_sweep", k_sweep, dim3((unsigned)sb), dim3(64), 0, s, sa);
-      CHERT_LAUNCH("k_warm3_folds", k_warm3_folds, dim3((unsigned)jobs), dim3(64), 0, s, w);
+      CHERT_LAUNCH("k_warm_folds", k_warm_folds,
+                   dim3((unsigned)(jobs < kFoldGrid ? jobs : kFoldGrid)), dim3(64), 0, s, w.so, w.fold,
+                   w.shard, jobs);
       CHERT_LAUNCH("k_warm3_predict", k_warm3_predict,
                    dim3((unsigned)((rows + mlp::kInferRows - 1) / mlp::kInferRows)),
                    dim3(mlp::kThreads), 0, s, w, rows);
@@ -1615,6 +1763,8 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
     w.dirs = (int4*)tail;
     w.br_cap = (jobs + w.parts - 1) / w.parts * kBracketsPerJob;
     w.brs = (WinBracket*)(tail + al256((jobs + kWarmParts) * kDirsPerJob * sizeof(int4)));
+    static_assert(kFoldWords * sizeof(uint32_t) <= kBracketsPerJob * sizeof(WinBracket));
+    w.fold = (uint32_t*)w.brs;
   }
   w.stats = stats_dev ? (unsigned long long*)stats_dev : (unsigned long long*)(w.fb_len + 16);
   w.shard = (unsigned long long*)(ws + chert_build_cache_surrogate_workspace_bytes(d, n_classes) -
@@ -1631,6 +1781,9 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
     if (blocks > 0x7fffffffLL) return fail(CHERT_ERR_INVALID_ARG, "too many entries");
     CHERT_LAUNCH("k_warm_predict", k_warm_predict, dim3((unsigned)blocks), dim3(mlp::kThreads),
                  0, s, w, rows);
+    CHERT_LAUNCH("k_warm_folds", k_warm_folds,
+                 dim3((unsigned)(jobs < kFoldGrid ? jobs : kFoldGrid)), dim3(64), 0, s, w.so, w.fold,
+                 w.shard, jobs);
     const int per = warm_jobs(w.so.n_solve);
     CHERT_LAUNCH("k_warm_solve", k_warm_solve, dim3((unsigned)((jobs + per - 1) / per)),
                  dim3(kWarmSolveThreads), 0, s, w, jobs);
@@ -1643,7 +1796,7 @@ extern "C" int chert_build_cache_surrogate(const chert_cache_desc* d,
                  dim3((unsigned)(fneed < fmost ? fneed : fmost), (unsigned)w.parts), dim3(64), 0, s,
                  w);
     CHERT_LAUNCH("k_build_fused", k_build_fused, dim3((unsigned)grid), dim3(kNodeThreads),
-                 (size_t)d->n_sweep * sizeof(double2), s, w.so, (const int32_t*)w.fb_list,
+                 (size_t)sweep_stored(d->n_sweep) * sizeof(double2), s, w.so, (const int32_t*)w.fb_list,
                  (const int32_t*)w.fb_len, jobs);
   }
   CHERT_LAUNCH("k_warm_stats_fold", k_warm_stats_fold, dim3(1), dim3(64), 0, s,

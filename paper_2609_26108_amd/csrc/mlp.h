@@ -97,21 +97,19 @@ __device__ __forceinline__ uint16_t to_bf16(float x) {
 }
 
 // tanh of a hidden pre-activation whose result is rounded to BF16 next:
-// within 1e-6 relative (BF16's step is 4e-3).  Below |x| = 1/2 the odd
-// Taylor series through x^11; above, 1 - 2 / (1 + e^{2|x|}) with the
-// hardware exp2 and reciprocal.  Half the instructions of tanhf.
+// within 9e-7 relative (BF16's step is 4e-3).  Below |x| = 1/4 the odd Taylor
+// series through x^7 (the next term is 3.3e-7 there); above, 1 - 2 / (1 + e^{2x})
+// with the hardware exp2 and reciprocal (e^{2x} = inf gives 1; one ulp each
+// makes 8.4e-7 at 1/4, less further out).  The inference kernels are bound by
+// these, 384 per row, so the shortest of both that holds the error of a series
+// through x^11 joined at 1/2 is taken.
 __device__ __forceinline__ float tanh_act(float x) {
-  const float a = fabsf(x);
-  const float s = a * a;
-  float p = -0.008863235f;  // -1382/155925
-  p = p * s + 0.021869489f;  // 62/2835
-  p = p * s - 0.053968254f;  // -17/315
-  p = p * s + 0.13333334f;   // 2/15
-  p = p * s - 0.33333334f;   // -1/3
-  const float small = a + a * s * p;
-  const float e = __builtin_amdgcn_exp2f(a * 2.88539008f);  // e^{2a}
+  const float s = x * x;
+  const float p = (s * -0.053968254f + 0.13333334f) * s - 0.33333334f;  // -17/315, 2/15, -1/3
+  const float small = x + x * s * p;
+  const float e = __builtin_amdgcn_exp2f(x * 2.88539008f);  // e^{2x}
   const float big = 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + e);
-  return copysignf(a < 0.5f ? small : big, x);
+  return s < 0.0625f ? small : big;
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -212,8 +210,12 @@ __device__ __forceinline__ void stage_x(const Net& n, uint16_t* tx, uint16_t* tx
 // inference layer over kInferRows rows: out = tanh(in W + b); wavefront w
 // owns column blocks 2w and 2w + 1, keeps each one's weight fragments in
 // registers and runs it over every row block (same products, in the same
-// k order, as hidden_layer).  out may alias in: all threads pass a barrier
-// between the last read of in and the first write of out.
+// k order, as hidden_layer).  The weights are the A operand, so a lane's four
+// accumulators are four neighbouring columns of one row: two packed
+// conversions and one 8-byte LDS write instead of four of each.  out may alias
+// in: all threads pass a barrier between the last read of in and the first
+// write of out.
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 template <int K>
 __device__ __forceinline__ void infer_layer(const uint16_t* in, int pin, const uint16_t* Wt,
                                             const float* bias, uint16_t* out, int wave, int lane) {
@@ -221,14 +223,15 @@ __device__ __forceinline__ void infer_layer(const uint16_t* in, int pin, const u
   f32x4 acc[2][RB];
   for (int q = 0; q < 2; ++q) {
     const int cb = 2 * wave + q;
+    // the lane's four columns' biases: where the sums start
+    const f32x4 b = *reinterpret_cast<const f32x4*>(bias + cb * 16 + 4 * (lane >> 4));
     if constexpr (K == 16) {
       const s16x4 bv =
           *reinterpret_cast<const s16x4*>(Wt + (cb * 16 + (lane & 15)) * K + 4 * (lane >> 4));
       for (int rb = 0; rb < RB; ++rb) {
         const s16x4 av = *reinterpret_cast<const s16x4*>(in + (rb * 16 + (lane & 15)) * pin +
                                                          4 * (lane >> 4));
-        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        acc[q][rb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, z, 0, 0, 0);
+        acc[q][rb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bv, av, b, 0, 0, 0);
       }
     } else {
       bf16x8 bv[K / 32];
@@ -236,21 +239,23 @@ __device__ __forceinline__ void infer_layer(const uint16_t* in, int pin, const u
       for (int kk = 0; kk < K / 32; ++kk) bv[kk] = *reinterpret_cast<const bf16x8*>(wb + 32 * kk);
       for (int rb = 0; rb < RB; ++rb) {
         const uint16_t* a = in + (rb * 16 + (lane & 15)) * pin + 8 * (lane >> 4);
-        f32x4 c = {0.f, 0.f, 0.f, 0.f};
+        f32x4 c = b;
         for (int kk = 0; kk < K / 32; ++kk)
-          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(a + 32 * kk),
-                                                      bv[kk], c, 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              bv[kk], *reinterpret_cast<const bf16x8*>(a + 32 * kk), c, 0, 0, 0);
         acc[q][rb] = c;
       }
     }
   }
   __syncthreads();
   for (int q = 0; q < 2; ++q) {
-    const int col = (2 * wave + q) * 16 + acc_col(lane);
-    const float b = bias[col];
-    for (int rb = 0; rb < RB; ++rb)
-      for (int t = 0; t < 4; ++t)
-        out[(rb * 16 + acc_row(lane, t)) * kPH + col] = to_bf16(tanh_act(acc[q][rb][t] + b));
+    const int col = (2 * wave + q) * 16 + 4 * (lane >> 4);  // the first of the lane's four
+    for (int rb = 0; rb < RB; ++rb) {
+      f32x4 v = acc[q][rb];
+      for (int t = 0; t < 4; ++t) v[t] = tanh_act(v[t]);
+      *reinterpret_cast<bf16x4*>(out + (rb * 16 + (lane & 15)) * kPH + col) =
+          __builtin_convertvector(v, bf16x4);
+    }
   }
 }
 
@@ -283,33 +288,47 @@ __device__ __forceinline__ void forward_infer(const Net& n, InferTile& t, Store 
   }
 }
 
-// standardised BF16 input row r of an inference tile from its 16 raw inputs
-// (a padding row or a NaN input is staged as zero, as in stage_x)
-__device__ __forceinline__ void stage_row(const Net& n, uint16_t* tx, int r, const float* f,
-                                          bool pad) {
-  for (int i = 0; i < kIn; ++i)
-    tx[r * kPX + i] =
-        (pad || isnan(f[i])) ? (uint16_t)0 : to_bf16((f[i] - n.norm[i]) * n.norm[16 + i]);
+// inputs 4 part .. 4 part + 3 of (class, mode, local target ray angle): moduli
+// ratios | inverse quality factors 0..3 | the last one, mode | target angle
+__device__ __forceinline__ void feature_part(const chert_class& c, int mode, double psi, int part,
+                                             float* f) {
+  const double* q = &c.q11;
+  if (part == 0) {
+    const double inv33 = 1.0 / c.a33;
+    f[0] = (float)(c.a11 * inv33 - 1.0);
+    f[1] = (float)(c.a13 * inv33);
+    f[2] = (float)(c.a44 * inv33);
+    f[3] = (float)(c.a66 * inv33);
+  } else if (part == 1) {
+    for (int i = 0; i < 4; ++i) f[i] = isinf(q[i]) ? 0.f : (float)(1.0 / q[i]);
+  } else if (part == 2) {
+    f[0] = isinf(q[4]) ? 0.f : (float)(1.0 / q[4]);
+    for (int m = 0; m < 3; ++m) f[1 + m] = (mode == m) ? 1.f : 0.f;
+  } else {
+    double s, co;
+    sincos(psi, &s, &co);
+    f[0] = (float)co;
+    f[1] = (float)s;
+    f[2] = (float)((co - s) * (co + s));
+    f[3] = (float)(2.0 * s * co);
+  }
 }
 
-// the 16 network inputs of (class, mode, local target ray angle)
-__device__ __forceinline__ void features(const chert_class& c, int mode, double psi,
-                                         float* f) {
-  const double inv33 = 1.0 / c.a33;
-  f[0] = (float)(c.a11 * inv33 - 1.0);
-  f[1] = (float)(c.a13 * inv33);
-  f[2] = (float)(c.a44 * inv33);
-  f[3] = (float)(c.a66 * inv33);
-  const double* q = &c.q11;
-  for (int i = 0; i < 5; ++i) f[4 + i] = isinf(q[i]) ? 0.f : (float)(1.0 / q[i]);
-  for (int m = 0; m < 3; ++m) f[9 + m] = (mode == m) ? 1.f : 0.f;
-  double s, co, s2, c2;
-  sincos(psi, &s, &co);
-  sincos(2.0 * psi, &s2, &c2);
-  f[12] = (float)co;
-  f[13] = (float)s;
-  f[14] = (float)c2;
-  f[15] = (float)s2;
+// the 16 network inputs
+__device__ __forceinline__ void features(const chert_class& c, int mode, double psi, float* f) {
+  for (int part = 0; part < 4; ++part) feature_part(c, mode, psi, part, f + 4 * part);
+}
+
+// four standardised BF16 inputs of row r of an inference tile (a padding row
+// or a NaN input is staged as zero, as in stage_x)
+__device__ __forceinline__ void stage_part(const Net& n, uint16_t* tx, int r, int part,
+                                           const float* f, bool pad) {
+  uint16_t v[4];
+  for (int t = 0; t < 4; ++t) {
+    const int i = 4 * part + t;
+    v[t] = (pad || isnan(f[t])) ? (uint16_t)0 : to_bf16((f[t] - n.norm[i]) * n.norm[16 + i]);
+  }
+  *reinterpret_cast<ushort4*>(tx + r * kPX + 4 * part) = make_ushort4(v[0], v[1], v[2], v[3]);
 }
 
 }  // namespace mlp

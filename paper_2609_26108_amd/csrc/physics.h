@@ -551,6 +551,29 @@ __device__ __forceinline__ double ray_angle_sc(const Medium& m, int mode, int ke
   return atan2((r.w1 * D).re, (r.w3 * D).re);
 }
 
+// Ray angle of the elastic medium with m's real moduli at a real theta_R: the
+// map above with everything real (both kernels then agree), a seventh of its
+// operations.  NaN where the eigenvalue is not positive (unstable moduli).
+__device__ __forceinline__ double ray_angle_elastic(const Medium& m, int mode, double sr,
+                                                    double cr) {
+  const double n11 = sr * sr, n33 = cr * cr, a44 = m.a44.re;
+  if (mode == CHERT_QSH) {
+    const double a66 = m.a66.re;
+    return a66 * n11 + a44 * n33 > 0.0 ? atan2(a66 * sr, a44 * cr) : NAN;
+  }
+  const double G11 = m.a11.re * n11 + a44 * n33, G33 = a44 * n11 + m.a33.re * n33;
+  const double b = m.a13.re + a44, G13 = b * (sr * cr);
+  const double half = 0.5 * (G11 - G33), root = sqrt(half * half + G13 * G13);
+  const double G = 0.5 * (G11 + G33) + (mode == CHERT_QP ? root : -root);
+  const double ub = G - G11, wa = G - G33;
+  const bool u = ub * ub >= wa * wa;
+  const double g1 = u ? G13 : wa, g3 = u ? ub : G13;
+  const double S11 = g1 * g1, S33 = g3 * g3, B = b * (g1 * g3);
+  const double w1 = sr * (m.a11.re * S11 + a44 * S33) + cr * B;
+  const double w3 = cr * (m.a33.re * S33 + a44 * S11) + sr * B;
+  return G > 0.0 ? atan2(w1, w3) : NAN;
+}
+
 struct Entry {
   double V, A, Q, r1, r3, thR, thI, res;
 };

@@ -263,24 +263,30 @@ struct WindowTable {
   }
 };
 
-// Refine the bracket starting at sweep sample j and fold the root into the
-// running first-arrival choice (largest ray velocity; ties to the smaller
-// |theta_R - psi*|).
-// The root of the bracket at sweep sample j and its ray quantities; false if
-// neither the Newton step nor the bisection converges.  *cand_ill: the
-// bracket's ray-angle slope is below kIllSlope.
-__device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium& m, int mode,
-                                             int j,
-                                             double2 sa, double2 sb, double psi_star, bool el,
-                                             Entry* cand, bool* cand_ill) {
+// A bracket of the target ray angle: its theta_R interval and the misses at
+// the ends.
+struct Bracket {
+  double ta, tb, fa, fb;
+};
+__device__ __forceinline__ Bracket bracket_at(const SolveParams& a, int j, double2 sa, double2 sb,
+                                              double psi_star) {
   const double dth = kTwoPi / a.n_sweep;
-  double fa = wrap_pi(sa.y - psi_star);
-  double fb = wrap_pi(sb.y - psi_star);
-  double ta = (j + 0.5) * dth;
-  double tb = ta + dth;
+  Bracket b;
+  b.fa = wrap_pi(sa.y - psi_star);
+  b.fb = wrap_pi(sb.y - psi_star);
+  b.ta = (j + 0.5) * dth;
+  b.tb = b.ta + dth;
+  return b;
+}
+
+// Newton step of a bracket whose ends have theta_I = ya, yb; false where the
+// bisection has to decide.
+__device__ __forceinline__ bool bracket_newton(const SolveParams& a, const Medium& m, int mode,
+                                               const Bracket& b, double ya, double yb,
+                                               double psi_star, bool el, double* xo, double* yo) {
   double x, y;
-  bool ok = newton_root(m, mode, a.kernel, psi_star, ta, tb, sa.x, sb.x, fa, fb, a.newton_iters,
-                        &x, &y);
+  bool ok = newton_root(m, mode, a.kernel, psi_star, b.ta, b.tb, ya, yb, b.fa, b.fb,
+                        a.newton_iters, &x, &y);
   // The 2D Newton iteration does not know which homogeneity root theta_I
   // must be: keep its root only if y is the root nearest 0 at the final
   // theta_R (the outward scan's answer there); otherwise -- theta_I(theta_R)
@@ -288,7 +294,7 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
   // that definition.
   // It must also lie in its own bracket (the bisection's interval), not
   // wander into a neighbouring one.
-  if (ok) ok = x >= ta - 1e-12 && x <= tb + 1e-12;
+  if (ok) ok = x >= b.ta - 1e-12 && x <= b.tb + 1e-12;
   // (y in the first bracket of the scan, alone there, is that answer without
   // refining it; anything else is compared with the scan's own root.)
   if (ok && !el && !thi_is_nearest(m, mode, a.kernel, x, y)) {
@@ -296,8 +302,16 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
     sincos(x, &sx, &cx);
     ok = theta_imag_sc(m, mode, a.kernel, sx, cx, &ys) && fabs(ys - y) <= 1e-9;
   }
-  if (!ok) ok = bisect_root(m, mode, a.kernel, psi_star, ta, tb, fa, a.bisect_iters, &x, &y);
-  if (!ok) return false;
+  *xo = x;
+  *yo = y;
+  return ok;
+}
+
+// The ray quantities of a bracket's root.  *ill: the bracket's ray-angle
+// slope is below kIllSlope.
+__device__ __forceinline__ void bracket_entry(const SolveParams& a, const Medium& m, int mode,
+                                              const Bracket& b, double psi_star, bool el, double x,
+                                              double y, Entry* cand, bool* ill) {
   if (x >= kTwoPi) x -= kTwoPi;
   if (x < 0.0) x += kTwoPi;
   Vel v = energy_velocity(m, mode, a.kernel, x, y);
@@ -306,7 +320,20 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
   cand->thI = y;
   double h = el ? 0.0 : homog_residual(v);
   cand->res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi_star)));
-  *cand_ill = fabs((fb - fa) / (tb - ta)) < kIllSlope;
+  *ill = fabs((b.fb - b.fa) / (b.tb - b.ta)) < kIllSlope;
+}
+
+// The root of the bracket at sweep sample j and its ray quantities; false if
+// neither the Newton step nor the bisection converges.
+__device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium& m, int mode,
+                                             int j, double2 sa, double2 sb, double psi_star,
+                                             bool el, Entry* cand, bool* cand_ill) {
+  const Bracket b = bracket_at(a, j, sa, sb, psi_star);
+  double x, y;
+  if (!bracket_newton(a, m, mode, b, sa.x, sb.x, psi_star, el, &x, &y) &&
+      !bisect_root(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
+    return false;
+  bracket_entry(a, m, mode, b, psi_star, el, x, y, cand, cand_ill);
   return true;
 }
 
