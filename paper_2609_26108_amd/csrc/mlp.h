@@ -67,7 +67,8 @@ constexpr float kOneMinusBeta1 = 0.1f, kOneMinusBeta2 = 0.001f;
 // per-workgroup gradient partial: kParams floats, then the loss sum
 constexpr int kPartStride = 35776;  // >= kParams + 1, multiple of 64
 constexpr int kRows = 32;           // samples per workgroup tile
-constexpr int kThreads = 256;       // 4 wavefronts
+constexpr int kThreads = 256;       // inference: 4 wavefronts
+constexpr int kTrainThreads = 1024; // training: 16 wavefronts, an output tile each
 
 struct Net {
   const float* norm;      // in_mean[16], in_inv[16], out_mean[4], out_std[4]
@@ -113,28 +114,40 @@ __device__ __forceinline__ float tanh_act(float x) {
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// 16 x 16 tile of A Bt^T over K (multiple of 32); A, Bt point at the tile's
-// first row; pa, pb are row pitches in elements
-__device__ __forceinline__ f32x4 mma_k32(const uint16_t* A, int pa, const uint16_t* Bt, int pb,
-                                         int K, int lane) {
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  const uint16_t* a = A + (lane & 15) * pa + 8 * (lane >> 4);
-  const uint16_t* b = Bt + (lane & 15) * pb + 8 * (lane >> 4);
-  for (int k = 0; k < K; k += 32) {
-    bf16x8 av = *reinterpret_cast<const bf16x8*>(a + k);
-    bf16x8 bv = *reinterpret_cast<const bf16x8*>(b + k);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
+// one lane's part of a 16-row operand (k-contiguous rows of K elements): the
+// fragments of every k step
+template <int K>
+struct Frag {
+  bf16x8 v[K / 32];
+};
+template <>
+struct Frag<16> {
+  s16x4 v;
+};
+template <int K>
+__device__ __forceinline__ Frag<K> frag_of(const uint16_t* p, int pitch, int lane) {
+  Frag<K> f;
+  if constexpr (K == 16) {
+    f.v = *reinterpret_cast<const s16x4*>(p + (lane & 15) * pitch + 4 * (lane >> 4));
+  } else {
+    for (int k = 0; k < K / 32; ++k)
+      f.v[k] = *reinterpret_cast<const bf16x8*>(p + (lane & 15) * pitch + 8 * (lane >> 4) + 32 * k);
   }
-  return acc;
+  return f;
 }
 
-// same for K = 16
-__device__ __forceinline__ f32x4 mma_k16(const uint16_t* A, int pa, const uint16_t* Bt, int pb,
-                                         int lane) {
+// 16 x 16 tile of A Bt^T over K; A points at the tile's first row
+template <int K>
+__device__ __forceinline__ f32x4 mma(const uint16_t* A, int pa, const Frag<K>& b, int lane) {
+  const Frag<K> a = frag_of<K>(A, pa, lane);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  s16x4 av = *reinterpret_cast<const s16x4*>(A + (lane & 15) * pa + 4 * (lane >> 4));
-  s16x4 bv = *reinterpret_cast<const s16x4*>(Bt + (lane & 15) * pb + 4 * (lane >> 4));
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
+  if constexpr (K == 16) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.v, b.v, acc, 0, 0, 0);
+  } else {
+    for (int k = 0; k < K / 32; ++k)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[k], b.v[k], acc, 0, 0, 0);
+  }
+  return acc;
 }
 
 // LDS row pitches (elements): +8 BF16 per row keeps 16-byte reads of 16
@@ -161,37 +174,28 @@ struct __align__(16) TrainTile {
   uint16_t ht[3][kHid * kPT];
   uint16_t d[kRows * kPH];
   uint16_t dt[kHid * kPT];
-  float loss[kThreads / 64];
+  float loss[kTrainThreads / 64];
 };
 
 // rows (4 (lane/16) + t) and column (lane % 16) of a tile's accumulator
 __device__ __forceinline__ int acc_row(int lane, int t) { return 4 * (lane >> 4) + t; }
 __device__ __forceinline__ int acc_col(int lane) { return lane & 15; }
 
-// hidden layer: out = tanh(in W + b), tiles (rb in {0,1}) x (cb in {2w, 2w+1})
-// of wavefront w; writes the BF16 activations row-major and, if ht != null,
-// transposed
+// hidden layer of a training tile: out = tanh(in W + b), tile (wave / 8,
+// wave % 8) of wavefront `wave`, whose weight fragments and bias are w and b;
+// writes the BF16 activations row-major and transposed
 template <int K>
-__device__ __forceinline__ void hidden_layer(const uint16_t* in, int pin, const uint16_t* Wt,
-                                             const float* bias, uint16_t* out, uint16_t* ht,
-                                             int wave, int lane) {
-  for (int rb = 0; rb < 2; ++rb)
-    for (int q = 0; q < 2; ++q) {
-      const int cb = 2 * wave + q;
-      f32x4 acc;
-      if constexpr (K == 16)
-        acc = mma_k16(in + rb * 16 * pin, pin, Wt + cb * 16 * K, K, lane);
-      else
-        acc = mma_k32(in + rb * 16 * pin, pin, Wt + cb * 16 * K, K, K, lane);
-      const int col = cb * 16 + acc_col(lane);
-      const float b = bias[col];
-      for (int t = 0; t < 4; ++t) {
-        const int row = rb * 16 + acc_row(lane, t);
-        const uint16_t v = to_bf16(tanhf(acc[t] + b));
-        out[row * kPH + col] = v;
-        if (ht) ht[col * kPT + row] = v;
-      }
-    }
+__device__ __forceinline__ void hidden_layer(const uint16_t* in, int pin, const Frag<K>& w, float b,
+                                             uint16_t* out, uint16_t* ht, int wave, int lane) {
+  const int rb = wave >> 3, col = (wave & 7) * 16 + acc_col(lane);
+  const f32x4 acc = mma<K>(in + rb * 16 * pin, pin, w, lane);
+  uint16_t v[4];
+  for (int t = 0; t < 4; ++t) {
+    v[t] = to_bf16(tanhf(acc[t] + b));
+    out[(rb * 16 + acc_row(lane, t)) * kPH + col] = v[t];
+  }
+  *reinterpret_cast<ushort4*>(ht + col * kPT + rb * 16 + acc_row(lane, 0)) =
+      make_ushort4(v[0], v[1], v[2], v[3]);
 }
 
 // stage R standardised input rows (BF16) into the tile; src(r, i) is the

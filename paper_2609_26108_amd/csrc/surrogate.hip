@@ -217,9 +217,10 @@ __device__ __forceinline__ void layer_grads(const uint16_t* at, const uint16_t* 
                                             int oW, int oB, int nvalid_out, int wave, int lane) {
   // dW[i][j] = sum_s a[s][i] d[s][j]: tiles (ib, jb), K = 32 samples
   constexpr int nib = KIN / 16, njb = NOUT / 16;
-  for (int tix = wave; tix < nib * njb; tix += kThreads / 64) {
+  for (int tix = wave; tix < nib * njb; tix += kTrainThreads / 64) {
     const int ib = tix / njb, jb = tix % njb;
-    const f32x4 acc = mma_k32(at + ib * 16 * kPT, kPT, dt + jb * 16 * kPT, kPT, kRows, lane);
+    const f32x4 acc = mma<kRows>(at + ib * 16 * kPT, kPT,
+                                 frag_of<kRows>(dt + jb * 16 * kPT, kPT, lane), lane);
     const int j = jb * 16 + acc_col(lane);
     if (j < nvalid_out)
       for (int t = 0; t < 4; ++t) {
@@ -227,76 +228,97 @@ __device__ __forceinline__ void layer_grads(const uint16_t* at, const uint16_t* 
         part[oW + i * nvalid_out + j] = acc[t];
       }
   }
-  for (int j = threadIdx.x; j < nvalid_out; j += blockDim.x) {
+  // the last threads: the first wavefronts may hold one tile more
+  const int j = (int)(kTrainThreads - 1 - threadIdx.x);
+  if (j < nvalid_out) {
+    __align__(16) uint16_t d[kRows];
+    for (int r = 0; r < kRows; r += 8)
+      *reinterpret_cast<bf16x8*>(d + r) = *reinterpret_cast<const bf16x8*>(dt + j * kPT + r);
     float s = 0.f;
-    for (int r = 0; r < kRows; ++r) s += from_bf16(dt[j * kPT + r]);
+    for (int r = 0; r < kRows; ++r) s += from_bf16(d[r]);
     part[oB + j] = s;
   }
 }
 
-// propagate the error through W (Bt = W [in=128][out=K]) and the tanh of
-// the layer below (activations h): t.d <- (d W^T) * (1 - h^2)
+// propagate the error through W (w: the wavefront's 16 rows of Bt = W
+// [in=128][out=K]) and the tanh of the layer below (activations h):
+// t.d <- (d W^T) * (1 - h^2)
 template <int K>
-__device__ __forceinline__ void back_error(TrainTile& t, const uint16_t* Wb, const uint16_t* h,
+__device__ __forceinline__ void back_error(TrainTile& t, const Frag<K>& w, const uint16_t* h,
                                            int wave, int lane) {
-  f32x4 acc[2][2];
-  for (int rb = 0; rb < 2; ++rb)
-    for (int q = 0; q < 2; ++q) {
-      const int cb = 2 * wave + q;
-      if constexpr (K == 16)
-        acc[rb][q] = mma_k16(t.d + rb * 16 * kPH, kPH, Wb + cb * 16 * K, K, lane);
-      else
-        acc[rb][q] = mma_k32(t.d + rb * 16 * kPH, kPH, Wb + cb * 16 * K, K, K, lane);
-    }
-  __syncthreads();  // every wave has read t.d
-  for (int rb = 0; rb < 2; ++rb)
-    for (int q = 0; q < 2; ++q) {
-      const int col = (2 * wave + q) * 16 + acc_col(lane);
-      for (int tt = 0; tt < 4; ++tt) {
-        const int row = rb * 16 + acc_row(lane, tt);
-        const float hv = from_bf16(h[row * kPH + col]);
-        const uint16_t v = to_bf16(acc[rb][q][tt] * (1.f - hv * hv));
-        t.d[row * kPH + col] = v;
-        t.dt[col * kPT + row] = v;
-      }
-    }
+  const int rb = wave >> 3, col = (wave & 7) * 16 + acc_col(lane);
+  const f32x4 acc = mma<K>(t.d + rb * 16 * kPH, kPH, w, lane);
+  __syncthreads();  // every wave has read t.d (and t.dt)
+  uint16_t v[4];
+  for (int tt = 0; tt < 4; ++tt) {
+    const int row = rb * 16 + acc_row(lane, tt);
+    const float hv = from_bf16(h[row * kPH + col]);
+    v[tt] = to_bf16(acc[tt] * (1.f - hv * hv));
+    t.d[row * kPH + col] = v[tt];
+  }
+  *reinterpret_cast<ushort4*>(t.dt + col * kPT + rb * 16 + acc_row(lane, 0)) =
+      make_ushort4(v[0], v[1], v[2], v[3]);
   __syncthreads();
 }
 
-__global__ void __launch_bounds__(kThreads) k_sg_grad(const uint8_t* blob, const float* x,
-                                                      const float* y, const int32_t* idx,
-                                                      int32_t batch, float* partials) {
+// A training batch is a few dozen workgroups, so the time is one workgroup's
+// chain of layers.  Sixteen wavefronts own one 16 x 16 output tile of a layer
+// each, and every weight fragment, bias and target a wavefront will need is
+// loaded before the first product: four wavefronts, loading each layer's
+// weights when they came to it, took 29 us at 2,048 samples, this 24 (event times, 5 us of them the launch).
+__global__ void __launch_bounds__(kTrainThreads) k_sg_grad(const uint8_t* blob, const float* x,
+                                                           const float* y, const int32_t* idx,
+                                                           int32_t batch, float* partials) {
   __shared__ TrainTile t;
   const Net n = net_of(blob);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int base = blockIdx.x * kRows;
   float* part = partials + (size_t)blockIdx.x * kPartStride;
+  const int cb = wave & 7, bcol = cb * 16 + acc_col(lane);
+  const Frag<kIn> w1 = frag_of<kIn>(n.fwd + fW1 + cb * 16 * kIn, kIn, lane);
+  const Frag<kHid> w2 = frag_of<kHid>(n.fwd + fW2 + cb * 16 * kHid, kHid, lane);
+  const Frag<kHid> w3 = frag_of<kHid>(n.fwd + fW3 + cb * 16 * kHid, kHid, lane);
+  const Frag<kHid> w4 = frag_of<kHid>(n.fwd + fW4, kHid, lane);
+  const Frag<kOutPad> u4 = frag_of<kOutPad>(n.bwd + bW4 + cb * 16 * kOutPad, kOutPad, lane);
+  const Frag<kHid> u3 = frag_of<kHid>(n.bwd + bW3 + cb * 16 * kHid, kHid, lane);
+  const Frag<kHid> u2 = frag_of<kHid>(n.bwd + bW2 + cb * 16 * kHid, kHid, lane);
+  const float b1 = n.master[oB1 + bcol], b2 = n.master[oB2 + bcol], b3 = n.master[oB3 + bcol];
+  const int col = acc_col(lane);
+  float ys[4], b4 = 0.f;  // targets of this lane's outputs (padded rows: any)
+  if (wave < 2) {
+    const int yc = col < kOut ? col : 0;
+    int at[4];
+    for (int tt = 0; tt < 4; ++tt) {
+      const int row = base + wave * 16 + acc_row(lane, tt);
+      at[tt] = idx[row < batch ? row : batch - 1];
+    }
+    b4 = n.master[oB4 + yc];
+    const float mean = n.norm[32 + yc], std = n.norm[36 + yc];
+    for (int tt = 0; tt < 4; ++tt) ys[tt] = (y[(int64_t)at[tt] * kOut + yc] - mean) / std;
+  }
   stage_x<true>(n, t.x, t.xt, [&](int r, int i) -> float {
     return base + r < batch ? x[(int64_t)idx[base + r] * kIn + i] : NAN;
   });
-  __syncthreads();
-  hidden_layer<kIn>(t.x, kPX, n.fwd + fW1, n.master + oB1, t.h[0], t.ht[0], wave, lane);
-  __syncthreads();
-  hidden_layer<kHid>(t.h[0], kPH, n.fwd + fW2, n.master + oB2, t.h[1], t.ht[1], wave, lane);
-  __syncthreads();
-  hidden_layer<kHid>(t.h[1], kPH, n.fwd + fW3, n.master + oB3, t.h[2], t.ht[2], wave, lane);
-  // output layer and its error: d = 2 (out - y) / (batch * 4), zero on
-  // padded rows and columns
+  // the output layer's error: zero on padded rows and columns
   for (int q = threadIdx.x; q < kRows * kPH; q += blockDim.x) t.d[q] = 0;
   for (int q = threadIdx.x; q < kHid * kPT; q += blockDim.x) t.dt[q] = 0;
   __syncthreads();
+  hidden_layer<kIn>(t.x, kPX, w1, b1, t.h[0], t.ht[0], wave, lane);
+  __syncthreads();
+  hidden_layer<kHid>(t.h[0], kPH, w2, b2, t.h[1], t.ht[1], wave, lane);
+  __syncthreads();
+  hidden_layer<kHid>(t.h[1], kPH, w3, b3, t.h[2], t.ht[2], wave, lane);
+  __syncthreads();
+  // output layer and its error: d = 2 (out - y) / (batch * 4)
   float lsum = 0.f;
   if (wave < 2) {
-    const f32x4 acc = mma_k32(t.h[2] + wave * 16 * kPH, kPH, n.fwd + fW4, kHid, kHid, lane);
-    const int col = acc_col(lane);
+    const f32x4 acc = mma<kHid>(t.h[2] + wave * 16 * kPH, kPH, w4, lane);
     const float scale = 2.f / ((float)batch * (float)kOut);
     if (col < kOut)
       for (int tt = 0; tt < 4; ++tt) {
         const int row = wave * 16 + acc_row(lane, tt);
         if (base + row >= batch) continue;
-        const float ys = (y[(int64_t)idx[base + row] * kOut + col] - n.norm[32 + col]) /
-                         n.norm[36 + col];
-        const float e = acc[tt] + n.master[oB4 + col] - ys;
+        const float e = acc[tt] + b4 - ys[tt];
         lsum += e * e;
         const uint16_t v = to_bf16(scale * e);
         t.d[row * kPH + col] = v;
@@ -307,21 +329,35 @@ __global__ void __launch_bounds__(kThreads) k_sg_grad(const uint8_t* blob, const
   if (lane == 0) t.loss[wave] = lsum;
   __syncthreads();
   layer_grads<kHid, kOutPad>(t.ht[2], t.dt, part, oW4, oB4, kOut, wave, lane);
-  back_error<kOutPad>(t, n.bwd + bW4, t.h[2], wave, lane);
+  back_error<kOutPad>(t, u4, t.h[2], wave, lane);
   layer_grads<kHid, kHid>(t.ht[1], t.dt, part, oW3, oB3, kHid, wave, lane);
-  back_error<kHid>(t, n.bwd + bW3, t.h[1], wave, lane);
+  back_error<kHid>(t, u3, t.h[1], wave, lane);
   layer_grads<kHid, kHid>(t.ht[0], t.dt, part, oW2, oB2, kHid, wave, lane);
-  back_error<kHid>(t, n.bwd + bW2, t.h[0], wave, lane);
+  back_error<kHid>(t, u2, t.h[0], wave, lane);
   layer_grads<kIn, kHid>(t.xt, t.dt, part, oW1, oB1, kHid, wave, lane);
-  if (threadIdx.x == 0) part[kParams] = t.loss[0] + t.loss[1] + t.loss[2] + t.loss[3];
+  if (threadIdx.x == 0) part[kParams] = t.loss[0] + t.loss[1];
 }
 
-__global__ void __launch_bounds__(256) k_sg_reduce(const float* partials, int n_parts,
-                                                   int32_t batch, float* grad, float* loss) {
+// sums the workgroups' partials in their order, a parameter per thread; the
+// loads of 16 partials are in flight together (one at a time: 18 us for 64
+// partials, 6 so)
+constexpr int kReduceThreads = 128;
+__global__ void __launch_bounds__(kReduceThreads) k_sg_reduce(const float* partials, int n_parts,
+                                                              int32_t batch, float* grad,
+                                                              float* loss) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > kParams) return;
+  constexpr int kFly = 16;
   float s = 0.f;
-  for (int w = 0; w < n_parts; ++w) s += partials[(size_t)w * kPartStride + p];
+  int w = 0;
+  for (; w + kFly <= n_parts; w += kFly) {
+    float v[kFly];
+#pragma unroll
+    for (int i = 0; i < kFly; ++i) v[i] = partials[(size_t)(w + i) * kPartStride + p];
+#pragma unroll
+    for (int i = 0; i < kFly; ++i) s += v[i];
+  }
+  for (; w < n_parts; ++w) s += partials[(size_t)w * kPartStride + p];
   if (p < kParams) grad[p] = s;
   else if (loss) *loss = s / ((float)batch * (float)kOut);
 }
@@ -459,9 +495,10 @@ extern "C" int chert_surrogate_grad(const void* blob_dev, const float* x_dev, co
   hipStream_t s = (hipStream_t)stream;
   const int parts = (batch + kRows - 1) / kRows;
   float* partials = (float*)workspace_dev;
-  CHERT_LAUNCH("k_sg_grad", k_sg_grad, dim3(parts), dim3(kThreads), 0, s,
+  CHERT_LAUNCH("k_sg_grad", k_sg_grad, dim3(parts), dim3(kTrainThreads), 0, s,
                (const uint8_t*)blob_dev, x_dev, y_dev, idx_dev, batch, partials);
-  CHERT_LAUNCH("k_sg_reduce", k_sg_reduce, dim3((kParams + 1 + 255) / 256), dim3(256), 0, s,
+  CHERT_LAUNCH("k_sg_reduce", k_sg_reduce,
+               dim3((kParams + kReduceThreads) / kReduceThreads), dim3(kReduceThreads), 0, s,
                partials, parts, batch, grad_dev, loss_dev);
   return launch_status();
 }
