@@ -446,10 +446,12 @@ __device__ __forceinline__ TileCtx tile_begin(const RelaxArgs& a, int round, int
     *s_flag = f;
   }
   __syncthreads();
+  // (uniform, but read from LDS: without the hint the problem's and job's
+  // fields live in vector registers)
   TileCtx c;
-  c.active = *s_flag;
+  c.active = __builtin_amdgcn_readfirstlane(*s_flag);
   if (!c.active) return c;
-  c.p = *s_prob;
+  c.p = __builtin_amdgcn_readfirstlane(*s_prob);
   const ProbDev& pr = a.probs[c.p];
   const JobDev& jb = a.jobs[pr.job];
   c.t = T - pr.tile_base;
@@ -864,21 +866,24 @@ __device__ __forceinline__ void relax_tau(const RelaxArgs& a, int round, int T) 
     levels = push_levels<G, kWLds>(a, c, jb, pr.field, s, Wp, 0, ml, nf, s_cnt, &raw,
                                         &again);
 
+  // the neighbours to wake first: their flags' atomics then overlap the
+  // field writes (a barrier waits for a workgroup's writes)
   int mask = again ? (1 << 4) : 0;  // bit 4 = this tile again
-  if (ml >= 0 && s.cls[ml] >= 0 && s.val[ml] < orig) {
-    int x, z;
+  const double v = ml >= 0 && s.cls[ml] >= 0 ? s.val[ml] : orig;
+  int x = 0, z = 0;
+  if (v < orig) {
     cell_xz(a, ml, &x, &z);
     x -= R;
     z -= R;
-    pr.tau[(int64_t)(c.x0 + x) + (int64_t)jb.nx * (c.z0 + z)] = s.val[ml];
     const int bb = border_bits(x, z, a.tx, a.tz, R);
     mask |= bb;
-    if (bb && a.bucket > 0.0) atomicMin(&s_key, dbits(s.val[ml]));
+    if (bb && a.bucket > 0.0) atomicMin(&s_key, dbits(v));
   }
-  count_visit(a, 0, raw + (long long)np * n_off, levels);
   if (mask) atomicOr(&s_mask, mask);
   __syncthreads();
+  if (v < orig) pr.tau[(int64_t)(c.x0 + x) + (int64_t)jb.nx * (c.z0 + z)] = v;
   if (threadIdx.x < 64 && s_mask) activate(a, round, c, pr, jb, s_mask, s_key);
+  count_visit(a, 0, raw + (long long)np * n_off, levels);
 }
 
 // ------------------------------------------- predecessor tree phase ---
@@ -998,55 +1003,61 @@ __device__ __forceinline__ unsigned long long tree_key(unsigned long long ki, in
 struct TreeSmem {
   unsigned long long* key;  // [lw*lh] hop << 32 | predecessor offset index
   double* ts;               // [lw*lh] t* (NaN while unknown)
+  int32_t* cls;             // [lw*lh]
   uint32_t* om;             // [nw][lw*lh] tight out-masks
-  int32_t* cls;
-  int32_t* off;
-  int32_t* list;            // frontier (interior LDS indices)
-  uint8_t* mark;            // [lw*lh] named or confirmed by a push of this level
+  int32_t* off;             // [n_off] offset in the box (low 16 bits), ox, oz (8 bits each)
 };
 
 __device__ __forceinline__ TreeSmem carve_tree(const RelaxArgs& a, void* base) {
   TreeSmem s;
-  const int n = a.lw * a.lh, T = a.tx * a.tz;
+  const int n = a.lw * a.lh;
   char* p = (char*)base;
   s.key = (unsigned long long*)p;
   p += sizeof(unsigned long long) * n;
   s.ts = (double*)p;
   p += sizeof(double) * n;
-  s.om = (uint32_t*)p;
-  p += sizeof(uint32_t) * a.nw * n;
   s.cls = (int32_t*)p;
   p += sizeof(int32_t) * n;
+  s.om = (uint32_t*)p;
+  p += sizeof(uint32_t) * a.nw * n;
   s.off = (int32_t*)p;
-  p += sizeof(int32_t) * ((a.n_off + 1) & ~1);
-  s.list = (int32_t*)p;
-  p += sizeof(int32_t) * T;
-  s.mark = (uint8_t*)p;
   return s;
 }
 
-static size_t tree_lds_bytes(int lw, int lh, int nw, int n_off, int tx, int tz) {
+static size_t tree_lds_bytes(int lw, int lh, int nw, int n_off) {
   const size_t n = (size_t)lw * lh;
   return (2 * sizeof(double) + sizeof(uint32_t) * nw + sizeof(int32_t)) * n +
-         sizeof(int32_t) * ((n_off + 1) & ~1) + sizeof(int32_t) * tx * tz + ((n + 7) & ~(size_t)7);
+         sizeof(int32_t) * ((n_off + 1) & ~1);
 }
 
 // Phase TREE: hop counts, predecessors (eq 33) and t* in one relaxation.
 // key_j = min over tight in-edges i -> j of (hop_i + 1, offset index): BFS
 // layers over the tight edges with eq 33's tie rule built in.  With t*,
-// t*_j = t*_p + w_I(p -> j) for the predecessor p the key names; a node
-// whose key or t* changed pushes to its tight children, and a child that
-// the push names its predecessor again re-reads the parent's t*.  Keys only
+// t*_j = t*_p + w_I(p -> j) for the predecessor p the key names.  Keys only
 // decrease, t* follows the (acyclic) predecessor tree, so the fixed point
 // is the ordered fold along that tree for any schedule.
-// Levels as in push_levels: the items are (frontier node, 32-offset word of
-// its tight mask), a node having little more than one tight out-edge on
-// average, and heads are lowered and marked without waiting for answers;
-// then each thread looks at its own node, re-reads t* and joins the next
-// frontier if its key or t* changed.
+//
+// A node has little more than one tight out-edge on average, so a visit lasts
+// as long as its longest chain, up to sixty nodes, times the latency of a
+// level, and a level moves few edges.  So a level is one barrier and three LDS
+// round trips, and the visit has two runs of them.  Keys: a thread polls its
+// own node's key and, if it changed, lowers the heads of its tight edges (the
+// first four held in registers) without waiting for answers.  Then the
+// predecessors are final and the weights of their edges are loaded together
+// (one cold load somewhere in every level cost as much as the rest of the
+// level twice over).  t*: a thread polls its predecessor's.  Polled values may
+// be a level old; whoever changes one asks for the next level.  Before level 0
+// the halo's tight edges are pushed into the tile (pulling the border band
+// through every offset cost as much as twenty levels).
+// 16 shots, 201,051 nodes, per-node caches: 4.8 -> 3.9 ms; layered 401 x 201
+// model: 0.89 -> 0.61; 101 x 101 nodes, one class: 0.35 -> 0.25 (frontier
+// lists, marks and two barriers took 2,600-3,900 cycles a level; now some 500).
+// (Tried: one lane walking a whole chain without barriers, the other heads
+// left for the next pass; chains branch all along, so there were as many
+// passes as levels, 9.0, 2.5 and 0.75 ms.)
 __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T) {
   extern __shared__ double smem_d[];
-  __shared__ int s_flag, s_prob, s_mask, s_cnt[3];
+  __shared__ int s_flag, s_prob, s_mask, s_due[3];
   __shared__ unsigned long long s_key;
   const TileCtx c = tile_begin(a, round, T, &s_flag, &s_prob, 1);
   if (!c.active) return;
@@ -1060,145 +1071,191 @@ __device__ __forceinline__ void relax_tree(const RelaxArgs& a, int round, int T)
   if (threadIdx.x == 0) {
     s_mask = 0;
     s_key = kInfBits;
-    s_cnt[0] = 0;
-    s_cnt[1] = 0;
-    s_cnt[2] = 0;
+    s_due[0] = 0;
   }
-  for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    int x, z;
-    cell_xz(a, q, &x, &z);
-    const int gx = c.x0 + x - R, gz = c.z0 + z - R;
-    const int32_t k = cell_class(a, jb, gx, gz);
-    const bool in = k != -1;
-    const int64_t g = (int64_t)gx + (int64_t)jb.nx * gz;
-    s.cls[q] = k;
-    s.mark[q] = 0;
-    s.key[q] = in ? pr.key[g] : kKeyUnset;
-    s.ts[q] = (in && fold) ? pr.tstar[g] : NAN;
-    for (int w = 0; w < nw; ++w) s.om[w * n + q] = in ? pr.tight[(int64_t)w * gn + g] : 0u;
+  // the box, two nodes a thread at a time with all their loads in flight (one
+  // node, its class first, was a third of a visit)
+  constexpr int kFly = 2, kWords = 3;
+  for (int q0 = threadIdx.x; q0 < n; q0 += kFly * blockDim.x) {
+    int64_t g[kFly];
+    bool in[kFly];
+    unsigned long long key[kFly];
+    double ts[kFly];
+    int32_t cls[kFly];
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      int x, z;
+      cell_xz(a, q0 + u * blockDim.x, &x, &z);
+      const int gx = c.x0 + x - R, gz = c.z0 + z - R;
+      in[u] = q0 + u * blockDim.x < n && gx >= 0 && gx < jb.nx && gz >= 0 && gz < jb.nz;
+      g[u] = in[u] ? (int64_t)gx + (int64_t)jb.nx * gz : 0;
+      key[u] = pr.key[g[u]];
+      ts[u] = fold ? pr.tstar[g[u]] : NAN;
+      cls[u] = jb.per_node ? 0 : jb.class_id[g[u]];
+    }
+    for (int w0 = 0; w0 < nw; w0 += kWords) {
+      uint32_t m[kFly][kWords];
+#pragma unroll
+      for (int u = 0; u < kFly; ++u)
+#pragma unroll
+        for (int v = 0; v < kWords; ++v)
+          m[u][v] = pr.tight[(int64_t)(w0 + v < nw ? w0 + v : w0) * gn + g[u]];
+#pragma unroll
+      for (int u = 0; u < kFly; ++u)
+#pragma unroll
+        for (int v = 0; v < kWords; ++v)
+          if (q0 + u * blockDim.x < n && w0 + v < nw)
+            s.om[(w0 + v) * n + q0 + u * blockDim.x] = in[u] ? m[u][v] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      const int q = q0 + u * blockDim.x;
+      if (q >= n) break;
+      s.cls[q] = !in[u] ? -1 : (cls[u] >= 0 && cls[u] < jb.K ? cls[u] : -2);
+      s.key[q] = in[u] ? key[u] : kKeyUnset;
+      s.ts[q] = in[u] ? ts[u] : NAN;
+    }
   }
-  for (int o = threadIdx.x; o < n_off; o += blockDim.x) s.off[o] = a.ox[o] + a.oz[o] * lw;
+  for (int o = threadIdx.x; o < n_off; o += blockDim.x)
+    s.off[o] = (int32_t)((uint32_t)((a.ox[o] & 0xff) << 8 | (a.oz[o] & 0xff)) << 16 |
+                         ((uint32_t)(a.ox[o] + a.oz[o] * lw) & 0xffffu));
   __syncthreads();
   const int ml = my_node(a, c);
-  long long raw = 0;
+  int raw = 0;
   const unsigned long long okey = ml >= 0 ? s.key[ml] : 0ull;
   const double ots = ml >= 0 ? s.ts[ml] : 0.0;
 
-  // t*_j from the predecessor its key names; true if t*_j changed
-  auto refold = [&](int j, unsigned long long k) -> bool {
-    if (k == kKeyUnset || (k >> 32) == 0ull) return false;  // unreached, or the source
-    const int o = (int)(k & 0xffffffffull);
-    const int p = j - s.off[o];
-    const double t =
-        __dadd_rn(s.ts[p], w_pull(jb, WI, kFieldI, s.cls[p], s.cls[j], o, n_off, gnode(a, c, jb, j)));
-    if (dbits(t) == dbits(s.ts[j])) return false;
-    s.ts[j] = t;
-    return true;
+  const auto step_of = [&](int o) { return (int)(int16_t)s.off[o]; };
+  const auto in_tile = [&](int x, int z) { return x >= R && x < R + a.tx && z >= R && z < R + a.tz; };
+  auto push = [&](unsigned long long ki, int o, int j) {
+    const unsigned long long cand = tree_key(ki, o);
+    if (cand < s.key[j]) atomicMin(&s.key[j], cand);
+  };
+  // levels until none asks for another; step() says whether this thread does
+  int it = 0;
+  auto levels = [&](auto&& step) {
+    for (;; ++it) {
+      const int d = it % 3;
+      if (step()) s_due[d] = 1;
+      if (threadIdx.x == 0) s_due[d == 2 ? 0 : d + 1] = 0;  // read two levels ago
+      __syncthreads();
+      if (!s_due[d]) break;
+    }
+    ++it;
   };
 
-  // pull over the border band (or every node), then seed the source: the
-  // pulled nodes' in-edges as (node, kPullGroup offsets) items over the
-  // block (64-bit LDS atomic min on the key), then each pulled node
-  // re-reads its t*
-  const bool pl = ml >= 0 && pulls(a, c, ml);
-  frontier_add(pl, ml, s.list, &s_cnt[2]);
-  __syncthreads();
-  const int np = s_cnt[2];
-  {
-    const int npg = (n_off + kPullGroup - 1) / kPullGroup;
-    const int total = np * npg;
-    for (int item = threadIdx.x; item < total; item += blockDim.x) {
-      const int j = s.list[item / npg], g = item % npg;
-      unsigned long long best = s.key[j];
+  // this thread's edges (the first kEdges as head << 16 | offset), then the
+  // halo's edges into the tile pushed
+  constexpr int kEdges = 4;
+  int edge[kEdges], n_edge = 0;
 #pragma unroll
-      for (int u = 0; u < kPullGroup; ++u) {
-        const int o = g * kPullGroup + u;
-        if (o >= n_off) break;
-        const int ii = j - s.off[o];
-        if (!((s.om[(o >> 5) * n + ii] >> (o & 31)) & 1u)) continue;
-        const unsigned long long ki = s.key[ii];
-        if (ki == kKeyUnset) continue;
-        const unsigned long long cand = tree_key(ki, o);
-        if (cand < best) best = cand;
-      }
-      if (best < s.key[j]) atomicMin(&s.key[j], best);
+  for (int e = 0; e < kEdges; ++e) edge[e] = ml << 16;  // to itself: lowers nothing
+  for (int w = 0; ml >= 0 && w < nw; ++w)
+    for (uint32_t m = s.om[w * n + ml]; m; m &= m - 1u) {
+      const int o = w * 32 + __ffs(m) - 1, j = ml + step_of(o);
+#pragma unroll
+      for (int e = 0; e < kEdges; ++e)
+        if (n_edge == e) edge[e] = j << 16 | o;
+      ++n_edge;
     }
-  }
-  __syncthreads();
-  unsigned long long last = ml >= 0 ? s.key[ml] : 0ull;  // this thread's node at the last look
-  {
-    bool changed = pl && last != okey;
-    if (pl && fold && refold(ml, last)) changed = true;
-    frontier_add(changed, ml, s.list, &s_cnt[0]);
-  }
-  if (threadIdx.x == 0) {
-    const int sn = seed_node(a, c, pr.src, jb.nx);
-    if (sn >= 0 && s.cls[sn] >= 0) s.list[atomicAdd(&s_cnt[0], 1)] = sn;
-  }
-  __syncthreads();
-
-  // push levels over the tight out-edges of the frontier nodes only
-  int it = 1;
-  int nf = s_cnt[0];
-  const int nt = blockDim.x;
-  while (nf > 0 && it <= kLocalIterCap) {
-    for (int item = threadIdx.x; item < nf * nw; item += nt) {
-      const int f = item / nw, w = item - f * nw;
-      const int i = s.list[f];
-      uint32_t m = s.om[w * n + i];
-      const unsigned long long ki = s.key[i];
-      if (ki == kKeyUnset) continue;
-      raw += __popc(m);
-      while (m) {
+  __syncthreads();  // every thread holds its node's old key
+  for (int q = threadIdx.x; q < n; q += blockDim.x) {
+    int x, z;
+    cell_xz(a, q, &x, &z);
+    const unsigned long long kq = s.key[q];
+    if (in_tile(x, z) || kq == kKeyUnset) continue;
+    for (int w = 0; w < nw; ++w)
+      for (uint32_t m = s.om[w * n + q]; m; m &= m - 1u) {
         const int o = w * 32 + __ffs(m) - 1;
-        m &= m - 1u;
-        const int j = i + s.off[o];
-        const unsigned long long cand = tree_key(ki, o), kj = s.key[j];
-        if (cand < kj) atomicMin(&s.key[j], cand);
-        if (cand < kj || (fold && cand == kj)) s.mark[j] = 1;
+        const int32_t d = s.off[o];
+        if (!in_tile(x + (d >> 24), z + (int)(int8_t)(d >> 16))) continue;
+        ++raw;
+        push(kq, o, q + (int)(int16_t)d);
       }
-    }
-    __syncthreads();
-    // (a halo head may be lowered too: it is neither looked at nor written
-    // back, and the tile that owns it is woken by this tile's border nodes)
-    bool on = false;
-    if (ml >= 0 && s.mark[ml]) {
-      s.mark[ml] = 0;
-      const unsigned long long k = s.key[ml];
-      on = k != last;
+  }
+  __syncthreads();
+
+  unsigned long long last = okey;  // this thread's key at the last look
+  const int sn = seed_node(a, c, pr.src, jb.nx);
+  bool on = ml >= 0 && ml == sn && s.cls[ml] >= 0;
+  levels([&]() -> bool {
+    if (ml < 0) return false;
+    const unsigned long long k = s.key[ml];
+    if (k != last) {
       last = k;
-      if (fold && refold(ml, k)) on = true;
+      on = true;
     }
-    if (threadIdx.x == 0) s_cnt[(it + 1) & 1] = 0;  // read before this level's first barrier
-    frontier_add(on, ml, s.list, &s_cnt[it & 1]);
-    __syncthreads();
-    nf = s_cnt[it & 1];
-    ++it;
+    if (!on) return false;
+    on = false;
+    raw += n_edge;
+    if (n_edge <= kEdges) {
+#pragma unroll
+      for (int e = 0; e < kEdges; ++e)
+        if (e == 0 || __any(n_edge > e)) push(last, edge[e] & 0xffff, edge[e] >> 16);
+    } else {
+      for (int w = 0; w < nw; ++w)
+        for (uint32_t m = s.om[w * n + ml]; m; m &= m - 1u) {
+          const int o = w * 32 + __ffs(m) - 1;
+          push(last, o, ml + step_of(o));
+        }
+    }
+    return true;
+  });
+
+  double ts = ots;
+  if (fold) {
+    // predecessor (-1: none), the weight of its edge, and its t* that ts was
+    // formed with
+    int p = -1;
+    double wi = 0.0;
+    unsigned long long seen = 0ull;
+    bool stale = false;
+    const int o = (int)(last & 0xffffffffull);
+    if (ml >= 0 && last != kKeyUnset && (last >> 32) != 0ull) {
+      p = ml - step_of(o);
+      int x, z;
+      cell_xz(a, p, &x, &z);
+      stale = last != okey || !in_tile(x, z);  // else settled by the last visit
+      if (!stale) seen = dbits(s.ts[p]);
+      wi = w_pull(jb, WI, kFieldI, s.cls[p], s.cls[ml], o, n_off, gnode(a, c, jb, ml));
+    }
+    __syncthreads();  // every thread holds its predecessor's old t*
+    levels([&]() -> bool {
+      if (p < 0) return false;
+      const unsigned long long tp = dbits(s.ts[p]);
+      if (!stale && tp == seen) return false;
+      seen = tp;
+      stale = false;
+      const double t = __dadd_rn(__longlong_as_double((long long)tp), wi);
+      if (dbits(t) == dbits(ts)) return false;
+      ts = t;
+      s.ts[ml] = t;
+      return true;
+    });
   }
 
-  int mask = (nf > 0) ? (1 << 4) : 0;
-  if (ml >= 0) {
-    const bool kc = s.key[ml] != okey;
-    const bool tc = fold && dbits(s.ts[ml]) != dbits(ots);
-    if (kc || tc) {
-      int x, z;
-      cell_xz(a, ml, &x, &z);
-      x -= R;
-      z -= R;
-      const int64_t g = (int64_t)(c.x0 + x) + (int64_t)jb.nx * (c.z0 + z);
-      if (kc) pr.key[g] = s.key[ml];
-      if (tc) pr.tstar[g] = s.ts[ml];
-      const int bb = border_bits(x, z, a.tx, a.tz, R);
-      mask |= bb;
-      if (bb && a.bucket > 0.0) atomicMin(&s_key, dbits((double)(s.key[ml] >> 32)));
-    }
+  // the neighbours to wake first: their flags' atomics then overlap the
+  // field writes (a barrier waits for a workgroup's writes)
+  int mask = 0;
+  const bool kc = ml >= 0 && last != okey;
+  const bool tc = ml >= 0 && fold && dbits(ts) != dbits(ots);
+  int x = 0, z = 0;
+  if (kc || tc) {
+    cell_xz(a, ml, &x, &z);
+    x -= R;
+    z -= R;
+    mask = border_bits(x, z, a.tx, a.tz, R);
+    if (mask && a.bucket > 0.0) atomicMin(&s_key, dbits((double)(last >> 32)));
   }
-  for (int d = 32; d >= 1; d >>= 1) raw += __shfl_xor(raw, d);  // the edges this wavefront pushed
-  if (__lane_id() == 0 && raw) atomicAdd(&stat_slot(a.stats)[3], (unsigned long long)raw);
-  count_visit(a, 1, (long long)np * n_off, it - 1);
   if (mask) atomicOr(&s_mask, mask);
   __syncthreads();
+  const int64_t g = (int64_t)(c.x0 + x) + (int64_t)jb.nx * (c.z0 + z);
+  if (kc) pr.key[g] = last;
+  if (tc) pr.tstar[g] = ts;
   if (threadIdx.x < 64 && s_mask) activate(a, round, c, pr, jb, s_mask, s_key);
+  for (int d = 32; d >= 1; d >>= 1) raw += __shfl_xor(raw, d);  // the edges this wavefront pushed
+  if (__lane_id() == 0 && raw) atomicAdd(&stat_slot(a.stats)[3], (unsigned long long)raw);
+  count_visit(a, 1, 0, it);
 }
 
 // pred_j = j - (the offset its key names); -1 for the source and unreached
@@ -1227,6 +1284,7 @@ __global__ void k_pred(RelaxArgs a) {
 // active-tile list.
 template <int G, int PH>
 __device__ __forceinline__ void visit(const RelaxArgs& a, int round, int T) {
+  T = __builtin_amdgcn_readfirstlane(T);
   if constexpr (PH == 0) relax_tau<G>(a, round, T);
   else relax_tree(a, round, T);
 }
@@ -1320,7 +1378,7 @@ __global__ void __launch_bounds__(kRelaxThreads) k_relax_persist(RelaxArgs a, Pe
     // visits differ in length by tens of levels: tiles are handed out as
     // workgroups free up rather than dealt round-robin
     for (int i = first_item(sh, n_act); i >= 0;) {
-      const int T = lst[i];
+      const int T = __builtin_amdgcn_readfirstlane(lst[i]);
       uint32_t t;
       if constexpr (PH == 0) {
         t = draw_ticket(p.tick, sh, n_act);  // the next entry's, in flight during the visit
@@ -1807,7 +1865,7 @@ static int prepare(const chert_trace_job* jobs, int n_jobs, const chert_trace_op
     a.abort_host = (const int32_t*)at.devicePointer;
   }
   Q->lds[0] = lds_bytes(P.lw, P.lh, P.w_lds_doubles, P.n_off, P.tx, P.tz);
-  Q->lds[1] = tree_lds_bytes(P.lw, P.lh, P.nw, P.n_off, P.tx, P.tz);
+  Q->lds[1] = tree_lds_bytes(P.lw, P.lh, P.nw, P.n_off);
   Q->pa.max_rounds = P.max_rounds;
   Q->pa.bar = (uint32_t*)(ws + P.off_err + 192);
   Q->pa.result = (int32_t*)(ws + P.off_err + 208);
