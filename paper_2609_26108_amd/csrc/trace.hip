@@ -1626,18 +1626,19 @@ static int make_plan(const chert_trace_job* jobs, int n_jobs, const chert_trace_
   return CHERT_OK;
 }
 
-// Rounds go out in groups between host checks of the round counters:
-// 16, then 32, then 64 at a time (a converged phase's extra launches find
-// no active tile and leave at once; each check costs a stream drain).
+// Rounds go out in groups between host checks of the round counters (a
+// converged phase's extra launches find no active tile and leave at once).
 static int run_rounds(hipStream_t s, const RelaxArgs& a, void (*kern)(RelaxArgs, int),
                       const char* name, int grid, size_t lds, int max_rounds,
                       const volatile int32_t* abort_flag, int* rounds) {
-  constexpr int kMaxBatch = 64;
-  int32_t counts[kMaxBatch];
-  int batch = 16;
-  for (int r = 0; r < max_rounds; r += batch, batch = std::min(2 * batch, kMaxBatch)) {
-    int nb = batch;
-    if (r + nb > max_rounds) nb = max_rounds - r;
+  // Rounds launched between two looks at the counts: a look drains the device
+  // (some 15 us), a launch past the last round costs 4 us.  Doubling to 64 ran
+  // 57 rounds too many after 55 useful ones (16 shots, 201,051 nodes: 12.3 ms,
+  // 11.8 so); 8 costs the layered 401 x 201 model 0.07 of 1.92 ms.
+  constexpr int kBatch = 16;
+  int32_t counts[kBatch];
+  for (int r = 0; r < max_rounds; r += kBatch) {
+    const int nb = std::min(kBatch, max_rounds - r);
     for (int q = 0; q < nb; ++q)
       CHERT_LAUNCH(name, kern, dim3((unsigned)grid), dim3((unsigned)tile_threads(a.tx, a.tz)), lds,
                    s, a, r + q);
@@ -1912,7 +1913,7 @@ static int prepare(const chert_trace_job* jobs, int n_jobs, const chert_trace_op
 
 // Enqueue every kernel of a prepared batch on s.  With the persistent
 // launch nothing here waits for the device, so the sequence can be captured
-// into a graph; the per-round launch synchronises s every 8 rounds to test
+// into a graph; the per-round launch synchronises s every 16 rounds to test
 // for termination.
 static int enqueue(const Prepared& Q, const chert_trace_job* jobs, int n_jobs,
                    const chert_trace_opts* o, hipStream_t s, int rounds[3]) {
