@@ -979,6 +979,7 @@ k_warm_window(WarmArgs w, int64_t n_jobs) {
 // steps.  A chain of some 45 evaluations of the nested solve in one lane set
 // the duration of the kernels that use it.
 constexpr int kBisectLanes = 16;
+template <bool LIT>
 __device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int kernel,
                                                   double psi_star, const Bracket& b, int iters,
                                                   double* xo, double* yo) {
@@ -998,8 +999,8 @@ __device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int
     if (node < kBisectLanes) {
       double thI, sr, cr;
       sincos(0.5 * (l + h), &sr, &cr);
-      ok = theta_imag_sc(m, mode, kernel, sr, cr, &thI);
-      if (ok) right = (wrap_pi(ray_angle_sc(m, mode, kernel, sr, cr, thI) - psi_star) < 0.0) == neg_lo;
+      ok = theta_imag_sc<LIT>(m, mode, kernel, sr, cr, &thI);
+      if (ok) right = (wrap_pi(ray_angle_sc<LIT>(m, mode, kernel, sr, cr, thI) - psi_star) < 0.0) == neg_lo;
     }
     const uint32_t oks = (uint32_t)(__ballot(ok) >> base), rights = (uint32_t)(__ballot(right) >> base);
     for (int id = 1; id < kBisectLanes && it < iters && hi - lo > 1e-14; ++it) {
@@ -1013,7 +1014,7 @@ __device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int
   }
   const double x = 0.5 * (lo + hi);
   double y;
-  if (!theta_imag(m, mode, kernel, x, &y)) return false;
+  if (!theta_imag<LIT>(m, mode, kernel, x, &y)) return false;
   *xo = x;
   *yo = y;
   return true;
@@ -1023,7 +1024,7 @@ __device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int
 // calls it): kBisectLanes lanes each, 64 / kBisectLanes at a time.  job(src)
 // gives the medium and mode of lane src's bracket.  True where the lane's own
 // bracket got its root.
-template <class Job>
+template <bool LIT, class Job>
 __device__ __forceinline__ bool bisect_roots(const SolveParams& a, bool need, const Bracket& br,
                                              double psi_star, double* x, double* y, Job job) {
   constexpr int kGroups = 64 / kBisectLanes;
@@ -1042,7 +1043,7 @@ __device__ __forceinline__ bool bisect_roots(const SolveParams& a, bool need, co
     const Medium m = job(src, &mode);
     double xs = 0.0, ys = 0.0;
     int ok = 0;
-    if (rest) ok = bisect_root_lanes(m, mode, a.kernel, psi, b, a.bisect_iters, &xs, &ys) ? 1 : 0;
+    if (rest) ok = bisect_root_lanes<LIT>(m, mode, a.kernel, psi, b, a.bisect_iters, &xs, &ys) ? 1 : 0;
     const int from = rank >= 0 && rank < kGroups ? rank * kBisectLanes : lane;
     ok = __shfl(ok, from);
     xs = __shfl(xs, from);
@@ -1102,16 +1103,23 @@ k_warm_fold(WarmArgs w) {
           ok = bracket_newton(a, m, mode, br, wb.sa.x, wb.sb.x, psi_star, el, &x, &y);
         }
         const int k32 = (int)k, md32 = mode;
-        if (bisect_roots(a, has && !ok, br, psi_star, &x, &y, [&](int src, int* md) {
-              *md = __shfl(md32, src);
-              return load_medium(a.classes[__shfl(k32, src)]);
-            }))
-          ok = true;
+        const auto job_of = [&](int src, int* md) {
+          *md = __shfl(md32, src);
+          return load_medium(a.classes[__shfl(k32, src)]);
+        };
+        if (bisect_roots<false>(a, has && !ok, br, psi_star, &x, &y, job_of)) ok = true;
+        SolveCand& sc = s_c[dl][i * kFoldLanes + q];
+        bool again = false;
         if (has) {
-          SolveCand& sc = s_c[dl][i * kFoldLanes + q];
           bool ill = false;
           if (ok) bracket_entry(a, m, mode, br, psi_star, el, x, y, &sc.e, &ill);
           sc.ok = ok ? 1 : 0;
+          sc.ill = ill ? 1 : 0;
+          again = ok && loss_cancelled(m, mode, el, sc.e);
+        }
+        if (bisect_roots<true>(a, again, br, psi_star, &x, &y, job_of)) {
+          bool ill = false;
+          bracket_entry(a, m, mode, br, psi_star, el, x, y, &sc.e, &ill);
           sc.ill = ill ? 1 : 0;
         }
       }

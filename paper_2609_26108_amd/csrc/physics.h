@@ -385,19 +385,23 @@ __device__ __forceinline__ NewtonSys newton_sys(const Medium& m, int mode, int k
 }
 
 // sign and zeros of the homogeneity residual (eq 9) at theta_R with
-// sine/cosine (sr, cr) and theta_I with (sh, ch)
+// sine/cosine (sr, cr) and theta_I with (sh, ch).  LIT: the residual itself
+// (literal normalised velocities; see bisect_root)
+template <bool LIT = false>
 __device__ __forceinline__ double h_sign(const Medium& m, int mode, int kernel, double sr,
                                          double cr, double sh, double ch) {
+  if constexpr (LIT) return homog_residual(energy_velocity_t(m, mode, kernel, Trig{sr, cr, sh, ch}));
   const Raw r = energy_raw(m, mode, kernel, Trig{sr, cr, sh, ch});
   return r.w1.re * r.w3.im - r.w3.re * r.w1.im;
 }
 
 // the outward scan's values at +-(k + 1) kThiStep (sinh is odd, cosh even)
+template <bool LIT = false>
 __device__ __forceinline__ void h_scan_pair(const Medium& m, int mode, int kernel, double sr,
                                             double cr, int k, double* hp, double* hn) {
   const double sb = kScan.sh[k], cb = kScan.ch[k];
-  *hp = h_sign(m, mode, kernel, sr, cr, sb, cb);
-  *hn = h_sign(m, mode, kernel, sr, cr, -sb, cb);
+  *hp = h_sign<LIT>(m, mode, kernel, sr, cr, sb, cb);
+  *hn = h_sign<LIT>(m, mode, kernel, sr, cr, -sb, cb);
 }
 
 __device__ __forceinline__ bool brackets(double fa, double fb) {
@@ -405,11 +409,12 @@ __device__ __forceinline__ bool brackets(double fa, double fb) {
   return (fa < 0.0) != (fb < 0.0);
 }
 
+template <bool LIT = false>
 __device__ __forceinline__ double h_at_thi(const Medium& m, int mode, int kernel, double sr,
                                            double cr, double y) {
   double sh, ch;
   sinh_cosh(y, &sh, &ch);
-  return h_sign(m, mode, kernel, sr, cr, sh, ch);
+  return h_sign<LIT>(m, mode, kernel, sr, cr, sh, ch);
 }
 
 // root of the parabola through (a, fa), (b, fb), (e, fe) nearest the secant
@@ -430,39 +435,42 @@ __device__ __forceinline__ double parabola_root(double a, double b, double e, do
 // (sr, cr) sine and cosine of thR.  Two interpolation steps leave an error of
 // ~1e-12 and 1e-19 rad on the smooth residual (bracket 4.4e-3 rad), so a
 // secant through them ends the search after two evaluations; where the last
-// step is not small yet, Illinois (modified regula falsi) on the bracket held
-// so far.
+// step is not small yet (LIT: at once), Illinois (modified regula falsi) on the
+// bracket held so far.
 constexpr double kThiStepDone = 1e-10;
+template <bool LIT = false>
 __device__ __forceinline__ double refine_thi(const Medium& m, int mode, int kernel, double sr,
                                              double cr, double a, double b, double fa,
                                              double fb, double e, double fe) {
-  const double y0 = parabola_root(a, b, e, fa, fb, fe);
-  const double f0 = h_at_thi(m, mode, kernel, sr, cr, y0);
-  if (f0 == 0.0) return y0;
-  double xe, fxe;  // the bracket end that y0 replaces stays as the third point
-  if ((f0 < 0.0) == (fa < 0.0)) {
-    xe = a; fxe = fa; a = y0; fa = f0;
-  } else {
-    xe = b; fxe = fb; b = y0; fb = f0;
+  if constexpr (!LIT) {
+    const double y0 = parabola_root(a, b, e, fa, fb, fe);
+    const double f0 = h_at_thi<LIT>(m, mode, kernel, sr, cr, y0);
+    if (f0 == 0.0) return y0;
+    double xe, fxe;  // the bracket end that y0 replaces stays as the third point
+    if ((f0 < 0.0) == (fa < 0.0)) {
+      xe = a; fxe = fa; a = y0; fa = f0;
+    } else {
+      xe = b; fxe = fb; b = y0; fb = f0;
+    }
+    const double y1 = parabola_root(a, b, xe, fa, fb, fxe);
+    const double f1 = h_at_thi<LIT>(m, mode, kernel, sr, cr, y1);
+    if (f1 == 0.0) return y1;
+    const double y2 = y1 - f1 * (y1 - y0) / (f1 - f0);
+    if ((f1 < 0.0) == (fa < 0.0)) {
+      a = y1; fa = f1;
+    } else {
+      b = y1; fb = f1;
+    }
+    // (where y1 is already the root to rounding, y2 may leave the bracket by
+    // an ulp)
+    if (fabs(y2 - y1) <= kThiStepDone && fabs(y1 - y0) <= 1e-4) return y2;
   }
-  const double y1 = parabola_root(a, b, xe, fa, fb, fxe);
-  const double f1 = h_at_thi(m, mode, kernel, sr, cr, y1);
-  if (f1 == 0.0) return y1;
-  const double y2 = y1 - f1 * (y1 - y0) / (f1 - f0);
-  if ((f1 < 0.0) == (fa < 0.0)) {
-    a = y1; fa = f1;
-  } else {
-    b = y1; fb = f1;
-  }
-  // (where y1 is already the root to rounding, y2 may leave the bracket by
-  // an ulp)
-  if (fabs(y2 - y1) <= kThiStepDone && fabs(y1 - y0) <= 1e-4) return y2;
   int side = 0;
   double c = 0.5 * (a + b);
   for (int it = 0; it < 80; ++it) {
     double cn = (a * fb - b * fa) / (fb - fa);
     if (!(cn > fmin(a, b) && cn < fmax(a, b))) cn = 0.5 * (a + b);
-    const double fc = h_at_thi(m, mode, kernel, sr, cr, cn);
+    const double fc = h_at_thi<LIT>(m, mode, kernel, sr, cr, cn);
     double step = fabs(cn - c);
     c = cn;
     if (fc == 0.0) break;
@@ -487,13 +495,14 @@ __device__ __forceinline__ double refine_thi(const Medium& m, int mode, int kern
 // Written for wavefront lockstep: every lane first scans until the whole
 // wavefront has its bracket, then all lanes refine together, whichever side
 // their bracket is on.  (sr, cr) = sine and cosine of thR.
+template <bool LIT = false>
 __device__ __forceinline__ bool theta_imag_sc(const Medium& m, int mode, int kernel, double sr,
                                               double cr, double* thI) {
   if (theta_i_zero(m, mode)) {
     *thI = 0.0;
     return true;
   }
-  const double h0 = h_sign(m, mode, kernel, sr, cr, 0.0, 1.0);
+  const double h0 = h_sign<LIT>(m, mode, kernel, sr, cr, 0.0, 1.0);
   bool done = (h0 == 0.0);
   bool bp = false, bn = false;
   int kb = 0;  // the bracket is [kb, kb + 1] steps out
@@ -505,7 +514,7 @@ __device__ __forceinline__ bool theta_imag_sc(const Medium& m, int mode, int ker
       p1 = p2;
       n0 = n1;
       n1 = n2;
-      h_scan_pair(m, mode, kernel, sr, cr, k, &p2, &n2);
+      h_scan_pair<LIT>(m, mode, kernel, sr, cr, k, &p2, &n2);
       if (k == 0) {
         p0 = n2;
         n0 = p2;
@@ -523,10 +532,10 @@ __device__ __forceinline__ bool theta_imag_sc(const Medium& m, int mode, int ker
   }
   if (!bp && !bn) return false;
   const double s = bp ? 1.0 : -1.0;
-  double r = refine_thi(m, mode, kernel, sr, cr, s * (kb * kThiStep), s * ((kb + 1) * kThiStep),
+  double r = refine_thi<LIT>(m, mode, kernel, sr, cr, s * (kb * kThiStep), s * ((kb + 1) * kThiStep),
                         bp ? p1 : n1, bp ? p2 : n2, s * ((kb - 1) * kThiStep), bp ? p0 : n0);
   if (bp && bn) {  // a bracket on each side: the root nearer 0, the positive one on a tie
-    const double rn = refine_thi(m, mode, kernel, sr, cr, -(kb * kThiStep),
+    const double rn = refine_thi<LIT>(m, mode, kernel, sr, cr, -(kb * kThiStep),
                                  -((kb + 1) * kThiStep), n1, n2, -((kb - 1) * kThiStep), n0);
     if (fabs(rn) < fabs(r)) r = rn;
   }
@@ -534,18 +543,21 @@ __device__ __forceinline__ bool theta_imag_sc(const Medium& m, int mode, int ker
   return true;
 }
 
+template <bool LIT = false>
 __device__ __forceinline__ bool theta_imag(const Medium& m, int mode, int kernel, double thR,
                                            double* thI) {
   double sr, cr;
   sincos(thR, &sr, &cr);
-  return theta_imag_sc(m, mode, kernel, sr, cr, thI);
+  return theta_imag_sc<LIT>(m, mode, kernel, sr, cr, thI);
 }
 
 // ray angle at (thR, thI) given sin, cos of thR
+template <bool LIT = false>
 __device__ __forceinline__ double ray_angle_sc(const Medium& m, int mode, int kernel, double sr,
                                                double cr, double thI) {
   double sh, ch;
   sinh_cosh(thI, &sh, &ch);
+  if constexpr (LIT) return ray_angle(energy_velocity_t(m, mode, kernel, Trig{sr, cr, sh, ch}));
   const Raw r = energy_raw(m, mode, kernel, Trig{sr, cr, sh, ch});
   const cd D = conjg(kernel == CHERT_KERNEL_OEV ? csqrt_p(r.G) * r.N : csqrt_p(r.G));
   return atan2((r.w1 * D).re, (r.w3 * D).re);

@@ -76,7 +76,10 @@ __device__ __forceinline__ bool newton_root(const Medium& m, int mode, int kerne
 }
 
 // Fallback: nested bisection on theta_R with the inner theta_I solve at every
-// trial point (slow, used only when Newton does not settle).
+// trial point (slow, used only when Newton does not settle or the entry's
+// attenuation cancels).  LIT: the definition in its literal operations --
+// normalised velocities and residuals, regula falsi -- at twice the cost.
+template <bool LIT>
 __device__ __forceinline__ bool bisect_root(const Medium& m, int mode, int kernel,
                                          double psi_star, double ta, double tb, double fa,
                                          int iters, double* xo, double* yo) {
@@ -86,14 +89,14 @@ __device__ __forceinline__ bool bisect_root(const Medium& m, int mode, int kerne
     double mid = 0.5 * (lo + hi);
     double thI, sr, cr;
     sincos(mid, &sr, &cr);
-    if (!theta_imag_sc(m, mode, kernel, sr, cr, &thI)) return false;
-    double fm = wrap_pi(ray_angle_sc(m, mode, kernel, sr, cr, thI) - psi_star);
+    if (!theta_imag_sc<LIT>(m, mode, kernel, sr, cr, &thI)) return false;
+    double fm = wrap_pi(ray_angle_sc<LIT>(m, mode, kernel, sr, cr, thI) - psi_star);
     if ((fm < 0.0) == neg_lo) lo = mid;
     else hi = mid;
   }
   double x = 0.5 * (lo + hi);
   double y;
-  if (!theta_imag(m, mode, kernel, x, &y)) return false;
+  if (!theta_imag<LIT>(m, mode, kernel, x, &y)) return false;
   *xo = x;
   *yo = y;
   return true;
@@ -323,6 +326,21 @@ __device__ __forceinline__ void bracket_entry(const SolveParams& a, const Medium
   *ill = fabs((b.fb - b.fa) / (b.tb - b.ta)) < kIllSlope;
 }
 
+// Has the attenuation of an entry cancelled to under a thousandth of the
+// medium's loss?  (The OEV maps pass through zero next to their branch
+// changes; MEV's do not.)  The angles' last bit then moves A by 1e-10 of
+// itself, so which of the neighbouring 64-bit angles is stored decides its
+// last six digits: they are the literal bisection's, not those a faster
+// iteration happens to end on.
+__device__ __forceinline__ bool loss_cancelled(const Medium& m, int mode, bool el,
+                                               const Entry& e) {
+  const double l44 = fabs(m.a44.im) / m.a44.re;
+  const double loss = mode == CHERT_QSH ? fmax(l44, fabs(m.a66.im) / m.a66.re)
+                                        : fmax(l44, fmax(fabs(m.a11.im) / m.a11.re,
+                                                         fabs(m.a33.im) / m.a33.re));
+  return !el && fabs(e.A) * e.V < 1e-3 * loss;
+}
+
 // The root of the bracket at sweep sample j and its ray quantities; false if
 // neither the Newton step nor the bisection converges.
 __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium& m, int mode,
@@ -331,9 +349,12 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
   const Bracket b = bracket_at(a, j, sa, sb, psi_star);
   double x, y;
   if (!bracket_newton(a, m, mode, b, sa.x, sb.x, psi_star, el, &x, &y) &&
-      !bisect_root(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
+      !bisect_root<false>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
     return false;
   bracket_entry(a, m, mode, b, psi_star, el, x, y, cand, cand_ill);
+  if (loss_cancelled(m, mode, el, *cand) &&
+      bisect_root<true>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
+    bracket_entry(a, m, mode, b, psi_star, el, x, y, cand, cand_ill);
   return true;
 }
 
