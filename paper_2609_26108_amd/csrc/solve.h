@@ -327,16 +327,16 @@ __device__ __forceinline__ void bracket_entry(const SolveParams& a, const Medium
 }
 
 // Has the attenuation of an entry cancelled to under a thousandth of the
-// medium's loss?  (The OEV maps pass through zero next to their branch
-// changes; MEV's do not.)  The angles' last bit then moves A by 1e-10 of
+// least of the mode's losses?  (The OEV maps pass through zero next to their
+// branch changes; MEV's do not.)  The angles' last bit then moves A by 1e-10 of
 // itself, so which of the neighbouring 64-bit angles is stored decides its
 // last six digits: they are the literal bisection's, not those a faster
 // iteration happens to end on.
 __device__ __forceinline__ bool loss_cancelled(const Medium& m, int mode, bool el,
                                                const Entry& e) {
   const double l44 = fabs(m.a44.im) / m.a44.re;
-  const double loss = mode == CHERT_QSH ? fmax(l44, fabs(m.a66.im) / m.a66.re)
-                                        : fmax(l44, fmax(fabs(m.a11.im) / m.a11.re,
+  const double loss = mode == CHERT_QSH ? fmin(l44, fabs(m.a66.im) / m.a66.re)
+                                        : fmin(l44, fmin(fabs(m.a11.im) / m.a11.re,
                                                          fabs(m.a33.im) / m.a33.re));
   return !el && fabs(e.A) * e.V < 1e-3 * loss;
 }
