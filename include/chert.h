@@ -316,8 +316,8 @@ typedef struct chert_trace_stats {
 /* How the relaxation rounds are launched (the fields are the same either
  * way: the fixed point does not depend on the schedule):
  *   PER_ROUND   one launch per round over every tile; the host checks for
- *               termination after 16, then every 32, then every 64 rounds
- *               (launches past convergence find no active tile);
+ *               termination after every 16 rounds (launches past convergence
+ *               find no active tile);
  *   PERSISTENT  one launch per phase: an occupancy-sized grid walks each
  *               round's active tiles, rounds separated by a device-wide
  *               barrier (bounded wait: a stalled barrier fails the call with
@@ -361,8 +361,10 @@ typedef struct chert_trace_opts {
                          the hop count with the width in hops) is visited
                          only once k <= its problem's smallest pending key
                          + width; otherwise it stays active for a later
-                         round (2D tiles; the 3D tiles have no
-                         ordering).  The fields do not depend on it.      */
+                         round (2D tiles; 3D tiles order batches of more
+                         tiles than twice the resident workgroups by
+                         themselves, unless max_rounds is given).  The
+                         fields do not depend on it.                      */
   chert_trace_stats *stats_host; /* nullable: filled when the call returns */
   const volatile int32_t *abort_flag_host; /* nullable caller-owned word in
                          pinned host memory (hipHostMalloc).  While it is

@@ -657,8 +657,8 @@ enum { kWUniform = 0, kWLds = 1, kWGlobal = 2, kWNode = 3 };
 // kWUniform: one class in the whole box, so a thread's G weights stay in
 // registers and an edge reads the head's value only.
 // Traveltime phase per call: 401 x 201 nodes, 5 classes, 6 fields 1.77 -> 1.12
-// ms; 801 x 251 per-node shots (32 fields) 12.4 -> 6.6 ms; whole calls 3.63 ->
-// 2.31 and 21.4 -> 13.3 ms with the tree phase's levels done the same way.
+// ms; 801 x 251 per-node shots (32 fields) 12.4 -> 6.6 ms.  (Tried: each
+// wavefront's lowered nodes its own frontier, one barrier a level: no gain.)
 template <int G, int SRC>
 __device__ __forceinline__ int push_levels(const RelaxArgs& a, const TileCtx& c, const JobDev& jb,
                                            int field, const Smem& s, const double* Wg, int k0,
