@@ -282,7 +282,9 @@ __device__ __forceinline__ Raw energy_raw(const Medium& m, int mode, int kernel,
 // One Newton system of the local solve: unknowns (theta_R, theta_I) = (x, y),
 // equations h = 0 (eq 9) and ray angle = psi*, both up to positive factors.
 //   f1 = Im(conj(U1) U3), f2 = sin(miss) cos(miss) |Re U|^2, U = w conj(D)
-// (a positive multiple of v).  Everything but the MEV products Re(g_j
+// (a positive multiple of v).  f2 also vanishes where the ray is reversed or
+// perpendicular to the target; `near` tells the target's own zero from those.
+// Everything but the MEV products Re(g_j
 // conj g_k) is analytic in z = x + i y, so one complex derivative gives both
 // columns (d/dy = i d/dz): about the cost of one evaluation more instead of
 // the two of difference quotients, and the iteration is truly quadratic.
@@ -290,6 +292,7 @@ struct NewtonSys {
   double f1, f2;
   double a11, a12, a21, a22;  // rows of f1 and f2
   double r2;                  // |Re U|^2: d psi / dx = a21 / r2
+  bool near;                  // |miss| < pi / 4
 };
 
 __device__ __forceinline__ cd times_i(cd a) { return cd{-a.im, a.re}; }
@@ -381,6 +384,7 @@ __device__ __forceinline__ NewtonSys newton_sys(const Medium& m, int mode, int k
   o.a21 = (U1x.re * cp - U3x.re * sp) * dt - cr * (U3x.re * cp + U1x.re * sp);
   o.a22 = (U1y.re * cp - U3y.re * sp) * dt - cr * (U3y.re * cp + U1y.re * sp);
   o.r2 = cr * cr + dt * dt;
+  o.near = fabs(cr) < dt;
   return o;
 }
 

@@ -28,8 +28,10 @@ constexpr double kNewtonDone = 1e-10;
 
 // One Newton step of (h, ray angle - psi*) at (x, y); (sp, cp) = sine and
 // cosine of psi*.  `el`: theta_I stays 0 and only the direction equation is
-// solved.  *slope: d psi / d theta_R along h = 0 (`el`: along y = 0).
-__device__ __forceinline__ void newton_step(const Medium& m, int mode, int kernel, bool el,
+// solved.  *slope: d psi / d theta_R along h = 0 (`el`: along y = 0).  False
+// where the ray at (x, y) is more than pi / 4 from the target: an iteration
+// that settles there has found the target's reverse or its perpendicular.
+__device__ __forceinline__ bool newton_step(const Medium& m, int mode, int kernel, bool el,
                                             double x, double y, double sp, double cp, double* dx,
                                             double* dy, double* slope) {
   const NewtonSys q = newton_sys(m, mode, kernel, trig_of(x, y), sp, cp);
@@ -37,17 +39,19 @@ __device__ __forceinline__ void newton_step(const Medium& m, int mode, int kerne
     *dx = -q.f2 / q.a21;
     *dy = 0.0;
     *slope = q.a21 / q.r2;
-    return;
+    return q.near;
   }
   const double det = q.a11 * q.a22 - q.a12 * q.a21;
   const double inv = 1.0 / det;
   *dx = -(q.a22 * q.f1 - q.a12 * q.f2) * inv;
   *dy = -(q.a11 * q.f2 - q.a21 * q.f1) * inv;
   *slope = -det / (q.a12 * q.r2);
+  return q.near;
 }
 
-// Newton on F = (h, psi - psi*) from the bracket interpolant.  Elastic modes
-// keep theta_I = 0 exactly and solve the 1D direction equation.
+// Newton on newton_sys's equations from the bracket interpolant; only the
+// target's own direction is accepted.  Elastic modes keep theta_I = 0 exactly
+// and solve the 1D direction equation.
 __device__ __forceinline__ bool newton_root(const Medium& m, int mode, int kernel,
                                          double psi_star, double ta, double tb,
                                          double ya, double yb, double fa, double fb,
@@ -59,9 +63,10 @@ __device__ __forceinline__ bool newton_root(const Medium& m, int mode, int kerne
   double y = el ? 0.0 : ya + t * (yb - ya);
   double last = 1.0, sp, cp;
   sincos(psi_star, &sp, &cp);
+  bool near = false;
   for (int it = 0; it < iters; ++it) {
     double dx, dy, slope;
-    newton_step(m, mode, kernel, el, x, y, sp, cp, &dx, &dy, &slope);
+    near = newton_step(m, mode, kernel, el, x, y, sp, cp, &dx, &dy, &slope);
     if (!isfinite(dx) || !isfinite(dy)) return false;
     x += dx;
     y += dy;
@@ -69,7 +74,7 @@ __device__ __forceinline__ bool newton_root(const Medium& m, int mode, int kerne
     last = fmax(fabs(dx), fabs(dy));
     if (last < kNewtonDone) break;
   }
-  if (!(last < kNewtonDone)) return false;
+  if (!(last < kNewtonDone) || !near) return false;
   *xo = x;
   *yo = y;
   return true;
@@ -430,7 +435,7 @@ __device__ __forceinline__ int32_t solve_dir(const SolveParams& a, const Medium&
   return solve_status(found, ill, *best);
 }
 
-// Newton on F = (h, psi - psi*) from (x0, y0), as newton_root but started
+// Newton on the same equations from (x0, y0), as newton_root but started
 // from a prediction and kept within kWarmWindow of it; *slope is
 // d psi / d theta_R along the homogeneous curve h = 0 at the last iterate.
 __device__ __forceinline__ bool warm_newton(const Medium& m, int mode, int kernel, bool el,
@@ -438,9 +443,10 @@ __device__ __forceinline__ bool warm_newton(const Medium& m, int mode, int kerne
                                          double* yo, double* slope) {
   double x = x0, y = el ? 0.0 : y0, last = 1.0, sl = NAN, sp, cp;
   sincos(psi_star, &sp, &cp);
+  bool near = false;
   for (int it = 0; it < 16; ++it) {
     double dx, dy;
-    newton_step(m, mode, kernel, el, x, y, sp, cp, &dx, &dy, &sl);
+    near = newton_step(m, mode, kernel, el, x, y, sp, cp, &dx, &dy, &sl);
     if (!isfinite(dx) || !isfinite(dy)) return false;
     x += dx;
     y += dy;
@@ -448,7 +454,7 @@ __device__ __forceinline__ bool warm_newton(const Medium& m, int mode, int kerne
     last = fmax(fabs(dx), fabs(dy));
     if (last < kNewtonDone) break;
   }
-  if (!(last < kNewtonDone)) return false;
+  if (!(last < kNewtonDone) || !near) return false;
   *xo = x;
   *yo = y;
   *slope = sl;

@@ -1,0 +1,52 @@
+"""The local solve's headers on the host (host_solve.cpp): what the bracket
+refinement accepts, where coarse sweeps and iteration caps leave it little to
+go by."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2609_26108_amd")
+
+# a strongly attenuating layer-like medium and a strongly anisotropic one, both
+# with sweep intervals of 22.5 degrees that span more than a right angle of ray
+# directions (qSV, opposite-end velocity)
+COARSE = np.array([
+    [5907509.213320775, 2918469.166620558, 5341460.524536856, 1631421.5936059605,
+     2060605.3945572022, 12.941943652162367, 2.9667210365482743, 8.509536873357579,
+     3.948429015215527, 5.893121311447293, 2300.0, -0.17949259425881514, 0.0],
+    [4102158.950271772, 1775638.28687719, 1090284.6187087786, 46382.89533621889,
+     36164.636058535085, 906.4433285547342, 14.095390222235016, 153.98735066119715,
+     647.9902803100911, 48.10317854220429, 2300.0, 0.0010491099580471897, 0.0]])
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host_solve") / "host_solve")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-ffp-contract=off",
+                    "-I", os.path.join(PKG, "opcount"), "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(PKG, "csrc"),
+                    os.path.join(ROOT, "tests", "host_solve.cpp"), "-o", exe, "-lm"],
+                   check=True, capture_output=True, text=True)
+
+    def run(classes, mode, kernel, n_sweep=1440, n_dirs=360, newton=12, bisect=200):
+        text = "\n".join(" ".join(repr(float(x)) for x in r) for r in classes) + "\n"
+        out = subprocess.run([exe] + [str(x) for x in (mode, kernel, n_sweep, n_dirs, newton, bisect)],
+                             input=text, check=True, capture_output=True, text=True).stdout
+        return np.array([[float(x) for x in line.split()] for line in out.splitlines()])
+    return run
+
+
+@pytest.mark.parametrize("kernel", [0, 1])
+@pytest.mark.parametrize("n_sweep", [16, 17, 20, 90])
+def test_newton_keeps_only_the_targets_own_direction(host, n_sweep, kernel):
+    """The iteration's direction equation also vanishes at the reverse of the
+    target and at right angles to it; a bracket that holds such a zero goes to
+    the bisection.  An accepted root's ray is the target's to far below any
+    residual bound (1e-6 rad against the last step's 1e-10)."""
+    b = host(COARSE, 1, kernel, n_sweep=n_sweep)
+    ok = b[:, 2] == 1
+    assert ok.any()
+    assert b[ok, 3].max() < 1e-6
