@@ -989,7 +989,7 @@ __device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int
   double lo = b.ta, hi = b.tb;
   const bool neg_lo = b.fa < 0.0;
   int it = 0;
-  while (it < iters && hi - lo > 1e-14) {
+  while (it < iters && hi - lo > kBisectStop) {
     double l = lo, h = hi;
     for (int q = depth - 1; q >= 0; --q) {
       const double mid = 0.5 * (l + h);
@@ -1004,7 +1004,7 @@ __device__ __forceinline__ bool bisect_root_lanes(const Medium& m, int mode, int
       if (ok) right = (wrap_pi(ray_angle_sc<LIT>(m, mode, kernel, sr, cr, thI) - psi_star) < 0.0) == neg_lo;
     }
     const uint32_t oks = (uint32_t)(__ballot(ok) >> base), rights = (uint32_t)(__ballot(right) >> base);
-    for (int id = 1; id < kBisectLanes && it < iters && hi - lo > 1e-14; ++it) {
+    for (int id = 1; id < kBisectLanes && it < iters && hi - lo > kBisectStop; ++it) {
       if (!((oks >> (id - 1)) & 1u)) return false;
       const double mid = 0.5 * (lo + hi);
       const int r = (rights >> (id - 1)) & 1u;
@@ -1116,12 +1116,13 @@ k_warm_fold(WarmArgs w) {
           if (ok) bracket_entry(a, m, mode, br, psi_star, el, x, y, &sc.e, &ill);
           sc.ok = ok ? 1 : 0;
           sc.ill = ill ? 1 : 0;
-          again = ok && loss_cancelled(m, mode, el, sc.e);
+          again = ok && loss_cancelled(m, mode, el, sc.e) && bisection_completes(a, br);
         }
         if (bisect_roots<true>(a, again, br, psi_star, &x, &y, job_of)) {
+          Entry lit;
           bool ill = false;
-          bracket_entry(a, m, mode, br, psi_star, el, x, y, &sc.e, &ill);
-          sc.ill = ill ? 1 : 0;
+          bracket_entry(a, m, mode, br, psi_star, el, x, y, &lit, &ill);
+          if (keep_literal(a, lit, sc.e)) sc.e = lit;
         }
       }
       __syncthreads();

@@ -26,6 +26,8 @@ constexpr double kWarmWindow = 0.35;  // the polish may move theta_R this far [r
 // rounding of the equations
 constexpr double kNewtonDone = 1e-10;
 
+constexpr double kBisectStop = 1e-14;  // the bisection's last interval [rad]
+
 // One Newton step of (h, ray angle - psi*) at (x, y); (sp, cp) = sine and
 // cosine of psi*.  `el`: theta_I stays 0 and only the direction equation is
 // solved.  *slope: d psi / d theta_R along h = 0 (`el`: along y = 0).  False
@@ -90,7 +92,7 @@ __device__ __forceinline__ bool bisect_root(const Medium& m, int mode, int kerne
                                          int iters, double* xo, double* yo) {
   double lo = ta, hi = tb;
   bool neg_lo = fa < 0.0;
-  for (int it = 0; it < iters && hi - lo > 1e-14; ++it) {
+  for (int it = 0; it < iters && hi - lo > kBisectStop; ++it) {
     double mid = 0.5 * (lo + hi);
     double thI, sr, cr;
     sincos(mid, &sr, &cr);
@@ -346,6 +348,20 @@ __device__ __forceinline__ bool loss_cancelled(const Medium& m, int mode, bool e
   return !el && fabs(e.A) * e.V < 1e-3 * loss;
 }
 
+// Can the bisection of bracket b reach its stop within the halvings that the
+// caller allows?  A converged Newton root is not given up for fewer.
+__device__ __forceinline__ bool bisection_completes(const SolveParams& a, const Bracket& b) {
+  const long long steps = 1ll << (a.bisect_iters < 62 ? a.bisect_iters : 62);
+  return b.tb - b.ta <= kBisectStop * (double)steps;
+}
+
+// Is `lit`, the literal bisection's entry, to replace `e`?  Not where the
+// bisection has closed on a jump of the ray-angle map and `e` is a root.
+__device__ __forceinline__ bool keep_literal(const SolveParams& a, const Entry& lit,
+                                             const Entry& e) {
+  return lit.res <= a.resid_tol || !(e.res <= a.resid_tol);
+}
+
 // The root of the bracket at sweep sample j and its ray quantities; false if
 // neither the Newton step nor the bisection converges.
 __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium& m, int mode,
@@ -357,9 +373,12 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
       !bisect_root<false>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
     return false;
   bracket_entry(a, m, mode, b, psi_star, el, x, y, cand, cand_ill);
-  if (loss_cancelled(m, mode, el, *cand) &&
-      bisect_root<true>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
-    bracket_entry(a, m, mode, b, psi_star, el, x, y, cand, cand_ill);
+  if (loss_cancelled(m, mode, el, *cand) && bisection_completes(a, b) &&
+      bisect_root<true>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y)) {
+    Entry lit;
+    bracket_entry(a, m, mode, b, psi_star, el, x, y, &lit, cand_ill);
+    if (keep_literal(a, lit, *cand)) *cand = lit;
+  }
   return true;
 }
 

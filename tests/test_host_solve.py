@@ -50,3 +50,30 @@ def test_newton_keeps_only_the_targets_own_direction(host, n_sweep, kernel):
     ok = b[:, 2] == 1
     assert ok.any()
     assert b[ok, 3].max() < 1e-6
+
+
+def layer_classes(n, seed):
+    """Thomsen media in the ranges of the layered models, a quality factor per modulus."""
+    rng = np.random.default_rng(seed)
+    rows = []
+    for _ in range(n):
+        vp = rng.uniform(2000.0, 4500.0)
+        a33, a44 = vp * vp, (vp / rng.uniform(1.6, 2.0)) ** 2
+        delta = rng.uniform(-0.1, 0.2)
+        a13 = np.sqrt((a33 - a44) * (a33 - a44 + 2.0 * delta * a33)) - a44
+        rows.append([a33 * (1.0 + 2.0 * rng.uniform(0.0, 0.3)), a13, a33, a44,
+                     a44 * (1.0 + 2.0 * rng.uniform(0.0, 0.2)), *rng.uniform(15.0, 150.0, 5),
+                     2300.0, rng.uniform(-np.pi / 4, np.pi / 4), 0.0])
+    return np.array(rows)
+
+
+@pytest.mark.parametrize("cap", [3, 12, 30, 200])
+def test_a_converged_root_survives_a_small_iteration_cap(host, cap):
+    """Entries whose attenuation cancels are bisected again for their last
+    digits; with few halvings allowed (or where the bisection closes on a jump)
+    a converged Newton root must not be given up for that."""
+    b = host(layer_classes(60, 5), 1, 1, newton=max(cap, 12), bisect=cap)
+    solved = (b[:, 2] == 1) & (b[:, 4] <= 1e-9)
+    assert solved.sum() > 5000
+    assert (b[solved, 5] == 1).all()
+    assert b[solved, 6].max() <= 1e-9
