@@ -465,7 +465,6 @@ constexpr double kFoldSlope = 0.2;                  // d psi / d theta_R below t
 constexpr double kFoldMargin = 2.0 * kPi / 180.0;   // guard band around a fold
 constexpr int kFoldBins = 720;                      // 0.5-degree ray-angle bins
 constexpr int kFoldWords = (kFoldBins + 31) / 32;
-constexpr double kWarmSlope = 0.05;                 // accepted roots: slope at least this
 constexpr int kWarmParts = 64;                      // most lists of fold directions
 constexpr int kLenStride = 16;                      // their lengths: a 128-byte line each
 
@@ -741,34 +740,11 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
       continue;
     }
     const float2 p = w.pred[job * a.n_solve + sidx];
-    double x, y, slope;
-    if (!warm_newton(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x, (double)p.y, &x,
-                     &y, &slope)) {
-      atomicAdd(&s_cnt[4], 1u);
-      reject = true;
-      continue;
-    }
-    if (!(slope >= kWarmSlope)) {
-      atomicAdd(&s_cnt[5], 1u);
-      reject = true;
-      continue;
-    }
-    if (!el && !thi_is_nearest(m, mode, a.kernel, x, y)) {
-      atomicAdd(&s_cnt[6], 1u);
-      reject = true;
-      continue;
-    }
-    if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
-    if (x < 0.0) x += kTwoPi;
-    const Vel v = energy_velocity(m, mode, a.kernel, x, y);
     Entry e;
-    ray_quantities(v, &e);
-    e.thR = x;
-    e.thI = y;
-    const double h = el ? 0.0 : homog_residual(v);
-    e.res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi_star)));
-    if (!(e.res <= w.resid_tol) || !(e.V > 0.0) || !isfinite(e.V) || !(e.A >= 0.0)) {
-      atomicAdd(&s_cnt[7], 1u);
+    const int why = warm_entry(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x,
+                               (double)p.y, w.resid_tol, &e);
+    if (why != kWarmOk) {
+      atomicAdd(&s_cnt[why], 1u);
       reject = true;
       continue;
     }
@@ -1238,37 +1214,17 @@ __global__ void __launch_bounds__(64) k_warm3_solve(Warm3Args w, int64_t n_rows)
       const bool el = theta_i_zero(m, mode);
       const double psi_star = polar_to_axis(f, c);
       const int fb = fold_bin(psi_star);
-      double x, y, slope;
       const float2 p = w.pred[e];
       if ((w.fold[job * kFoldWords + (fb >> 5)] >> (fb & 31)) & 1u) {
         cnt[3] = 1;
         plain = true;
-      } else if (!warm_newton(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x,
-                              (double)p.y, &x, &y, &slope)) {
-        cnt[4] = 1;
-        plain = true;
-      } else if (!(slope >= kWarmSlope)) {
-        cnt[5] = 1;
-        plain = true;
-      } else if (!el && !thi_is_nearest(m, mode, a.kernel, x, y)) {
-        cnt[6] = 1;
-        plain = true;
       } else {
-        if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
-        if (x < 0.0) x += kTwoPi;
-        const Vel v = energy_velocity(m, mode, a.kernel, x, y);
         Entry en;
-        ray_quantities(v, &en);
-        en.thR = x;
-        en.thI = y;
-        const double h = el ? 0.0 : homog_residual(v);
-        en.res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi_star)));
-        if (!(en.res <= w.resid_tol) || !(en.V > 0.0) || !isfinite(en.V) || !(en.A >= 0.0)) {
-          cnt[7] = 1;
-          plain = true;
-        } else {
-          store_single(a, idx, stride, en, f, CHERT_ST_OK);
-        }
+        const int why = warm_entry(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x,
+                                   (double)p.y, w.resid_tol, &en);
+        for (int q = kWarmNewton; q <= kWarmEntry; ++q) cnt[q] = q == why ? 1 : 0;
+        plain = why != kWarmOk;
+        if (!plain) store_single(a, idx, stride, en, f, CHERT_ST_OK);
       }
       if (plain) {
         cnt[1] = 1;

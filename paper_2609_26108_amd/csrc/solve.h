@@ -337,8 +337,11 @@ __device__ __forceinline__ void bracket_entry(const SolveParams& a, const Medium
 // least of the mode's losses?  (The OEV maps pass through zero next to their
 // branch changes; MEV's do not.)  The angles' last bit then moves A by 1e-10 of
 // itself, so which of the neighbouring 64-bit angles is stored decides its
-// last six digits: they are the literal bisection's, not those a faster
-// iteration happens to end on.
+// last six digits.  Every build takes the literal bisection's, which are the
+// sequential definition's, digit for digit; they are no closer to the exact
+// root than Newton's (240,000 OEV qSV entries against 80-bit roots: A off by
+// more than 1e-10 in one of them, without this rule in none, by finite
+// differences and bisection alone in five).
 __device__ __forceinline__ bool loss_cancelled(const Medium& m, int mode, bool el,
                                                const Entry& e) {
   const double l44 = fabs(m.a44.im) / m.a44.re;
@@ -478,6 +481,33 @@ __device__ __forceinline__ bool warm_newton(const Medium& m, int mode, int kerne
   *yo = y;
   *slope = sl;
   return true;
+}
+
+// Surrogate start of one direction away from the folds: Newton from the
+// prediction (x0, y0), and the checks that the plain search would store the
+// same entry.  kWarmOk, or why the direction goes to the plain search instead
+// (the CHERT_WARM_NSTATS counter of that reason).
+constexpr double kWarmSlope = 0.05;  // accepted roots: slope at least this
+enum { kWarmOk = 0, kWarmNewton = 4, kWarmFlat = 5, kWarmBranch = 6, kWarmEntry = 7 };
+__device__ __forceinline__ int warm_entry(const Medium& m, int mode, int kernel, bool el,
+                                          double psi_star, double x0, double y0, double resid_tol,
+                                          Entry* e) {
+  double x, y, slope;
+  if (!warm_newton(m, mode, kernel, el, psi_star, x0, y0, &x, &y, &slope)) return kWarmNewton;
+  if (!(slope >= kWarmSlope)) return kWarmFlat;
+  if (!el && !thi_is_nearest(m, mode, kernel, x, y)) return kWarmBranch;
+  if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
+  if (x < 0.0) x += kTwoPi;
+  const Vel v = energy_velocity(m, mode, kernel, x, y);
+  ray_quantities(v, e);
+  e->thR = x;
+  e->thI = y;
+  const double h = el ? 0.0 : homog_residual(v);
+  e->res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi_star)));
+  if (!(e->res <= resid_tol) || !(e->V > 0.0) || !isfinite(e->V) || !(e->A >= 0.0) ||
+      loss_cancelled(m, mode, el, *e))
+    return kWarmEntry;
+  return kWarmOk;
 }
 
 }  // namespace chert

@@ -63,6 +63,7 @@ inline F fmin(F a, F b) { return F(::fmin(a.v, b.v)); }
 inline F fmax(F a, F b) { return F(::fmax(a.v, b.v)); }
 inline F copysign(F a, F b) { return F(::copysign(a.v, b.v)); }
 inline F floor(F a) { return F(::floor(a.v)); }
+inline F fmod(F a, F b) { return F(::fmod(a.v, b.v)); }
 inline F expm1(F a) { ++opc::g.trans; return F(::expm1(a.v)); }
 inline F atan2(F a, F b) { ++opc::g.trans; return F(::atan2(a.v, b.v)); }
 inline void sincos(F a, F* s, F* c) {
@@ -185,18 +186,10 @@ int main() {
         ++n_dir;
         if (st & (CHERT_ST_NO_BRACKET | CHERT_ST_NONPHYS)) continue;
         // as k_warm_solve from a prediction off the root by (dx0, dy0)
-        F x, y, slope;
+        Entry e{};
         take();
-        bool ok = warm_newton(m, mode, sp.kernel, el, psi, best.thR + dx0, best.thI + dy0, &x,
-                              &y, &slope);
-        if (ok && !el) ok = thi_is_nearest(m, mode, sp.kernel, x, y);
-        if (ok) {
-          const Vel v = energy_velocity(m, mode, sp.kernel, x, y);
-          Entry e;
-          ray_quantities(v, &e);
-          const F h = el ? F(0.0) : homog_residual(v);
-          e.res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi)));
-        }
+        const bool ok = warm_entry(m, mode, sp.kernel, el, psi, best.thR + dx0, best.thI + dy0,
+                                   F(1e-11), &e) == kWarmOk;
         opc::Counts c2 = take();
         wa_fl += c2.flops;
         wa_tr += c2.trans;

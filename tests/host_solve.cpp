@@ -4,7 +4,9 @@
 //   class direction newton_ok newton_miss newton_residual root_ok root_residual
 // where the Newton columns are bracket_newton's answer and the root columns
 // bracket_root's.  Arguments: mode kernel n_sweep n_dirs newton_iters
-// bisect_iters.
+// bisect_iters.  With a seventh, "warm", one line per direction instead:
+//   class direction status V A reason V A
+// of the plain search and of warm_entry started 1e-3 rad off its root.
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -42,6 +44,14 @@ int main(int argc, char** argv) {
     const SweepTable t{tab.data(), nullptr, a.n_sweep, h};
     for (int d = 0; d < n_dirs / 2; ++d) {
       const double psi = wrap_pi(d * (kTwoPi / n_dirs) - m.tilt);
+      if (argc > 7) {
+        int br[kMaxBr];
+        Entry p{}, w{};
+        const int st = solve_dir(a, m, mode, t, psi, br, &p);
+        const int why = warm_entry(m, mode, a.kernel, el, psi, p.thR + 1e-3, p.thI + 2e-4, 1e-11, &w);
+        printf("%d %d %d %.17g %.17g %d %.17g %.17g\n", k, d, st, p.V, p.A, why, w.V, w.A);
+        continue;
+      }
       t.for_brackets(psi, [&](int j, double2 sa, double2 sb) {
         const Bracket b = bracket_at(a, j, sa, sb, psi);
         double x = 0.0, y = 0.0, miss = NAN;

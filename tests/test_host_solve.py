@@ -31,9 +31,9 @@ def host(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host_solve.cpp"), "-o", exe, "-lm"],
                    check=True, capture_output=True, text=True)
 
-    def run(classes, mode, kernel, n_sweep=1440, n_dirs=360, newton=12, bisect=200):
+    def run(classes, mode, kernel, n_sweep=1440, n_dirs=360, newton=12, bisect=200, extra=()):
         text = "\n".join(" ".join(repr(float(x)) for x in r) for r in classes) + "\n"
-        out = subprocess.run([exe] + [str(x) for x in (mode, kernel, n_sweep, n_dirs, newton, bisect)],
+        out = subprocess.run([exe] + [str(x) for x in (mode, kernel, n_sweep, n_dirs, newton, bisect, *extra)],
                              input=text, check=True, capture_output=True, text=True).stdout
         return np.array([[float(x) for x in line.split()] for line in out.splitlines()])
     return run
@@ -77,3 +77,20 @@ def test_a_converged_root_survives_a_small_iteration_cap(host, cap):
     assert solved.sum() > 5000
     assert (b[solved, 5] == 1).all()
     assert b[solved, 6].max() <= 1e-9
+
+
+def test_surrogate_start_leaves_cancelled_attenuation_to_the_plain_search(host):
+    """Both builds store the same digits of an attenuation that has cancelled:
+    the surrogate start accepts no such entry, and what it accepts is the plain
+    search's entry within the cache bar."""
+    cls = layer_classes(60, 6)
+    b = host(cls, 1, 1, extra=("warm",))
+    im = [cls[:, i] / cls[:, 5 + i] for i in range(5)]  # imaginary parts of the moduli
+    loss = np.minimum.reduce([im[0] / cls[:, 0], im[2] / cls[:, 2], im[3] / cls[:, 3]])
+    ok = b[:, 5] == 0
+    assert ok.sum() > 5000
+    a_v = np.abs(b[ok, 7]) * b[ok, 6]
+    assert (a_v >= 1e-3 * loss[b[ok, 0].astype(int)]).all()
+    same = ok & (b[:, 2] == 0) & (np.abs(b[:, 6] - b[:, 3]) < 1e-6 * b[:, 3])
+    assert same.sum() > 5000
+    assert (np.abs(b[same, 7] - b[same, 4]) / np.abs(b[same, 4])).max() <= 1e-10
