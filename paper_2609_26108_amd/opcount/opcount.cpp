@@ -186,10 +186,18 @@ int main() {
         ++n_dir;
         if (st & (CHERT_ST_NO_BRACKET | CHERT_ST_NONPHYS)) continue;
         // as k_warm_solve from a prediction off the root by (dx0, dy0)
-        Entry e{};
+        F x, y, slope;
         take();
-        const bool ok = warm_entry(m, mode, sp.kernel, el, psi, best.thR + dx0, best.thI + dy0,
-                                   F(1e-11), &e) == kWarmOk;
+        bool ok = warm_newton(m, mode, sp.kernel, el, psi, best.thR + dx0, best.thI + dy0, &x,
+                              &y, &slope);
+        if (ok && !el) ok = thi_is_nearest(m, mode, sp.kernel, x, y);
+        if (ok) {
+          const Vel v = energy_velocity(m, mode, sp.kernel, x, y);
+          Entry e;
+          ray_quantities(v, &e);
+          const F h = el ? F(0.0) : homog_residual(v);
+          e.res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi)));
+        }
         opc::Counts c2 = take();
         wa_fl += c2.flops;
         wa_tr += c2.trans;
