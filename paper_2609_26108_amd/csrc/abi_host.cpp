@@ -91,14 +91,18 @@ int star_columns(const chert_cache_desc* d, const int32_t* bin, int n_off, int32
 // azimuth within 2 asin(sin(delta / 2) / sqrt(r r_u)) of u's (haversine), so
 // only those are evaluated: ~450 azimuths and a handful of dot products at N =
 // 41,253 instead of N (a 3D trace at radius 3 spent 7.9 of 22.7 ms in that
-// search, a block trace 1.1 ms on the directions' upload).  If the best one found lies within delta nothing
-// outside can beat it; else delta doubles.
+// search, a block trace 1.1 ms on the directions' upload).  If the best one
+// found lies within delta nothing outside can beat it; else delta doubles.
+// That holds for unit vectors: others (an infinite spacing, or one whose
+// square underflows, has no direction) get the search over all N, and index 0
+// where no dot product is a number.
 int fib_nearest(int N, const double* u) {
   const double ga = M_PI * (3.0 - sqrt(5.0));
   const double uz = u[2] > 1.0 ? 1.0 : (u[2] < -1.0 ? -1.0 : u[2]);
   const double th = acos(uz), ru = sin(th), phi = atan2(u[1], u[0]) / (2.0 * M_PI);
+  const bool unit = fabs(u[0] * u[0] + u[1] * u[1] + u[2] * u[2] - 1.0) < 1e-9;
   for (double delta = 2.2 / sqrt((double)N);; delta *= 2.0) {
-    const bool all = delta > 0.5;  // (few directions)
+    const bool all = !unit || delta > 0.5;  // (few directions)
     const double zhi = all || th - delta <= 0.0 ? 1.0 : cos(th - delta);
     const double zlo = all || th + delta >= M_PI ? -1.0 : cos(th + delta);
     // z_i = 1 - (2 i + 1) / N within [zlo, zhi], a few indices to spare
@@ -127,7 +131,8 @@ int fib_nearest(int N, const double* u) {
         best = i;
       }
     }
-    if (best >= 0 && (all || bd >= cos(delta) + 1e-12)) return best;
+    if (all) return best < 0 ? 0 : best;
+    if (best >= 0 && bd >= cos(delta) + 1e-12) return best;
   }
 }
 
