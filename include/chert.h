@@ -363,8 +363,9 @@ typedef struct chert_trace_opts {
                          + width; otherwise it stays active for a later
                          round (2D tiles; 3D tiles order batches of more
                          tiles than twice the resident workgroups by
-                         themselves, unless max_rounds is given).  The
-                         fields do not depend on it.                      */
+                         themselves, for a bounded number of rounds,
+                         unless max_rounds is given).  The fields do not
+                         depend on it.                                    */
   chert_trace_stats *stats_host; /* nullable: filled when the call returns */
   const volatile int32_t *abort_flag_host; /* nullable caller-owned word in
                          pinned host memory (hipHostMalloc).  While it is

@@ -93,9 +93,8 @@ int enqueue_wmin(const double* W, int64_t per_field, double* wmin, hipStream_t s
 // problem per (source, field).  The star offsets are device arrays.  Runs the
 // rounds to convergence on s (host checks every 8 rounds, or every round in
 // one persistent launch when `persistent`); tau must hold its initial values
-// (0 at the source, +inf elsewhere).  wmin_dev (nullable): the smallest
-// positive edge weight per field; with it the tiles are taken in the order of
-// their keys within a width (fewer visits, more rounds).
+// (0 at the source, +inf elsewhere).  `ordered`: large batches may take the
+// tiles in the order of their keys within a width (fewer visits, more rounds).
 struct Tile3Job {
   int nx, ny, nz, K;
   const int32_t* cls;
@@ -112,7 +111,7 @@ int relax_tiles_3d(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int
                    const int32_t* ox_dev, const int32_t* oy_dev, const int32_t* oz_dev, int n_off,
                    int R, int tile_x, int tile_z, int push_group, int max_rounds, void* ws,
                    size_t ws_bytes, hipStream_t s, const volatile int32_t* abort_flag,
-                   bool persistent, const double* wmin_dev, int* rounds, int64_t* visits,
+                   bool persistent, bool ordered, int* rounds, int64_t* visits,
                    int64_t* edges);
 
 // Raise *err if any of the n class ids lies outside [0, K) (trace.hip).

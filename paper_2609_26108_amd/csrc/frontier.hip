@@ -758,9 +758,7 @@ int trace_batch_frontier(const chert_trace_job* jobs, int n_jobs, const chert_tr
     }
   }
   enqueue_wmin_init(a.wmin, s);
-  // a caller's own round cap was chosen for unordered rounds
-  const bool ordered = P.tiles && o->max_rounds <= 0;
-  if (a.far || ordered) {
+  if (a.far) {
     for (int j = 0; j < n_jobs; ++j) {
       const int64_t rows = jd[j].per_node ? jd[j].n : jobs[j].n_classes * jobs[j].n_classes;
       enqueue_wmin((const double*)(ws + P.off_W[j]), rows * (int64_t)P.n_off, a.wmin, s);
@@ -788,7 +786,9 @@ int trace_batch_frontier(const chert_trace_job* jobs, int n_jobs, const chert_tr
     rc = relax_tiles_3d(tj.data(), n_jobs, tp.data(), (int)tp.size(), a.ox, a.oy, a.oz, P.n_off,
                         P.R, o->tile_x, o->tile_z, o->push_group, P.max_iter, ws + P.off_tiles,
                         P.total - P.off_tiles, s, o->abort_flag_host,
-                        o->launch == CHERT_LAUNCH_PERSISTENT, ordered ? a.wmin : nullptr, &rounds, &tile_visits, &tile_edges);
+                        o->launch == CHERT_LAUNCH_PERSISTENT,
+                        o->max_rounds <= 0,  // a caller's own cap was chosen for unordered rounds
+                        &rounds, &tile_visits, &tile_edges);
     if (rc) return rc;
     iters = rounds;
   }

@@ -47,14 +47,18 @@ constexpr int kT3Self = 13;             // s of (0, 0, 0)
 // (seven rows of 290 offsets), which with the 8 x 8 x 8 tile's 32 KiB leaves
 // three workgroups per compute unit
 constexpr size_t kT3WLdsBytes = 16 * 1024;
-// Width of the tile ordering in tile sides (times the smallest edge weight).
-// Ordered rounds visit a tile fewer times (42,799 instead of 67,163 visits on
-// a 121 x 121 x 61 grid, 4 fields) but there are more of them, so only batches
-// of more than twice the resident workgroups -- rounds that fill the device
-// several times over -- take it: there 9.0 -> 7.6 ms, while 800 tiles (every
-// visit of a round at once) went from 1.80 to 1.98 ms.  Half a side: 9.5 ms,
-// one: 7.8, two: 7.6, four: 8.5.
-constexpr double kT3OrderSides = 2.0;
+// Width of the tile ordering in tile sides (times the typical edge weight).
+// Ordered rounds visit a tile fewer times (43,061 instead of 67,762 visits on
+// a 121 x 121 x 61 grid, 4 fields), but a round holds fewer tiles, so only
+// batches of more than twice the resident workgroups -- rounds that fill the
+// device several times over -- take it: there 9.0 -> 6.9 ms, while 800 tiles
+// (every visit of a round at once) went from 1.80 to 1.98 ms.  A quarter side:
+// 6.94 ms, 32 rounds; this: 6.93, 30; half: 6.98, 29; one: 7.78, 29.
+constexpr double kT3OrderSides = 0.35;
+// Rounds that the ordering may take, some four times what it takes on layered
+// models: whatever the weights' contrast, the rounds after these visit every
+// active tile, no more of them than an unordered relaxation needs.
+inline int order_cap(int span) { return 64 + 2 * span; }
 constexpr int kT3PminStride = 16;  // one 128-byte line per shard
 constexpr unsigned long long kT3Inf = 0x7ff0000000000000ull;
 
@@ -88,11 +92,13 @@ struct T3Args {
   int32_t* err;
   unsigned long long* stats;  // [kStatSlots][16] shards of: [0] visits, [1] edges examined
   // Tile ordering: a tile woken with key k (the smallest changed border value
-  // that woke it) is visited in a round only if k is within `width` times the
-  // field's smallest edge weight of its problem's smallest pending key;
-  // otherwise it stays active for a later round.  width 0: every active tile.
+  // that woke it) is visited in a round before order_rounds only if k is within
+  // `width` times its job's and field's typical edge weight of its problem's
+  // smallest pending key; otherwise it stays active for a later round.
+  // width 0: every active tile.
   double width;
-  const double* wmin;        // [2]
+  int order_rounds;
+  double* typ;               // [n_jobs][2] typical edge weights (k_tile3_typ)
   unsigned long long* key;   // [2][n_tiles] keys (double bits) by round parity
   unsigned long long* pmin;  // [3][n_prob][shards][kT3PminStride] smallest key, by round mod 3
   int pmin_shards;
@@ -176,6 +182,39 @@ __global__ void k_tile3_clear(int32_t* flags, int64_t n_flags, int32_t* counter,
   if (tid < 64) err[tid] = 0;  // error word, barrier words, result, abort record
   for (int64_t t = tid; t < kStatSlots * kStatSlotU64; t += (int64_t)gridDim.x * blockDim.x)
     stats[t] = 0ull;
+}
+
+// The typical edge weight of (job blockIdx.x, field blockIdx.y): the mean of its
+// classes' own positive finite weights, summed in a fixed order; +inf (no
+// ordering) where there is none.  A mean, not the smallest weight: one nearly
+// lossless class or one fine axis makes the smallest arbitrarily small against
+// the keys, and every round then holds a tile or two.
+constexpr int kTypThreads = 256;
+__global__ void __launch_bounds__(kTypThreads) k_tile3_typ(T3Args a) {
+  __shared__ double s_sum[kTypThreads];
+  __shared__ int s_n[kTypThreads];
+  const T3JobDev J = a.jobs[blockIdx.x];
+  const int f = blockIdx.y, tid = threadIdx.x;
+  double sum = 0.0;
+  int n = 0;
+  for (int64_t q = tid; q < (int64_t)J.K * a.n_off; q += kTypThreads) {
+    const int64_t k = q / a.n_off, o = q - k * a.n_off;
+    const double w = J.W[(((int64_t)f * J.K + k) * J.K + k) * a.n_off + o];
+    if (w > 0.0 && w < INFINITY) {
+      sum += w;
+      ++n;
+    }
+  }
+  s_sum[tid] = sum;
+  s_n[tid] = n;
+  for (int d = kTypThreads / 2; d >= 1; d >>= 1) {
+    __syncthreads();
+    if (tid < d) {
+      s_sum[tid] += s_sum[tid + d];
+      s_n[tid] += s_n[tid + d];
+    }
+  }
+  if (tid == 0) a.typ[2 * blockIdx.x + f] = s_n[0] ? s_sum[0] / s_n[0] : INFINITY;
 }
 
 // activate the source tile of every problem
@@ -362,7 +401,7 @@ __device__ __forceinline__ bool defer3(const T3Args& a, int round, int T, int p,
   for (int q = 0; q < a.pmin_shards; ++q) lo = min(lo, pm[q * kT3PminStride]);
   if (k <= lo) return false;
   const double lim =
-      __longlong_as_double((long long)lo) + a.width * a.wmin[a.probs[p].field];
+      __longlong_as_double((long long)lo) + a.width * a.typ[2 * a.probs[p].job + a.probs[p].field];
   if (__longlong_as_double((long long)k) <= lim) return false;
   const int64_t out = (int64_t)((round + 1) & 1) * a.n_tiles;
   if (atomicOr(&a.flags[out + T], f) == 0)
@@ -392,7 +431,7 @@ __device__ void visit3(const T3Args& a, int round, int T) {
     const int p = a.tile_prob[T];  // in flight with the flag
     if (f) {
       fin[T] = 0;
-      if (a.width > 0.0 && defer3(a, round, T, p, f)) f = 0;
+      if (a.width > 0.0 && round < a.order_rounds && defer3(a, round, T, p, f)) f = 0;
     }
     s_prob = p;
     s_flag = f;
@@ -533,7 +572,7 @@ __device__ void visit3(const T3Args& a, int round, int T) {
                     ny_ < J.nty && nz_ >= 0 && nz_ < J.ntz;
     const int TN = P.tile_base + (nz_ * J.nty + ny_) * J.ntx + nx_;
     bool fresh = false;
-    if (a.width > 0.0) {
+    if (a.width > 0.0 && round + 1 < a.order_rounds) {
       const unsigned long long k = s_key;
       if (on) atomicMin(&a.key[out + TN], k);
       if (n == 27)
@@ -630,7 +669,8 @@ size_t align256_t3(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct T3Plan {
   int tx = 0, tz = 0, lx = 0, lz = 0, n_tiles = 0, w_classes = 0, pmin_shards = 1;
-  size_t off_jobs = 0, off_probs = 0, off_flags = 0, off_list = 0, off_tprob = 0, off_soff = 0, off_counter = 0, off_key = 0, off_pmin = 0, off_err = 0,
+  int span = 0;  // most tiles along the three axes together
+  size_t off_typ = 0, off_jobs = 0, off_probs = 0, off_flags = 0, off_list = 0, off_tprob = 0, off_soff = 0, off_counter = 0, off_key = 0, off_pmin = 0, off_err = 0,
          off_stats = 0, total = 0;
   size_t lds = 0;
 };
@@ -650,7 +690,13 @@ int plan_t3(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int n_prob
     tiles += (int64_t)((J.nx + P->tx - 1) / P->tx) * ((J.ny + P->tx - 1) / P->tx) *
              ((J.nz + P->tz - 1) / P->tz);
   }
-  for (int j = 0; j < n_jobs; ++j) maxK = jobs[j].K > maxK ? jobs[j].K : maxK;
+  for (int j = 0; j < n_jobs; ++j) {
+    const Tile3Job& J = jobs[j];
+    maxK = J.K > maxK ? J.K : maxK;
+    const int span = (J.nx + P->tx - 1) / P->tx + (J.ny + P->tx - 1) / P->tx +
+                     (J.nz + P->tz - 1) / P->tz;
+    P->span = span > P->span ? span : P->span;
+  }
   if (tiles >= 0x7fffffffLL) return fail(CHERT_ERR_UNSUPPORTED, "batch too large for one launch");
   P->n_tiles = (int)tiles;
   P->w_classes = code_classes(maxK, n_off, kT3WLdsBytes);
@@ -679,6 +725,8 @@ int plan_t3(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int n_prob
   P->pmin_shards = n_prob <= 8 ? 8 : (n_prob <= 32 ? 2 : 1);
   P->off_pmin = off;
   off += align256_t3((size_t)3 * n_prob * P->pmin_shards * kT3PminStride * sizeof(uint64_t));
+  P->off_typ = off;
+  off += align256_t3((size_t)2 * n_jobs * sizeof(double));
   P->off_err = off;
   off += 256;
   P->off_stats = off;
@@ -703,9 +751,16 @@ int read_back(const T3Args& a, hipStream_t s, int32_t* herr, int64_t* visits, in
   return CHERT_OK;
 }
 
+// Switch the tile ordering on (the jobs' tables are on the device).
+void order_tiles(const T3Plan& P, int n_jobs, hipStream_t s, T3Args* a) {
+  a->width = kT3OrderSides * P.tx;
+  a->order_rounds = order_cap(P.span);
+  CHERT_LAUNCH("k_tile3_typ", k_tile3_typ, dim3((unsigned)n_jobs, 2), dim3(kTypThreads), 0, s, *a);
+}
+
 // Every round in one launch of an occupancy-sized grid (all of its
 // workgroups resident, which the device-wide barrier needs).
-int run_persistent(const T3Plan& P, T3Args a, const int32_t* ox_dev,
+int run_persistent(const T3Plan& P, T3Args a, int n_jobs, bool ordered, const int32_t* ox_dev,
                    const int32_t* oy_dev, const int32_t* oz_dev, int push_group, int max_rounds,
                    int threads, hipStream_t s, int* rounds, int64_t* visits, int64_t* edges) {
   void (*kern)(T3Args, PersistArgs) =
@@ -720,7 +775,7 @@ int run_persistent(const T3Plan& P, T3Args a, const int32_t* ox_dev,
   if (per_cu < 1) return fail(CHERT_ERR_UNSUPPORTED, "3D tile does not fit on a compute unit");
   const int64_t resident = (int64_t)per_cu * cus;
   const int grid = (int)(P.n_tiles < resident ? P.n_tiles : resident);
-  if (a.wmin && P.n_tiles > 2 * resident) a.width = kT3OrderSides * P.tx;
+  if (ordered && P.n_tiles > 2 * resident) order_tiles(P, n_jobs, s, &a);
   PersistArgs pa{};
   pa.max_rounds = max_rounds;
   pa.bar = (uint32_t*)(a.err + 48);  // [0] arrivals, [1] generation, [2] abort
@@ -761,7 +816,7 @@ int relax_tiles_3d(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int
                    const int32_t* ox_dev, const int32_t* oy_dev, const int32_t* oz_dev, int n_off,
                    int R, int tile_x, int tile_z, int push_group, int max_rounds, void* ws,
                    size_t ws_bytes, hipStream_t s, const volatile int32_t* abort_flag,
-                   bool persistent, const double* wmin_dev, int* rounds, int64_t* visits,
+                   bool persistent, bool ordered, int* rounds, int64_t* visits,
                    int64_t* edges) {
   T3Plan P;
   int rc = plan_t3(jobs, n_jobs, probs, n_prob, R, n_off, tile_x, tile_z, max_rounds, &P);
@@ -808,8 +863,9 @@ int relax_tiles_3d(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int
   a.n_prob = n_prob;
   a.n_tiles = P.n_tiles;
   a.w_classes = P.w_classes;
-  a.width = 0.0;  // set below
-  a.wmin = wmin_dev;
+  a.width = 0.0;  // order_tiles sets it
+  a.order_rounds = 0;
+  a.typ = (double*)(w + P.off_typ);
   a.key = (unsigned long long*)(w + P.off_key);
   a.pmin = (unsigned long long*)(w + P.off_pmin);
   a.pmin_shards = P.pmin_shards;
@@ -837,8 +893,9 @@ int relax_tiles_3d(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int
     }
     a.abort_host = (const int32_t*)at.devicePointer;
   }
-  if (persistent) return run_persistent(P, a, ox_dev, oy_dev, oz_dev, push_group, max_rounds,
-                                        threads_of(P), s, rounds, visits, edges);
+  if (persistent)
+    return run_persistent(P, a, n_jobs, ordered, ox_dev, oy_dev, oz_dev, push_group, max_rounds,
+                          threads_of(P), s, rounds, visits, edges);
   void (*kern)(T3Args, int) = push_group == 1 ? k_tile3_tau<1> : (push_group == 4 ? k_tile3_tau<4>
                                                                                    : k_tile3_tau<2>);
   const int threads = threads_of(P);
@@ -854,7 +911,7 @@ int relax_tiles_3d(const Tile3Job* jobs, int n_jobs, const Tile3Prob* probs, int
   // the resident walking each round's list by ticket (twice measured 5 %
   // faster than four times on the 3D layered batch)
   const int grid = (int)(P.n_tiles <= 2 * resident ? P.n_tiles : 2 * resident);
-  if (a.wmin && P.n_tiles > 2 * resident) a.width = kT3OrderSides * P.tx;
+  if (ordered && P.n_tiles > 2 * resident) order_tiles(P, n_jobs, s, &a);
   CHERT_LAUNCH("k_tile3_clear", k_tile3_clear, dim3(256), dim3(256), 0, s, a.flags,
                (int64_t)2 * P.n_tiles, a.counter, (int)counter_words(max_rounds), a.err, a.stats, a.probs, a.n_prob,
                a.tile_prob, a.key, a.pmin,
