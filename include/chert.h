@@ -527,8 +527,10 @@ size_t chert_trace_cells_workspace_bytes(const chert_cache_desc *d, int64_t n_cl
  * read: outputs, max_rounds, bucket_width, stats_host (rounds[0] =
  * traveltime rounds, rounds[1] = BFS levels of the deepest tree, tile_visits[0] = cell
  * visits, edge_relaxations[0] = pair relaxations, levels_sum[0] = passes
- * over the pairs of the visited cells), abort_flag_host; the tile fields and
- * launch are ignored.  INVALID_ARG on a source inside a cell, a class id out
+ * over the pairs of the visited cells), abort_flag_host (polled by the host
+ * between groups of rounds and of BFS levels: a call that passes it takes a
+ * launch per round and per level, with the same results, where it might have
+ * taken one workgroup per problem); the tile fields and launch are ignored.  INVALID_ARG on a source inside a cell, a class id out
  * of range (checked on the device before any output is written) or a
  * workspace that is too small or not 256-byte aligned.  Synchronous with
  * respect to `stream` (the host checks the rounds); NO_CONVERGENCE when the

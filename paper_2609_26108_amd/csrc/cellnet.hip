@@ -1642,7 +1642,8 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   a.key = (unsigned long long*)(ws + P.off_key);
   a.list = (int32_t*)(ws + P.off_list);
   a.bfs = (int32_t*)(ws + P.off_bfs);
-  const bool tree1 = single_tree(P, outs);
+  // (not with an abort word, which the host polls between groups of levels)
+  const bool tree1 = single_tree(P, outs) && !o->abort_flag_host;
   a.hop = tree1 ? nullptr : (int32_t*)(ws + P.off_hop);
   a.bid = (int32_t*)(ws + P.off_hop + al256((size_t)P.n_prob * P.n * sizeof(int32_t)));
   a.tkey = (unsigned long long*)(ws + P.off_hop);
@@ -1825,8 +1826,6 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return fail(CHERT_ERR_HIP, hipGetErrorString(e));
-    if (o->abort_flag_host && *o->abort_flag_host)
-      return fail(CHERT_ERR_ABORTED, "aborted by the caller");
     if (tree1 && a.tree_mask) levels = alive;
     if (march) rounds = done[0];
     if (done[1]) return fail(CHERT_ERR_NO_CONVERGENCE, "round cap reached");
