@@ -1353,12 +1353,35 @@ struct CellPlan {
          off_kt = 0, off_vt = 0, off_jobs = 0, off_part = 0, total = 0;
 };
 
-// Lattice points up to which one workgroup runs a problem's BFS: its levels
-// are then narrow enough for 1024 threads (beyond, a launch per level over
-// many workgroups catches up).
-constexpr int64_t kTreeNodes = 1 << 20;
+// Does one workgroup run a problem's BFS, or a launch per level all of them?  A
+// workgroup takes some 20 ns a node in 2D and 36 in 3D, whatever the number of
+// problems; a launch per level costs 10 us a level and 1.9 ns a node and problem
+// beyond that.  Whole calls, launches against one workgroup, in ms: 2D, one
+// source (two problems) 321 thousand lattice points 6.5, 6.2 and 501 thousand
+// 8.1, 8.7; the trees of 802 thousand points with 2, 4 and 16 problems 3.4, 4.2,
+// 7.4 against 4.0, 4.1, 4.7.  3D, two problems: 39 thousand points 2.4, 2.2; 51
+// thousand 2.50, 2.53; 79 thousand 2.9, 3.5; 1 million 13.7, 34.9; 166 thousand
+// points with 8 and 32 problems 5.9, 16.6 against 7.8, 11.7.
 bool single_tree(const CellPlan& P, uint32_t outs) {
-  return (outs & (CHERT_OUT_PRED_P | CHERT_OUT_PRED_A)) && P.n <= kTreeNodes;
+  const bool d3 = P.dim == 3;
+  return (outs & (CHERT_OUT_PRED_P | CHERT_OUT_PRED_A)) && P.n <= 1 << 20 &&
+         (P.n <= (d3 ? 49152 : 400000) || P.n_prob >= (d3 ? 16 : 8));
+}
+
+// Does one workgroup run all rounds of a problem (2D), or a launch per round
+// all of them?  One workgroup's time follows the pairs of the network, 2.5 ns
+// each where every woken cell is visited and 0.8 where cells are ordered,
+// whatever the number of problems; launches cost 13.6 us per cell along x and z
+// and 0.055 ns a pair and problem.  Rounds, launches against one workgroup, in
+// ms (5 x 5 intervals a cell; one source: two problems): 40 x 20 cells unordered
+// 0.8, 0.6; 80 x 40 unordered 1.8, 2.2, with 16 sources 3.7, 2.7, at width 16
+// 1.9, 1.3; 160 x 80 unordered 3.3, 9.1, with 16 sources 12.4, 14.5, at width 16
+// 3.7, 4.0 and with two sources 4.7, 4.1; 40 x 20 cells of 16 x 16 intervals 2.2,
+// 9.2.
+bool march_pays(const CellPlan& P, const CellGeo& G, double width) {
+  const double pairs = (double)P.C * P.ns * P.ns;
+  return (width > 0.0 ? 0.8 : 2.5) * pairs <
+         13.6e3 * (G.ncx + G.ncz) + 0.055 * P.n_prob * pairs;
 }
 
 int cell_plan(const CellSrc& w, int64_t n_classes, const CellGeo& G, int32_t mode,
@@ -1734,7 +1757,8 @@ int trace_cells_impl(const CellSrc& w, int64_t n_classes, const CellGeo& G, int3
   int64_t table_n = P.K * P.K * s2;
   if (march_lds(table_n, P.C) > kMarchLds) table_n = 0;
   const bool march = P.dim == 2 && !w.mspm && !o->abort_flag_host && P.C <= 65535 &&
-                     march_lds(table_n, P.C) <= kMarchLds;
+                     march_lds(table_n, P.C) <= kMarchLds &&
+                     march_pays(P, G, o->bucket_width);
   a.mask = (unsigned long long*)(ws + P.off_mask);
   void (*km)(CellArgs, int) =
       P.ns <= 16 ? (table_n ? k_cell_march<true, 16> : k_cell_march<false, 16>)

@@ -101,3 +101,52 @@ def test_mspm_with_abort_word_bitwise(G, monkeypatch):
     both_forms(monkeypatch, lambda: G.trace_mspm(cls, 6, 5, 3, 10.0, 10.0, cid, 0, [0],
                                                  outputs=C.OUT_ALL, n_sweep=360),
                ("k_cell_relax", "k_cell_level"), ("k_cell_tight", "k_cell_tree"))
+
+
+@pytest.mark.parametrize("ncx,ncz,cn,n_src,bucket,launched", [
+    (20, 12, 5, 1, 0.0, False), (80, 40, 5, 1, 0.0, True), (80, 40, 5, 16, 0.0, False),
+    (80, 40, 5, 1, 16.0, False), (160, 80, 5, 1, 0.0, True), (20, 10, 16, 1, 0.0, True)])
+def test_rounds_take_the_faster_form(G, ncx, ncz, cn, n_src, bucket, launched):
+    """Networks on both sides of the rule between one workgroup per problem and
+    a launch per round: the form taken, and both forms' fields bitwise alike."""
+    import paper_2609_26108_amd as C
+    cls = tti_classes()
+    f, s = O.build_cache_2d(cls, n_dirs=360, mode_mask=0b001)
+    desc = C.cache_desc(n_dirs=360, modes=(0,))
+    cache = G.import_cache(f, s, desc, 3)
+    NX, NZ, _ = O.cell_lattice(ncx, ncz, cn)
+    cid = layered_cells(ncx, ncz, cn, 3, 0)
+    srcs = [(q * 977 * cn) % NX for q in range(n_src)]  # on the top edge
+    run = lambda: G.trace_cells(cache, desc, 3, ncx, ncz, cn, 10.0, 10.0, cid, 0, srcs,  # noqa: E731
+                                bucket_width=bucket)
+    with pytest.MonkeyPatch.context() as mp:
+        with Recorded(mp, False) as r:
+            a = run()
+    assert ("k_cell_relax" in r.kernels) == launched and ("k_cell_march" in r.kernels) != launched
+    with pytest.MonkeyPatch.context() as mp:
+        with Recorded(mp, True):
+            b = run()
+    for key in KEYS:
+        assert np.array_equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("nc,n_src,launched", [((8, 8, 8), 1, False), ((14, 14, 14), 1, True),
+                                               ((14, 14, 14), 8, False)])
+def test_block_trees_take_the_faster_form(G, nc, n_src, launched):
+    import paper_2609_26108_amd as C
+    f, s = O.build_cache_3d(tti3_classes(), N=400, mode_mask=0b001, n_sweep=360)
+    desc = C.cache_desc(dim=3, n_dirs=400, modes=(0,), n_sweep=360)
+    cache = G.import_cache(f, s, desc, 3)
+    NX, NY, NZ, _ = O.block_lattice(*nc, 3)
+    cid = banded(NX, NY, NZ, 3, 3)
+    srcs = [3 * q for q in range(n_src)]
+    run = lambda: G.trace_blocks(cache, desc, 3, *nc, 3, 10.0, 10.0, 10.0, cid, 0, srcs)  # noqa: E731
+    with pytest.MonkeyPatch.context() as mp:
+        with Recorded(mp, False) as r:
+            a = run()
+    assert ("k_block_level" in r.kernels) == launched and ("k_cell_tree" in r.kernels) != launched
+    with pytest.MonkeyPatch.context() as mp:
+        with Recorded(mp, True):
+            b = run()
+    for key in KEYS:
+        assert np.array_equal(a[key], b[key]), key
