@@ -740,11 +740,26 @@ k_warm_solve(WarmArgs w, int64_t n_jobs) {
       continue;
     }
     const float2 p = w.pred[job * a.n_solve + sidx];
+    double x, y, slope;
+    if (!warm_newton(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x, (double)p.y, &x,
+                     &y, &slope)) {
+      atomicAdd(&s_cnt[4], 1u);
+      reject = true;
+      continue;
+    }
+    if (!(slope >= kWarmSlope)) {
+      atomicAdd(&s_cnt[5], 1u);
+      reject = true;
+      continue;
+    }
+    if (!el && !thi_is_nearest(m, mode, a.kernel, x, y)) {
+      atomicAdd(&s_cnt[6], 1u);
+      reject = true;
+      continue;
+    }
     Entry e;
-    const int why = warm_entry(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x,
-                               (double)p.y, w.resid_tol, &e);
-    if (why != kWarmOk) {
-      atomicAdd(&s_cnt[why], 1u);
+    if (!warm_entry(m, mode, a.kernel, el, psi_star, x, y, w.resid_tol, &e)) {
+      atomicAdd(&s_cnt[7], 1u);
       reject = true;
       continue;
     }
@@ -1094,11 +1109,10 @@ k_warm_fold(WarmArgs w) {
           sc.ill = ill ? 1 : 0;
           again = ok && loss_cancelled(m, mode, el, sc.e) && bisection_completes(a, br);
         }
-        if (bisect_roots<true>(a, again, br, psi_star, &x, &y, job_of)) {
-          Entry lit;
+        double xl = x, yl = y;
+        if (bisect_roots<true>(a, again, br, psi_star, &xl, &yl, job_of) && same_root(xl, x)) {
           bool ill = false;
-          bracket_entry(a, m, mode, br, psi_star, el, x, y, &lit, &ill);
-          if (keep_literal(a, lit, sc.e)) sc.e = lit;
+          bracket_entry(a, m, mode, br, psi_star, el, xl, yl, &sc.e, &ill);
         }
       }
       __syncthreads();
@@ -1214,17 +1228,29 @@ __global__ void __launch_bounds__(64) k_warm3_solve(Warm3Args w, int64_t n_rows)
       const bool el = theta_i_zero(m, mode);
       const double psi_star = polar_to_axis(f, c);
       const int fb = fold_bin(psi_star);
+      double x, y, slope;
       const float2 p = w.pred[e];
       if ((w.fold[job * kFoldWords + (fb >> 5)] >> (fb & 31)) & 1u) {
         cnt[3] = 1;
         plain = true;
+      } else if (!warm_newton(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x,
+                              (double)p.y, &x, &y, &slope)) {
+        cnt[4] = 1;
+        plain = true;
+      } else if (!(slope >= kWarmSlope)) {
+        cnt[5] = 1;
+        plain = true;
+      } else if (!el && !thi_is_nearest(m, mode, a.kernel, x, y)) {
+        cnt[6] = 1;
+        plain = true;
       } else {
         Entry en;
-        const int why = warm_entry(m, mode, a.kernel, el, psi_star, psi_star + (double)p.x,
-                                   (double)p.y, w.resid_tol, &en);
-        for (int q = kWarmNewton; q <= kWarmEntry; ++q) cnt[q] = q == why ? 1 : 0;
-        plain = why != kWarmOk;
-        if (!plain) store_single(a, idx, stride, en, f, CHERT_ST_OK);
+        if (warm_entry(m, mode, a.kernel, el, psi_star, x, y, w.resid_tol, &en)) {
+          store_single(a, idx, stride, en, f, CHERT_ST_OK);
+        } else {
+          cnt[7] = 1;
+          plain = true;
+        }
       }
       if (plain) {
         cnt[1] = 1;

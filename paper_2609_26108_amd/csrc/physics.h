@@ -97,6 +97,7 @@ __device__ __forceinline__ cd csqrt_p(cd z) {
 // complex moduli of one class
 struct Medium {
   cd a11, a13, a33, a44, a66;
+  double q_ps, q_sh;  // largest quality factor of the coupled modes' a11, a33, a44; of qSH's
   bool elastic_ps, elastic_sh;
   bool fluid;  // no shear stiffness and a11 = a13 = a33: isotropic fluid
   double tilt;
@@ -114,6 +115,9 @@ __device__ __forceinline__ Medium load_medium(const chert_class& c) {
   m.a33 = complex_modulus(c.a33, c.q33);
   m.a44 = complex_modulus(c.a44, c.q44);
   m.a66 = complex_modulus(c.a66, c.q66);
+  const double q44 = c.a44 == 0.0 ? 0.0 : c.q44;
+  m.q_ps = fmax(q44, fmax(c.q11, c.q33));
+  m.q_sh = fmax(q44, c.q66);
   m.elastic_ps = m.a11.im == 0.0 && m.a13.im == 0.0 && m.a33.im == 0.0 && m.a44.im == 0.0;
   m.elastic_sh = m.a44.im == 0.0 && m.a66.im == 0.0;
   m.fluid = m.a44.re == 0.0 && m.a44.im == 0.0 && m.a66.re == 0.0 && m.a66.im == 0.0 &&

@@ -20,6 +20,7 @@ struct SolveParams {
 };
 
 constexpr double kWarmWindow = 0.35;  // the polish may move theta_R this far [rad]
+constexpr double kWarmSlope = 0.05;   // its accepted roots: slope at least this
 
 // Newton steps below this end the iteration: it is quadratic, so the error
 // left is the square of the last step (times the curvature), far below the
@@ -344,11 +345,8 @@ __device__ __forceinline__ void bracket_entry(const SolveParams& a, const Medium
 // differences and bisection alone in five).
 __device__ __forceinline__ bool loss_cancelled(const Medium& m, int mode, bool el,
                                                const Entry& e) {
-  const double l44 = fabs(m.a44.im) / m.a44.re;
-  const double loss = mode == CHERT_QSH ? fmin(l44, fabs(m.a66.im) / m.a66.re)
-                                        : fmin(l44, fmin(fabs(m.a11.im) / m.a11.re,
-                                                         fabs(m.a33.im) / m.a33.re));
-  return !el && fabs(e.A) * e.V < 1e-3 * loss;
+  // (the loss of a modulus, |Im a| / Re a, is 1 / Q)
+  return !el && fabs(e.A) * e.V * (mode == CHERT_QSH ? m.q_sh : m.q_ps) < 1e-3;
 }
 
 // Can the bisection of bracket b reach its stop within the halvings that the
@@ -358,12 +356,9 @@ __device__ __forceinline__ bool bisection_completes(const SolveParams& a, const 
   return b.tb - b.ta <= kBisectStop * (double)steps;
 }
 
-// Is `lit`, the literal bisection's entry, to replace `e`?  Not where the
-// bisection has closed on a jump of the ray-angle map and `e` is a root.
-__device__ __forceinline__ bool keep_literal(const SolveParams& a, const Entry& lit,
-                                             const Entry& e) {
-  return lit.res <= a.resid_tol || !(e.res <= a.resid_tol);
-}
+// Is the literal bisection's theta_R the root x again?  (Where the ray-angle
+// map jumps inside the bracket, it may close on the jump instead.)
+__device__ __forceinline__ bool same_root(double lit, double x) { return fabs(lit - x) <= 1e-6; }
 
 // The root of the bracket at sweep sample j and its ray quantities; false if
 // neither the Newton step nor the bisection converges.
@@ -376,12 +371,11 @@ __device__ __forceinline__ bool bracket_root(const SolveParams& a, const Medium&
       !bisect_root<false>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y))
     return false;
   bracket_entry(a, m, mode, b, psi_star, el, x, y, cand, cand_ill);
+  double xl, yl;
   if (loss_cancelled(m, mode, el, *cand) && bisection_completes(a, b) &&
-      bisect_root<true>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &x, &y)) {
-    Entry lit;
-    bracket_entry(a, m, mode, b, psi_star, el, x, y, &lit, cand_ill);
-    if (keep_literal(a, lit, *cand)) *cand = lit;
-  }
+      bisect_root<true>(m, mode, a.kernel, psi_star, b.ta, b.tb, b.fa, a.bisect_iters, &xl, &yl) &&
+      same_root(xl, x))
+    bracket_entry(a, m, mode, b, psi_star, el, xl, yl, cand, cand_ill);
   return true;
 }
 
@@ -483,19 +477,12 @@ __device__ __forceinline__ bool warm_newton(const Medium& m, int mode, int kerne
   return true;
 }
 
-// Surrogate start of one direction away from the folds: Newton from the
-// prediction (x0, y0), and the checks that the plain search would store the
-// same entry.  kWarmOk, or why the direction goes to the plain search instead
-// (the CHERT_WARM_NSTATS counter of that reason).
-constexpr double kWarmSlope = 0.05;  // accepted roots: slope at least this
-enum { kWarmOk = 0, kWarmNewton = 4, kWarmFlat = 5, kWarmBranch = 6, kWarmEntry = 7 };
-__device__ __forceinline__ int warm_entry(const Medium& m, int mode, int kernel, bool el,
-                                          double psi_star, double x0, double y0, double resid_tol,
-                                          Entry* e) {
-  double x, y, slope;
-  if (!warm_newton(m, mode, kernel, el, psi_star, x0, y0, &x, &y, &slope)) return kWarmNewton;
-  if (!(slope >= kWarmSlope)) return kWarmFlat;
-  if (!el && !thi_is_nearest(m, mode, kernel, x, y)) return kWarmBranch;
+// The entry of a polished root whose slope and theta_I have passed, and whether
+// it stands as the plain search's: a physical root within resid_tol whose
+// attenuation has not cancelled.
+__device__ __forceinline__ bool warm_entry(const Medium& m, int mode, int kernel, bool el,
+                                           double psi_star, double x, double y, double resid_tol,
+                                           Entry* e) {
   if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
   if (x < 0.0) x += kTwoPi;
   const Vel v = energy_velocity(m, mode, kernel, x, y);
@@ -504,10 +491,8 @@ __device__ __forceinline__ int warm_entry(const Medium& m, int mode, int kernel,
   e->thI = y;
   const double h = el ? 0.0 : homog_residual(v);
   e->res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi_star)));
-  if (!(e->res <= resid_tol) || !(e->V > 0.0) || !isfinite(e->V) || !(e->A >= 0.0) ||
-      loss_cancelled(m, mode, el, *e))
-    return kWarmEntry;
-  return kWarmOk;
+  return e->res <= resid_tol && e->V > 0.0 && isfinite(e->V) && e->A >= 0.0 &&
+         !loss_cancelled(m, mode, el, *e);
 }
 
 }  // namespace chert

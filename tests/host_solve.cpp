@@ -5,8 +5,8 @@
 // where the Newton columns are bracket_newton's answer and the root columns
 // bracket_root's.  Arguments: mode kernel n_sweep n_dirs newton_iters
 // bisect_iters.  With a seventh, "warm", one line per direction instead:
-//   class direction status V A reason V A
-// of the plain search and of warm_entry started 1e-3 rad off its root.
+//   class direction status V A rejected V A
+// of the plain search and of the surrogate start from 1e-3 rad off its root.
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -48,8 +48,12 @@ int main(int argc, char** argv) {
         int br[kMaxBr];
         Entry p{}, w{};
         const int st = solve_dir(a, m, mode, t, psi, br, &p);
-        const int why = warm_entry(m, mode, a.kernel, el, psi, p.thR + 1e-3, p.thI + 2e-4, 1e-11, &w);
-        printf("%d %d %d %.17g %.17g %d %.17g %.17g\n", k, d, st, p.V, p.A, why, w.V, w.A);
+        double x, y, slope;
+        const bool ok = warm_newton(m, mode, a.kernel, el, psi, p.thR + 1e-3, p.thI + 2e-4, &x, &y,
+                                    &slope) &&
+                        slope >= kWarmSlope && (el || thi_is_nearest(m, mode, a.kernel, x, y)) &&
+                        warm_entry(m, mode, a.kernel, el, psi, x, y, 1e-11, &w);
+        printf("%d %d %d %.17g %.17g %d %.17g %.17g\n", k, d, st, p.V, p.A, ok ? 0 : 1, w.V, w.A);
         continue;
       }
       t.for_brackets(psi, [&](int j, double2 sa, double2 sb) {
