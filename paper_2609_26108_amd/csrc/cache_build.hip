@@ -1162,7 +1162,7 @@ __global__ void __launch_bounds__(256) k_build_slow(SolveArgs a) {
     }
     const Vel v = energy_velocity(m, mode, a.kernel, thR, thI);
     Entry e;
-    ray_quantities(v, &e);
+    ray_quantities(v, m.unit, &e);
     e.thR = thR;
     e.thI = thI;
     e.res = theta_i_zero(m, mode) ? 0.0 : fabs(homog_residual(v));

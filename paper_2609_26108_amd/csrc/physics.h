@@ -94,9 +94,13 @@ __device__ __forceinline__ cd csqrt_p(cd z) {
   return cd{fabs(z.im) / (2.0 * t), copysign(t, z.im)};
 }
 
-// complex moduli of one class
+// complex moduli of one class, over 4^unit: a power of four near a33, so that
+// products of many moduli (the Newton determinant holds twenty-two) stay in
+// range whatever the caller's units; angles and residuals do not change by a
+// bit, velocities are over 2^unit
 struct Medium {
   cd a11, a13, a33, a44, a66;
+  int unit;
   double q_ps, q_sh;  // largest quality factor of the coupled modes' a11, a33, a44; of qSH's
   bool elastic_ps, elastic_sh;
   bool fluid;  // no shear stiffness and a11 = a13 = a33: isotropic fluid
@@ -110,11 +114,15 @@ __device__ __forceinline__ cd complex_modulus(double aR, double q) {
 
 __device__ __forceinline__ Medium load_medium(const chert_class& c) {
   Medium m;
-  m.a11 = complex_modulus(c.a11, c.q11);
-  m.a13 = complex_modulus(c.a13, c.q13);
-  m.a33 = complex_modulus(c.a33, c.q33);
-  m.a44 = complex_modulus(c.a44, c.q44);
-  m.a66 = complex_modulus(c.a66, c.q66);
+  int e = 0;
+  (void)frexp(c.a33, &e);  // (unusable classes: any)
+  m.unit = e >> 1;
+  const int s = -2 * m.unit;
+  m.a11 = complex_modulus(ldexp(c.a11, s), c.q11);
+  m.a13 = complex_modulus(ldexp(c.a13, s), c.q13);
+  m.a33 = complex_modulus(ldexp(c.a33, s), c.q33);
+  m.a44 = complex_modulus(ldexp(c.a44, s), c.q44);
+  m.a66 = complex_modulus(ldexp(c.a66, s), c.q66);
   const double q44 = c.a44 == 0.0 ? 0.0 : c.q44;
   m.q_ps = fmax(q44, fmax(c.q11, c.q33));
   m.q_sh = fmax(q44, c.q66);
@@ -598,15 +606,16 @@ struct Entry {
   double V, A, Q, r1, r3, thR, thI, res;
 };
 
-// ray quantities from a homogeneous complex energy velocity (eqs 10-11)
-__device__ __forceinline__ void ray_quantities(const Vel& v, Entry* e) {
+// ray quantities from a homogeneous complex energy velocity (eqs 10-11) over
+// 2^unit
+__device__ __forceinline__ void ray_quantities(const Vel& v, int unit, Entry* e) {
   double r1 = v.v1.re, r3 = v.v3.re, i1 = v.v1.im, i3 = v.v3.im;
   double vr = sqrt(r1 * r1 + r3 * r3);
   double u1 = r1 / vr, u3 = r3 / vr;
   double vi = i1 * u1 + i3 * u3;
   double s = vr * vr + vi * vi;
-  e->V = s / vr;
-  e->A = -vi / s;
+  e->V = ldexp(s / vr, unit);
+  e->A = ldexp(-vi / s, -unit);
   e->Q = (vi == 0.0) ? INFINITY : -(vr * vr - vi * vi) / (2.0 * vr * vi);
   e->r1 = u1;
   e->r3 = u3;

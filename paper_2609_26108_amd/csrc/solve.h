@@ -326,7 +326,7 @@ __device__ __forceinline__ void bracket_entry(const SolveParams& a, const Medium
   if (x >= kTwoPi) x -= kTwoPi;
   if (x < 0.0) x += kTwoPi;
   Vel v = energy_velocity(m, mode, a.kernel, x, y);
-  ray_quantities(v, cand);
+  ray_quantities(v, m.unit, cand);
   cand->thR = x;
   cand->thI = y;
   double h = el ? 0.0 : homog_residual(v);
@@ -486,7 +486,7 @@ __device__ __forceinline__ bool warm_entry(const Medium& m, int mode, int kernel
   if (fabs(x) >= kTwoPi) x = fmod(x, kTwoPi);
   if (x < 0.0) x += kTwoPi;
   const Vel v = energy_velocity(m, mode, kernel, x, y);
-  ray_quantities(v, e);
+  ray_quantities(v, m.unit, e);
   e->thR = x;
   e->thI = y;
   const double h = el ? 0.0 : homog_residual(v);

@@ -64,6 +64,7 @@ inline F fmax(F a, F b) { return F(::fmax(a.v, b.v)); }
 inline F copysign(F a, F b) { return F(::copysign(a.v, b.v)); }
 inline F floor(F a) { return F(::floor(a.v)); }
 inline F fmod(F a, F b) { return F(::fmod(a.v, b.v)); }
+inline F ldexp(F a, int e) { return F(::ldexp(a.v, e)); }
 inline F expm1(F a) { ++opc::g.trans; return F(::expm1(a.v)); }
 inline F atan2(F a, F b) { ++opc::g.trans; return F(::atan2(a.v, b.v)); }
 inline void sincos(F a, F* s, F* c) {
@@ -132,7 +133,7 @@ int main() {
           ++n_t;
           t_ok += ok;
           Entry en;
-          ray_quantities(ve, &en);
+          ray_quantities(ve, m.unit, &en);
           F h = homog_residual(ve);
           (void)h;
           opc::Counts c3 = take();
@@ -194,7 +195,7 @@ int main() {
         if (ok) {
           const Vel v = energy_velocity(m, mode, sp.kernel, x, y);
           Entry e;
-          ray_quantities(v, &e);
+          ray_quantities(v, m.unit, &e);
           const F h = el ? F(0.0) : homog_residual(v);
           e.res = fmax(fabs(h), fabs(wrap_pi(ray_angle(v) - psi)));
         }

@@ -94,3 +94,16 @@ def test_surrogate_start_leaves_cancelled_attenuation_to_the_plain_search(host):
     same = ok & (b[:, 2] == 0) & (np.abs(b[:, 6] - b[:, 3]) < 1e-6 * b[:, 3])
     assert same.sum() > 5000
     assert (np.abs(b[same, 7] - b[same, 4]) / np.abs(b[same, 4])).max() <= 1e-10
+
+
+@pytest.mark.parametrize("power", [-200, -50, -13, 13, 50, 200])
+@pytest.mark.parametrize("mode,kernel", [(0, 0), (1, 0), (1, 1), (2, 1)])
+def test_the_unit_of_the_moduli_does_not_matter(host, mode, kernel, power):
+    """Moduli times a power of four: the same angles and residuals to the last
+    bit, so the same brackets, roots and misses, whatever the unit."""
+    cls = layer_classes(6, 7)
+    scaled = cls.copy()
+    scaled[:, :5] = np.ldexp(cls[:, :5], 2 * power)
+    a = host(cls, mode, kernel, n_dirs=72)
+    assert len(a) > 200
+    np.testing.assert_array_equal(a, host(scaled, mode, kernel, n_dirs=72))
