@@ -24,6 +24,7 @@
 
 #include "chert.h"
 #include "chert_internal.h"
+#include "job_lists.h"
 #include "mlp.h"
 #include "physics.h"
 #include "solve.h"
@@ -484,9 +485,9 @@ struct WarmArgs {
   int32_t* win;                 // [jobs] 1: directions near a fold, for k_warm_window
   uint32_t* fold;               // [jobs][kFoldWords] fold bins (until k_warm_window: in brs)
   // Fold directions and their brackets, in `parts` lists of dir_cap and br_cap
-  // entries each (a workgroup appends to list blockIdx mod parts: returning
-  // atomics on one address serialise across the chip); len[part]: entries,
-  // directions << 32 | brackets, a 128-byte line each.
+  // entries each, a job's in list list_of_job (returning atomics on one address
+  // serialise across the chip); len[part]: entries, directions << 32 | brackets,
+  // a 128-byte line each.
   int parts;
   unsigned long long* len;
   int4* dirs;                   // (job, sidx, first bracket, brackets)
@@ -924,7 +925,7 @@ k_warm_window(WarmArgs w, int64_t n_jobs) {
       });
       if (f0 + lane < nflag) s_nbr[f0 + lane] = (uint16_t)nbr;
     }
-    const int part = (int)(job % w.parts);
+    const int part = list_of_job(job, w.parts);
     unsigned long long at = 0;
     if (lane == 0)
       at = atomicAdd(&w.len[part * kLenStride],
