@@ -3,9 +3,9 @@
 //   k_sweep: one lane per (mode, class, theta_R sample); solves the inner
 //            homogeneity root theta_I(theta_R) (eq 9) by the outward scan and
 //            stores (theta_I, local ray angle) in the sweep table.
-//   k_solve: one workgroup per (mode, class, 64 target directions); stages
-//            the class's sweep table in LDS, brackets every theta_R whose ray
-//            angle crosses the target, refines each root with a 2D Newton
+//   k_solve: one workgroup per (mode, class, 16 or 256 target directions);
+//            stages the class's sweep table in LDS, brackets every theta_R whose
+//            ray angle crosses the target, refines each root with a 2D Newton
 //            iteration on (homogeneity residual, ray-direction miss), keeps
 //            the largest ray velocity (first arrival) and writes the entry and
 //            its centrosymmetric copy (eqs 10-11).
@@ -233,7 +233,7 @@ __device__ __forceinline__ int32_t class_block(const chert_class& c, int mode) {
 // spills a few registers and still beats one without spills: 270 -> 206 us)
 // since the directions test chunk ranges instead of all 1440 intervals: the
 // 41,253-direction cache of 6 classes x 2 modes went from 2.17 ms to 0.23 ms,
-// the 5-class 2D cache from 117 to 70 us.
+// the 5-class 2D cache from 117 to 59 us.
 constexpr int kSolveSlots = 3;
 constexpr int kSolveThreads = 256;
 struct SolveCand {
@@ -331,11 +331,12 @@ k_solve(SolveArgs a) {
 // (mode, class) sweeps half of theta_R into LDS, then solves that class's
 // directions; no sweep table in HBM.  One wavefront: a job has some 40
 // directions, so of 256 threads 216 were idle in the solves (10,201 nodes x 2
-// modes: 7.7 ms with 256 and all samples, 6.2 with 128 and half of them, 5.2
-// with 64).  Its directions test every interval, without k_solve's chunk
-// ranges (1.2 ms there): the surrogate-started build is held by its tests to a
-// quarter of this one's time (9,600 nodes: 0.46 ms against 2.6, 0.65 with the
-// ranges), and both are wanted.
+// modes: 7.7 ms with 256 threads and every sample solved, 6.2 with 128 and half
+// of them, 5.3 with 64).  Its directions test every sweep interval: with
+// k_solve's chunk ranges this build takes 1.2 ms, but the surrogate-started
+// build is required to take at most a quarter of this one's time, and does so
+// only without them (9,600 nodes, qSV: 0.49 ms against 2.33, and against 0.65
+// with the ranges).
 constexpr int kNodeThreads = 64;
 __global__ void __launch_bounds__(kNodeThreads) __attribute__((amdgpu_waves_per_eu(2)))
 k_build_fused(SolveArgs a, const int32_t* list,

@@ -17,14 +17,16 @@
 // round holds many cells).  The fixed point is the network's shortest-path
 // traveltimes whatever the schedule.
 //
-// 2D cached networks whose cells' keys fit in LDS run all rounds of a problem
-// in one workgroup (k_cell_march), several cells per wave, and the BFS below
-// likewise (k_cell_tree): a round there is a few microseconds of LDS work
-// instead of two launches whose loads all miss the caches.
+// Small 2D cached networks run all rounds of a problem in one workgroup
+// (k_cell_march), several cells per wave, and the BFS below runs likewise on
+// networks of all kinds (k_cell_tight, k_cell_tree): a round there is a few
+// microseconds of LDS work instead of two launches whose loads all miss the
+// caches.  march_pays and single_tree say where that is the faster form; a call
+// with an abort word, which the host polls between launches, never takes it.
 //
 // Predecessors and t*: level-synchronous BFS over tight segments
-// (tau_i + w_ij == tau_j) from the source, one launch per level, threads
-// over (node, boundary slot) pairs: pred_j = the tight neighbour one
+// (tau_i + w_ij == tau_j) from the source, one launch per level (or one
+// workgroup for all of them), threads over (node, boundary slot) pairs: pred_j = the tight neighbour one
 // level up with the smallest node
 // index (the smallest (hop, index) among all tight neighbours), t*_j =
 // t*_pred + the attenuation weight of that segment, each parent's value

@@ -2284,8 +2284,8 @@ extern "C" int chert_trace_autotune(const chert_trace_job* jobs, int32_t n_jobs,
     }
   };
   for (const chert_trace_opts& c : cands) consider(c);
-  // 2D tiles: then the ordering width for the fastest shape (the 3D tiles
-  // have no ordering)
+  // 2D tiles: then the ordering width for the fastest shape (large 3D batches
+  // order their tiles by themselves)
   if (tried > 0 && pick.launch != CHERT_LAUNCH_FRONTIER && !three_d)
     for (double bw : kTuneTileBuckets) {
       chert_trace_opts c = pick;
