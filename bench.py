@@ -52,13 +52,13 @@ FP64_VALU_PEAK_TOPS = 39.3  # 256 CUs x 4 SIMDs x 16 FP64 lanes x 2.4 GHz, one o
 # Valid only for the kernel source it was measured on.
 MEASURED_TRAFFIC = {
     "source": "paper_2609_26108_amd/csrc/trace.hip",
-    "source_sha256_16": "c3d68e8c76134a9d",
+    "source_sha256_16": "7c3c6abca29224b1",
     "fetch_scale": 2.0, "write_scale": 1.0,
     # workload -> kernel -> (FETCH_SIZE KiB, WRITE_SIZE KiB) per dispatch
     # (profiles/k_relax_tau__shots_4_grids_per_node.md: one step, 16 x 64
     # tiles, push group 4, 112 dispatches of each relaxation kernel)
-    "kib_per_dispatch": {"shots": {"k_relax_tau": (824262.62, 11104.91),
-                                   "k_relax_tree": (305617.93, 94374.55)}},
+    "kib_per_dispatch": {"shots": {"k_relax_tau": (814294.32, 11306.94),
+                                   "k_relax_tree": (350012.59, 94666.25)}},
 }
 
 
@@ -84,9 +84,9 @@ def measured_traffic_bytes(kernel, workload="layered"):
 MEASURED_FP64 = {
     "sources": ["paper_2609_26108_amd/csrc/cache_build.hip",
                 "paper_2609_26108_amd/csrc/physics.h", "paper_2609_26108_amd/csrc/mlp.h"],
-    "sources_sha256_16": "174eaadc021096df",
-    "flops_per_dispatch": {"k_warm_solve": 1.1138e11, "k_warm_window": 6.1756e10,
-                           "k_warm_folds": 1.2707e10, "k_warm_fold": 6.2049e9,
+    "sources_sha256_16": "174f19893ebf1e9e",
+    "flops_per_dispatch": {"k_warm_solve": 1.1143e11, "k_warm_window": 6.1728e10,
+                           "k_warm_folds": 1.2707e10, "k_warm_fold": 6.1227e9,
                            "k_warm_predict": 4.0599e9},
 }
 
